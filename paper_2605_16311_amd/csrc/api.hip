@@ -593,7 +593,6 @@ int spectral_sigma(signmuon_ctx* ctx, ns_plan* pl, int buf, int items, int items
     D.v = scratch + (long long)items * up;
     D.part = D.v + (long long)items * cl.cp;
     D.chunks = chunks;
-    D.pad_ = 0;
     scratch += (long long)items * (up + (long long)cl.cp * (1 + (cl.rows + SM_PI_FUSED_ROWS - 1) / SM_PI_FUSED_ROWS));
     D.sigma = at<float>(ctx, cl.off_sig) + first;
     D.rows = cl.rows;
@@ -601,7 +600,6 @@ int spectral_sigma(signmuon_ctx* ctx, ns_plan* pl, int buf, int items, int items
     D.ld = cl.cp;
     D.up = up;
     D.items = items;
-    D.block_begin = 0;
   }
   return sm_launch_power_iter_group(ctx, d.data(), n, P, eps);
 }
@@ -620,8 +618,6 @@ int class_inv_sigma(signmuon_ctx* ctx, ns_plan* pl, int items, int mode, float e
     D.count = cl.count * items;
     D.mode = mode;
     D.value = 1.0f / fmaxf(sqrtf((float)cl.rows * (float)cl.cols), eps);
-    D.block_begin = 0;
-    D.pad_ = 0;
     d.push_back(D);
   }
   return sm_launch_sigma_group(ctx, d.data(), (int)d.size(), eps);
@@ -642,7 +638,7 @@ int clear_padding(signmuon_ctx* ctx, ns_plan* pl, int buf, F items_per_class) {
     D.rp = cl.rp;
     D.cp = cl.cp;
     D.items = items_per_class(cl);
-    D.blocks_per_item = D.block_begin = D.pad_ = 0;
+    D.blocks_per_item = 0;
     d.push_back(D);
   }
   if (d.empty()) return SM_OK;
@@ -672,7 +668,7 @@ static int momentum_one(signmuon_ctx* ctx, float* mom, const float* grad, const 
   D.cols = cols;
   D.ld = cols;
   D.chunks = chunks;
-  D.block_begin = 0;
+  D.pad_ = 0;
   int rc = sm_launch_momentum(ctx, &D, 1, M, beta, weight_decay);
   if (rc != SM_OK) return rc;
   if (sumsq) return sm_launch_reduce_partials(ctx, partial_buf, chunks, M, sumsq);
@@ -880,7 +876,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     D.cols = cl.cols;
     D.ld = cl.cp;
     D.chunks = cl.chunks;
-    D.block_begin = 0;
+    D.pad_ = 0;
   }
   rc = sm_launch_momentum(ctx, descs.data(), n, M, s->beta, s->weight_decay);
   if (rc != SM_OK) return rc;
@@ -955,7 +951,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
       S.bytes_per_row = 0;
       S.cols = cl.cols;
       S.ld = cl.cp;
-      S.blocks_per_row = S.block_begin = 0;
+      S.blocks_per_row = S.pad_ = 0;
       sp.push_back(S);
     }
     float step = s->lr;
@@ -967,7 +963,6 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     V.counts = (s->counts_out) ? s->counts_out[i] : nullptr;
     V.lr = step;
     V.M = M;
-    V.block_begin = 0;
     if (Kp == 0 && !op_norm) {
       V.voted = nullptr;
       V.vfmt = SM_VOTE_BF16;
@@ -1046,8 +1041,6 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     ud[i].cols = cl.cols;
     ud[i].ld = cl.cp;
     ud[i].step = step;
-    ud[i].block_begin = 0;
-    ud[i].pad_ = 0;
     if (s->d_out && s->d_out[i]) {
       rc = sm_launch_copy_out(ctx, dmat, cl.cp, cl.mat, 1, cl.rows, cl.cols, s->d_out[i], SM_BF16, nullptr);
       if (rc != SM_OK) return rc;

@@ -89,6 +89,32 @@ int sm_aux_reserve(signmuon_ctx* ctx, size_t bytes);
 static inline int64_t sm_round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 static inline bool sm_aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+// ---------------------------------------------------------------- descriptor tables
+// Grouped launches carry their table in the kernel arguments, which lie in host memory: every cache line of it
+// that a compute unit reads costs about a microsecond, one after the other where an address depends on what the
+// line before it held.  A workgroup finds its entry from the entries' first workgroups, which therefore stand side
+// by side (unused ones INT_MAX) and are compared sixteen at a time; walking the descriptors themselves took 6.8 us
+// per launch of 24 entries against 3.2 us.
+template <int N>
+struct sm_starts {
+  static_assert(N % 16 == 0, "compared sixteen at a time");
+  int v[N];
+};
+template <int N>
+static inline void sm_starts_clear(sm_starts<N>& s) {
+  for (int i = 0; i < N; ++i) s.v[i] = 0x7FFFFFFF;
+}
+// Largest i with v[i] <= bx, among the first n entries (v[0] <= bx).
+template <int N>
+__device__ __forceinline__ int sm_find(const sm_starts<N>& s, int n, int bx) {
+  int at = -1;
+  for (int i = 0; i < n; i += 16) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) at += (bx >= s.v[i + k]) ? 1 : 0;
+  }
+  return at;
+}
+
 // ---------------------------------------------------------------- streaming kernels (stream.hip)
 // Descriptor of one weight block for the grouped momentum launch.
 struct sm_mom_desc {
@@ -101,9 +127,9 @@ struct sm_mom_desc {
   long long x_stride;  // elements between workers in x
   int cols, ld;        // logical row length and padded row length of x
   int chunks;          // chunks per worker
-  int block_begin;     // first workgroup of this block in the grouped launch
+  int pad_;
 };
-constexpr int SM_MOM_MAX_GROUP = 52;  // blocks per launch: the table rides in the kernel arguments (4 KB at most)
+constexpr int SM_MOM_MAX_GROUP = 48;  // blocks per launch: the table rides in the kernel arguments (4 KB at most)
 constexpr int SM_MOM_CHUNK = 1024;  // elements per workgroup: one 16-byte piece per thread (short-lived workgroups
                                     // keep the four streams of the momentum update close together in memory)
 
@@ -121,8 +147,6 @@ struct sm_sigma_desc {
   float* inv;
   int chunks, count, mode;
   float value;
-  int block_begin;  // filled by the launcher
-  int pad_;
 };
 constexpr int SM_SIGMA_MAX_GROUP = 64;
 int sm_launch_sigma_group(signmuon_ctx* ctx, const sm_sigma_desc* descs, int n, float eps);
@@ -136,7 +160,8 @@ struct sm_sp_desc {
   long long out_stride;     // bytes
   long long bytes_per_row;  // filled by the launcher
   int cols, ld;
-  int blocks_per_row, block_begin;  // filled by the launcher
+  int blocks_per_row;  // filled by the launcher
+  int pad_;
 };
 constexpr int SM_SP_MAX_GROUP = 48;
 int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n, int dtype, int fmt, int M);
@@ -150,7 +175,6 @@ struct sm_vote_desc {
   float* w;
   float lr;
   int M, vfmt, cols, ld;
-  int block_begin;   // filled by the launcher
 };
 constexpr int SM_VOTE_MAX_GROUP = 48;
 int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, int fmt);
@@ -162,8 +186,6 @@ struct sm_upd_desc {
   const float* kappa;  // optional device scalar multiplied into step
   int rows, cols, ld;
   float step;
-  int block_begin;   // filled by the launcher
-  int pad_;
 };
 constexpr int SM_UPD_MAX_GROUP = 64;
 int sm_launch_update_group(signmuon_ctx* ctx, const sm_upd_desc* descs, int n);
@@ -203,8 +225,7 @@ struct sm_pad_desc {
   long long stride;
   int rows, cols, rp, cp;
   int items;
-  int blocks_per_item, block_begin;  // filled by the launcher
-  int pad_;
+  int blocks_per_item;  // filled by the launcher
 };
 constexpr int SM_PAD_MAX_GROUP = 64;
 int sm_launch_pad_clear(signmuon_ctx* ctx, const sm_pad_desc* descs, int n);
@@ -232,7 +253,6 @@ struct sm_gemm_prob {
   int lda, ldb, ldc;
   int batch;
   int tiles_m, tiles_n;  // filled by the launcher
-  int tile_begin;        // filled by the launcher
   int layout;            // bit 0: A stored [K][M] (lda = its row length), bit 1: B stored [K][N]
   // Optional sign output of a general (non-symmetric) bf16 product: the signs (x >= 0) of the
   // leading sign_rows x sign_cols part of C[b], packed row-major into
@@ -250,7 +270,9 @@ struct sm_gemm_prob {
   int mu, nu, ku;
 };
 constexpr int SM_GEMM_MAX_PROB = 24;
+constexpr int SM_GEMM_STARTS = 32;
 struct sm_gemm_args {
+  sm_starts<SM_GEMM_STARTS> tile_begin;  // first tile of every problem; filled by the launcher
   int n_prob;
   int total_tiles;
   int xcd_begin[9];  // XCD x owns tiles [xcd_begin[x], xcd_begin[x + 1]) of the tile list
@@ -263,6 +285,7 @@ struct sm_gemm_args {
   int reverse;       // an XCD walks its range of the tile list from the end (set by the launcher: every other launch)
   sm_gemm_prob p[SM_GEMM_MAX_PROB];
 };
+static_assert(sizeof(sm_gemm_args) <= 4096, "kernel arguments are limited to 4 KB");
 // One grouped launch over the problem table.  sym: every problem's output is symmetric (M == N;
 // layout 0 or 3): only the upper triangle of tiles is computed and stored mirrored.  Otherwise
 // layout 0 or 2.  Half-precision operands need sym and layout 0.  klass is the profiling class
@@ -284,8 +307,6 @@ struct sm_pi_desc {
   int up;               // rows rounded up to a multiple of 8
   int items;
   int chunks;           // ceil(rows / SM_PI_ROW_CHUNK)
-  int block_begin;      // filled by the launcher
-  int pad_;
 };
 constexpr int SM_PI_MAX_GROUP = 40;
 constexpr int SM_PI_ROW_CHUNK = 128;

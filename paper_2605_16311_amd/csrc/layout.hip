@@ -69,16 +69,16 @@ __global__ void __launch_bounds__(TPB) sm_sumsq_kernel(const void* __restrict__ 
 struct pad_args {
   int n;
   int pad_;
+  sm_starts<SM_PAD_MAX_GROUP> begin;
   sm_pad_desc d[SM_PAD_MAX_GROUP];
 };
 
 // Zero padding of the working layout: thread = one padding element of one matrix, first the strip to the
 // right of the logical columns (row by row), then the rows below the logical ones.
 __global__ void __launch_bounds__(TPB) sm_pad_clear_kernel(const pad_args a) {
-  int di = 0;
-  while (di + 1 < a.n && (int)blockIdx.x >= a.d[di + 1].block_begin) ++di;
+  const int di = sm_find(a.begin, a.n, blockIdx.x);
   const sm_pad_desc& D = a.d[di];
-  const int local = blockIdx.x - D.block_begin;
+  const int local = blockIdx.x - a.begin.v[di];
   const int item = local / D.blocks_per_item;
   const long long e = (long long)(local - item * D.blocks_per_item) * TPB + threadIdx.x;
   const int pc = D.cp - D.cols;
@@ -102,6 +102,7 @@ int sm_launch_pad_clear(signmuon_ctx* ctx, const sm_pad_desc* descs, int n) {
   while (done < n) {
     const int g = std::min(n - done, SM_PAD_MAX_GROUP);
     pad_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
     long long blocks = 0;
@@ -110,7 +111,7 @@ int sm_launch_pad_clear(signmuon_ctx* ctx, const sm_pad_desc* descs, int n) {
       D = descs[done + i];
       const long long total = (long long)D.rows * (D.cp - D.cols) + (long long)(D.rp - D.rows) * D.cp;
       D.blocks_per_item = (int)((total + TPB - 1) / TPB);
-      D.block_begin = (int)blocks;
+      a.begin.v[i] = (int)blocks;
       blocks += (long long)D.blocks_per_item * D.items;
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "padding clear: too many elements for one launch");

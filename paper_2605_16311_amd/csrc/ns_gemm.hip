@@ -725,9 +725,9 @@ __global__ void __launch_bounds__(NTH) sm_ns_gemm_kernel(const sm_gemm_args args
     const int L = args.reverse ? xcd_first + xcd_end - 1 - Lf : Lf;
     if (!first_tile) __syncthreads();  // the previous tile has been read out of the stage arrays
     first_tile = false;
-    int pi = 0;
-    while (pi + 1 < args.n_prob && L >= args.p[pi + 1].tile_begin) ++pi;
-    int t = L - args.p[pi].tile_begin;
+    // (a mate owns no tiles: it begins where the problem after it does, and the last of equal starts is found)
+    int pi = sm_find(args.tile_begin, args.n_prob, L);
+    int t = L - args.tile_begin.v[pi];
     const int per_batch = SYM ? args.p[pi].tiles_m * (args.p[pi].tiles_m + 1) / 2 : args.p[pi].tiles_m * args.p[pi].tiles_n;
     const int mate = args.p[pi].mate;
     const int per_item = mate ? 2 * per_batch : per_batch;
@@ -765,6 +765,7 @@ static int fill_tiles(sm_gemm_args& args, bool sym, int ts) {
   constexpr double FIXED = 6.0;
   int total = 0;
   double cost = 0.0;
+  sm_starts_clear(args.tile_begin);
   bool is_mate[SM_GEMM_MAX_PROB] = {};
   for (int i = 0; i < args.n_prob; ++i)
     if (args.p[i].mate) is_mate[args.p[i].mate] = true;
@@ -772,7 +773,7 @@ static int fill_tiles(sm_gemm_args& args, bool sym, int ts) {
     sm_gemm_prob& P = args.p[i];
     P.tiles_m = (P.M + ts - 1) / ts;
     P.tiles_n = (P.N + ts - 1) / ts;
-    P.tile_begin = total;  // for a mate: the end of its leader's range, which the tile lookup steps over
+    args.tile_begin.v[i] = total;  // for a mate: the end of its leader's range, which the tile lookup steps over
     if (is_mate[i]) continue;
     const int n = (sym ? P.tiles_m * (P.tiles_m + 1) / 2 : P.tiles_m * P.tiles_n) * P.batch * (P.mate ? 2 : 1);
     total += n;
@@ -784,15 +785,16 @@ static int fill_tiles(sm_gemm_args& args, bool sym, int ts) {
   double done = 0.0;  // cost of the problems before pi
   while (x < 8 && pi < args.n_prob) {
     const sm_gemm_prob& P = args.p[pi];
-    const int end = (pi + 1 < args.n_prob) ? args.p[pi + 1].tile_begin : total;  // == tile_begin for a mate
+    const int begin = args.tile_begin.v[pi];
+    const int end = (pi + 1 < args.n_prob) ? args.tile_begin.v[pi + 1] : total;  // == begin for a mate
     const double per_tile = P.K / 64 + FIXED, target = cost * x / 8;
-    const double here = done + (double)(end - P.tile_begin) * per_tile;
+    const double here = done + (double)(end - begin) * per_tile;
     if (here < target) {
       done = here;
       ++pi;
       continue;
     }
-    int cut = P.tile_begin + (int)((target - done) / per_tile + 0.5);
+    int cut = begin + (int)((target - done) / per_tile + 0.5);
     cut = std::min(std::max(cut, args.xcd_begin[x - 1]), end);
     args.xcd_begin[x++] = cut;
   }
@@ -822,7 +824,7 @@ extern "C" int signmuon_debug_tile_ranges(int n_prob, const int* M, const int* N
   }
   fill_tiles(a, sym != 0, ts);
   for (int x = 0; x < 9; ++x) xcd_begin[x] = a.xcd_begin[x];
-  for (int i = 0; i < n_prob; ++i) tile_begin[i] = a.p[i].tile_begin;
+  for (int i = 0; i < n_prob; ++i) tile_begin[i] = a.tile_begin.v[i];
   return a.total_tiles;
 }
 

@@ -20,9 +20,11 @@ namespace {
 
 constexpr int TPB = 256;
 
+constexpr int SM_PI_STARTS = (SM_PI_MAX_GROUP + 15) / 16 * 16;
 struct pi_args {
   int n;
   float eps;
+  sm_starts<SM_PI_STARTS> begin;
   sm_pi_desc d[SM_PI_MAX_GROUP];
 };
 
@@ -33,9 +35,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 __device__ __forceinline__ const sm_pi_desc& find_desc(const pi_args& a, int bx, int& local) {
-  int di = 0;
-  while (di + 1 < a.n && bx >= a.d[di + 1].block_begin) ++di;
-  local = bx - a.d[di].block_begin;
+  const int di = sm_find(a.begin, a.n, bx);
+  local = bx - a.begin.v[di];
   return a.d[di];
 }
 
@@ -321,14 +322,15 @@ static int power_iter_fused(signmuon_ctx* ctx, const sm_pi_desc* descs, int n, i
     for (pi_args* a : {&a_pass, &a_nrm}) {
       a->n = g;
       a->eps = eps;
+      sm_starts_clear(a->begin);
     }
     for (int i = 0; i < g; ++i) {
       const sm_pi_desc& d = descs[done + i];
       if (d.ld % 64 || d.up % 8 || d.up < d.rows || !sm_aligned(d.x, 16) || d.stride % 8 || !sm_aligned(d.v, 16))
         return sm_fail(ctx, SM_EINVAL, "internal: power iteration operands not padded/aligned");
       a_pass.d[i] = a_nrm.d[i] = d;
-      a_pass.d[i].block_begin = (int)b_pass;
-      a_nrm.d[i].block_begin = (int)b_nrm;
+      a_pass.begin.v[i] = (int)b_pass;
+      a_nrm.begin.v[i] = (int)b_nrm;
       b_pass += (long long)((d.rows + SM_PI_FUSED_ROWS - 1) / SM_PI_FUSED_ROWS) * d.items;
       b_nrm += d.items;
     }
@@ -398,6 +400,7 @@ int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n
     for (pi_args* a : {&a_xv, &a_xtu, &a_nrm}) {
       a->n = g;
       a->eps = eps;
+      sm_starts_clear(a->begin);
     }
     for (int i = 0; i < g; ++i) {
       const sm_pi_desc& d = descs[done + i];
@@ -405,9 +408,9 @@ int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n
       if (d.ld % 64 || d.up % 8 || d.up < d.rows || !sm_aligned(d.x, 16) || d.stride % 8 || !sm_aligned(d.v, 16))
         return sm_fail(ctx, SM_EINVAL, "internal: power iteration operands not padded/aligned");
       a_xv.d[i] = a_xtu.d[i] = a_nrm.d[i] = d;
-      a_xv.d[i].block_begin = (int)b_xv;
-      a_xtu.d[i].block_begin = (int)b_xtu;
-      a_nrm.d[i].block_begin = (int)b_nrm;
+      a_xv.begin.v[i] = (int)b_xv;
+      a_xtu.begin.v[i] = (int)b_xtu;
+      a_nrm.begin.v[i] = (int)b_nrm;
       b_xv += (long long)((d.rows + 3) / 4) * d.items;
       b_xtu += (long long)((d.ld + 511) / 512) * d.chunks * d.items;
       b_nrm += d.items;

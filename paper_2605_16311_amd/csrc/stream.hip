@@ -33,12 +33,13 @@ __device__ __forceinline__ unsigned ge0_bf16(unsigned h) { return (h <= 0x7F80u)
 
 // ------------------------------------------------------------------ momentum
 // start[k]: the block that holds workgroup (k << shift) of the launch, so that a workgroup finds its
-// block in a step or two instead of walking the table (workgroups are short: the walk would show).
+// block in a step or two instead of comparing all starts (workgroups are short: that would show).
 struct mom_args {
   int n, M;
   float beta, omb, wd;
   int shift;
-  int start[64];
+  sm_starts<SM_MOM_MAX_GROUP> begin;
+  unsigned char start[64];
   sm_mom_desc d[SM_MOM_MAX_GROUP];
 };
 static_assert(sizeof(mom_args) <= 4096, "kernel arguments are limited to 4 KB");
@@ -52,9 +53,9 @@ template <bool VEC>
 __global__ void __launch_bounds__(TPB) sm_momentum_kernel(const mom_args a) {
   __shared__ float red[4];
   int bi = a.start[blockIdx.x >> a.shift];
-  while (bi + 1 < a.n && (int)blockIdx.x >= a.d[bi + 1].block_begin) ++bi;
+  while (bi + 1 < a.n && (int)blockIdx.x >= a.begin.v[bi + 1]) ++bi;
   const sm_mom_desc& D = a.d[bi];
-  const int local = blockIdx.x - D.block_begin;
+  const int local = blockIdx.x - a.begin.v[bi];
   const int p = local / D.chunks, ch = local - p * D.chunks;
   const long long d = D.d;
   float* mom = D.mom + (long long)p * d;
@@ -132,16 +133,16 @@ __global__ void sm_inv_sigma_kernel(const float* sig, int count, float eps, int 
 struct sigma_args {
   int n;
   float eps;
+  sm_starts<SM_SIGMA_MAX_GROUP> begin;
   sm_sigma_desc d[SM_SIGMA_MAX_GROUP];
 };
 
 // One workgroup per item of every class of the table.
 __global__ void __launch_bounds__(TPB) sm_sigma_group_kernel(const sigma_args a) {
   __shared__ float red[4];
-  int di = 0;
-  while (di + 1 < a.n && (int)blockIdx.x >= a.d[di + 1].block_begin) ++di;
+  const int di = sm_find(a.begin, a.n, blockIdx.x);
   const sm_sigma_desc& D = a.d[di];
-  const int i = blockIdx.x - D.block_begin;
+  const int i = blockIdx.x - a.begin.v[di];
   if (D.mode == 0) {
     const float* src = D.partial + (long long)i * D.chunks;
     float s = 0.f;
@@ -164,15 +165,15 @@ __global__ void __launch_bounds__(TPB) sm_sigma_group_kernel(const sigma_args a)
 struct sp_args {
   int n;
   int pad_;
+  sm_starts<SM_SP_MAX_GROUP> begin;
   sm_sp_desc d[SM_SP_MAX_GROUP];
 };
 
 template <int DT, int FMT, bool FAST>
 __global__ void __launch_bounds__(TPB) sm_sign_pack_kernel(const sp_args a) {
-  int di = 0;
-  while (di + 1 < a.n && (int)blockIdx.x >= a.d[di + 1].block_begin) ++di;
+  const int di = sm_find(a.begin, a.n, blockIdx.x);
   const sm_sp_desc& D = a.d[di];
-  const int local = blockIdx.x - D.block_begin;
+  const int local = blockIdx.x - a.begin.v[di];
   const int b = local / D.blocks_per_row, bx = local - b * D.blocks_per_row;
   const long long n = D.n, bytes_per_row = D.bytes_per_row;
   const int cols = D.cols, ld = D.ld;
@@ -237,10 +238,9 @@ constexpr int SPB_UNROLL = 2;
 
 template <int DT>
 __global__ void __launch_bounds__(TPB) sm_sign_pack_bits_kernel(const sp_args a) {
-  int di = 0;
-  while (di + 1 < a.n && (int)blockIdx.x >= a.d[di + 1].block_begin) ++di;
+  const int di = sm_find(a.begin, a.n, blockIdx.x);
   const sm_sp_desc& D = a.d[di];
-  const int local = blockIdx.x - D.block_begin;
+  const int local = blockIdx.x - a.begin.v[di];
   const int b = local / D.blocks_per_row, bx = local - b * D.blocks_per_row;
   const long long n = D.n, bytes_per_row = D.bytes_per_row;  // a multiple of 8: a 4-lane group is in range as a whole
   const int cols = D.cols, ld = D.ld;
@@ -423,6 +423,7 @@ typedef sm_vote_desc vote_x_args;
 struct vote_g_args {
   int n;
   int pad_;
+  sm_starts<SM_VOTE_MAX_GROUP> begin;
   sm_vote_desc d[SM_VOTE_MAX_GROUP];
 };
 
@@ -431,10 +432,9 @@ struct vote_g_args {
 // optional.  n4 = ceil(n/4) threads in total.
 template <int FMT>
 __global__ void __launch_bounds__(TPB) sm_vote_expand_kernel(const vote_g_args g) {
-  int di = 0;
-  while (di + 1 < g.n && (int)blockIdx.x >= g.d[di + 1].block_begin) ++di;
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
-  const long long t = (long long)(blockIdx.x - a.block_begin) * TPB + threadIdx.x;
+  const long long t = (long long)(blockIdx.x - g.begin.v[di]) * TPB + threadIdx.x;
   const long long e0 = t * 4;
   if (e0 >= a.n) return;
   int c[4] = {0, 0, 0, 0};
@@ -554,6 +554,7 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_bits_kernel(const signed cha
 struct upd_args {
   int n;
   int pad_;
+  sm_starts<SM_UPD_MAX_GROUP> begin;
   sm_upd_desc d[SM_UPD_MAX_GROUP];
 };
 
@@ -563,15 +564,14 @@ constexpr int UPD_ITERS = 4;
 constexpr int UPD_CHUNK = UPD_ITERS * TPB * 4;
 
 __global__ void __launch_bounds__(TPB) sm_update_kernel(const upd_args g) {
-  int di = 0;
-  while (di + 1 < g.n && (int)blockIdx.x >= g.d[di + 1].block_begin) ++di;
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
   const sm_upd_desc& D = g.d[di];
   float* __restrict__ w = D.w;
   const bf16_t* __restrict__ d = D.d;
   const int cols = D.cols, ld = D.ld;
   const float step = D.kappa ? __fmul_rn(D.step, D.kappa[0]) : D.step;
   const long long n = (long long)D.rows * cols;
-  const long long base = (long long)(blockIdx.x - D.block_begin) * UPD_CHUNK + threadIdx.x * 4;
+  const long long base = (long long)(blockIdx.x - g.begin.v[di]) * UPD_CHUNK + threadIdx.x * 4;
   if ((cols & 3) == 0 && base - threadIdx.x * 4 + UPD_CHUNK <= n) {  // a full chunk of whole groups of 4
     bf16x4 h[UPD_ITERS];
     f32x4 wv[UPD_ITERS];
@@ -623,6 +623,7 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
   while (done < n) {
     const int g = std::min(n - done, SM_MOM_MAX_GROUP);
     mom_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.M = M;
     a.beta = beta;
@@ -632,7 +633,7 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
     bool vec = true;
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
-      a.d[i].block_begin = (int)blocks;
+      a.begin.v[i] = (int)blocks;
       blocks += (long long)M * a.d[i].chunks;
       const sm_mom_desc& D = a.d[i];
       vec = vec && (D.d % 4 == 0) && sm_aligned(D.mom, 16) && sm_aligned(D.grad, 16) &&
@@ -642,8 +643,8 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
     a.shift = 0;
     while ((blocks >> a.shift) >= 64) ++a.shift;
     for (int k = 0, bi = 0; k < 64; ++k) {
-      while (bi + 1 < g && ((long long)k << a.shift) >= a.d[bi + 1].block_begin) ++bi;
-      a.start[k] = bi;
+      while (bi + 1 < g && ((long long)k << a.shift) >= a.begin.v[bi + 1]) ++bi;
+      a.start[k] = (unsigned char)bi;
     }
     if (blocks > 0) {
       sm_launch_scope sc(ctx, SM_K_MOMENTUM);
@@ -678,12 +679,13 @@ int sm_launch_sigma_group(signmuon_ctx* ctx, const sm_sigma_desc* descs, int n, 
   while (done < n) {
     const int g = std::min(n - done, SM_SIGMA_MAX_GROUP);
     sigma_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.eps = eps;
     int blocks = 0;
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
-      a.d[i].block_begin = blocks;
+      a.begin.v[i] = blocks;
       blocks += a.d[i].count;
     }
     if (blocks > 0) {
@@ -701,6 +703,7 @@ int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n,
   while (done < n) {
     const int g = std::min(n - done, SM_SP_MAX_GROUP);
     sp_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
     int blocks = 0;
@@ -719,7 +722,7 @@ int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n,
     for (int i = 0; i < g; ++i) {
       sm_sp_desc& D = a.d[i];
       D.blocks_per_row = (int)((D.bytes_per_row + per_block - 1) / per_block);
-      D.block_begin = blocks;
+      a.begin.v[i] = blocks;
       blocks += D.blocks_per_row * M;
     }
     if (blocks > 0) {
@@ -765,7 +768,6 @@ int sm_launch_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, 
   D.cols = cols;
   D.ld = ld;
   D.blocks_per_row = 0;
-  D.block_begin = 0;
   return sm_launch_sign_pack_group(ctx, &D, 1, dtype, fmt, batch);
 }
 
@@ -811,7 +813,6 @@ int sm_launch_vote(signmuon_ctx* ctx, const sm_vote_args& v) {
     a.vfmt = v.vfmt;
     a.cols = v.cols;
     a.ld = v.ld;
-    a.block_begin = 0;
     return sm_launch_vote_group(ctx, &a, 1, v.fmt);
   }
   return SM_OK;
@@ -831,13 +832,12 @@ constexpr int VW_GROUPS = 1;
 
 template <int PLANES>
 __global__ void __launch_bounds__(TPB) sm_vote_wide_kernel(const vote_g_args g) {
-  int di = 0;
-  while (di + 1 < g.n && (int)blockIdx.x >= g.d[di + 1].block_begin) ++di;
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
   const long long words = a.n >> 5;
   const int lane = threadIdx.x & 63;
   // the wave's first word: a workgroup covers TPB * VW_GROUPS words
-  const long long wbase = ((long long)(blockIdx.x - a.block_begin) * TPB + (threadIdx.x & ~63)) * VW_GROUPS;
+  const long long wbase = ((long long)(blockIdx.x - g.begin.v[di]) * TPB + (threadIdx.x & ~63)) * VW_GROUPS;
   const long long stride_w = a.stride_bytes >> 2;
   const unsigned* sbase = reinterpret_cast<const unsigned*>(a.signs);
   unsigned plane[VW_GROUPS][PLANES];
@@ -915,10 +915,9 @@ __global__ void __launch_bounds__(TPB) sm_vote_wide_kernel(const vote_g_args g) 
 // worker), int32 sums, then any of: counts, voted int8 / bf16 (flat), fused W update.  For tables whose
 // entries have n % 16 == 0 and 16-byte aligned rows.
 __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_args g) {
-  int di = 0;
-  while (di + 1 < g.n && (int)blockIdx.x >= g.d[di + 1].block_begin) ++di;
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
-  const long long t = (long long)(blockIdx.x - a.block_begin) * TPB + threadIdx.x;
+  const long long t = (long long)(blockIdx.x - g.begin.v[di]) * TPB + threadIdx.x;
   const long long e0 = t * 16;
   if (e0 >= a.n) return;
   int c[16];
@@ -978,6 +977,7 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
   while (done < n) {
     const int g = std::min(n - done, SM_VOTE_MAX_GROUP);
     vote_g_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
     // the wide kernel serves tables made only of whole 32-entry words, bf16 flat outputs, no counts
@@ -1002,7 +1002,7 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
-      a.d[i].block_begin = (int)blocks;
+      a.begin.v[i] = (int)blocks;
       const long long threads = wide ? (a.d[i].n / 32 + VW_GROUPS - 1) / VW_GROUPS : wide8 ? a.d[i].n / 16 : (a.d[i].n + 3) / 4;
       blocks += (threads + TPB - 1) / TPB;
     }
@@ -1034,12 +1034,13 @@ int sm_launch_update_group(signmuon_ctx* ctx, const sm_upd_desc* descs, int n) {
   while (done < n) {
     const int g = std::min(n - done, SM_UPD_MAX_GROUP);
     upd_args a;
+    sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
-      a.d[i].block_begin = (int)blocks;
+      a.begin.v[i] = (int)blocks;
       blocks += ((long long)a.d[i].rows * a.d[i].cols + UPD_CHUNK - 1) / UPD_CHUNK;
     }
     if (blocks > 0) {
@@ -1061,7 +1062,5 @@ int sm_launch_update(signmuon_ctx* ctx, float* w, const bf16_t* d, int rows, int
   D.ld = ld;
   D.kappa = nullptr;
   D.step = step;
-  D.block_begin = 0;
-  D.pad_ = 0;
   return sm_launch_update_group(ctx, &D, 1);
 }
