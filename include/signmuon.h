@@ -83,7 +83,7 @@ int signmuon_destroy(signmuon_ctx* ctx);
 /* Tuning switches of a context.  Every setting computes the same path within the
  * same tolerances; they exist for measurements and tests.  Values other than the
  * listed ones give SM_EINVAL. */
-#define SM_OPT_GEMM_TILE 0 /* workgroup tile of the Newton-Schulz GEMMs: 0 = by launch size (default), 128, 256 */
+#define SM_OPT_GEMM_TILE 0 /* workgroup tile of the Newton-Schulz GEMMs: 0 = by launch size (default), 64, 128, 256 */
 #define SM_OPT_NS_PATH 1   /* how the K steps of the cubic iteration are grouped: */
 #define SM_NS_PATH_PAIRS 0    /*   short-side recurrence, two steps per quartic (default) */
 #define SM_NS_PATH_SINGLE 1   /*   short-side recurrence, one step at a time */

@@ -107,6 +107,7 @@ static inline void sm_starts_clear(sm_starts<N>& s) {
 // Largest i with v[i] <= bx, among the first n entries (v[0] <= bx).
 template <int N>
 __device__ __forceinline__ int sm_find(const sm_starts<N>& s, int n, int bx) {
+  if (n == 1) return 0;
   int at = -1;
   for (int i = 0; i < n; i += 16) {
 #pragma unroll
@@ -286,6 +287,12 @@ struct sm_gemm_args {
   sm_gemm_prob p[SM_GEMM_MAX_PROB];
 };
 static_assert(sizeof(sm_gemm_args) <= 4096, "kernel arguments are limited to 4 KB");
+// Output tiles of a launch at tile sizes 64, 128 and 256, and the tile size it gets.
+struct sm_tile_count {
+  double tiles[3] = {0, 0, 0};
+  void add(int M, int N, int batch, bool sym);
+};
+int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c);
 // One grouped launch over the problem table.  sym: every problem's output is symmetric (M == N;
 // layout 0 or 3): only the upper triangle of tiles is computed and stored mirrored.  Otherwise
 // layout 0 or 2.  Half-precision operands need sym and layout 0.  klass is the profiling class

@@ -54,7 +54,16 @@
 
 namespace sm_gemm {
 
-constexpr int BK = 64, NTH = 512;
+constexpr int BK = 64;
+
+// Shape of a workgroup by tile size: waves in two rows of NW / 2, each with a WM x WN sub-tile of FM x FN
+// accumulators of 32 x 32, and NLOAD wave-loads of 1 KB per operand, wave and slice.
+template <int TS>
+struct tile_shape {
+  static constexpr int NW = (TS == 64) ? 4 : 8, NTH = NW * 64;
+  static constexpr int WM = TS / 2, WN = TS / (NW / 2), FM = WM / 32, FN = WN / 32, NLOAD = TS / 8 / NW;
+  static constexpr int STAGES = (TS == 64) ? 3 : 2;
+};
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
@@ -72,8 +81,11 @@ __device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* p) {
 // Per-lane constants of one operand: where its global->LDS loads read, where its fragments sit.
 template <bool MN, int TS>
 struct operand_lane {
-  static constexpr int NLOAD = TS / 64;  // wave-loads of this operand per wave and slice
+  static constexpr int NLOAD = tile_shape<TS>::NLOAD;  // wave-loads of this operand per wave and slice
   static constexpr int ROWB = TS * 2;    // MN: bytes per k-row
+  // MN: the 16-byte chunk c of k-row k sits at slot c ^ mn_swizzle(k), which spreads the four k-rows that 32 lanes
+  // read together over the 256 bytes of LDS banks (one row fills them at TS >= 128, two rows at TS = 64)
+  static __device__ __forceinline__ int mn_swizzle(int k) { return TS == 64 ? 4 * ((k >> 1) & 1) : 4 * (k & 3); }
   int voff[NLOAD];  // byte offset of this lane's wave-loads inside the operand (slice offset is scalar)
   int frag_off;     // KC: LDS byte offset of this lane's row in fragment 0
   int frag_mn[4];   // MN: LDS byte offset of fragment f (k-step 0, first half) for this lane
@@ -100,7 +112,7 @@ struct operand_lane {
 #pragma unroll
       for (int q = 0; q < NLOAD; ++q) {
         const int k = KPL * (NLOAD * wv + q) + lane / LPR;
-        const int chunk = (lane % LPR) ^ (4 * (k & 3));
+        const int chunk = (lane % LPR) ^ mn_swizzle(k);
         voff[q] = (k * ld + min(row0 + chunk * 8, rows - 8)) * 2;
       }
       // transposed read: 16-lane group g16, lane i in it; the group covers columns 16 (g16 & 1) ..+15
@@ -110,7 +122,7 @@ struct operand_lane {
       const int k = 8 * (g16 >> 1) + (i >> 2);
 #pragma unroll
       for (int f = 0; f < 4; ++f)  // fragment f lies 32 columns further
-        frag_mn[f] = k * ROWB + ((((col + 32 * f) >> 3) ^ (4 * (i >> 2))) << 4) + (col & 7) * 2;
+        frag_mn[f] = k * ROWB + ((((col + 32 * f) >> 3) ^ mn_swizzle(i >> 2)) << 4) + (col & 7) * 2;
       frag_off = 0;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) ks_off[ks] = 16 * ks * ROWB;
@@ -162,8 +174,11 @@ __device__ __forceinline__ unsigned ge0_bf16(unsigned h) {
 template <int TS, bool A_MN, bool B_MN, bool SYM, bool F16, bool SYMSTORE = false>
 __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gemm_prob& P, int b, int tm, int tn,
                                           unsigned char (&sA0)[TS * 128], unsigned char (&sA1)[TS * 128],
-                                          unsigned char (&sB0)[TS * 128], unsigned char (&sB1)[TS * 128]) {
-  constexpr int WM = TS / 2, WN = TS / 4, FM = TS / 64, FN = TS / 128, NLOAD = TS / 64;
+                                          unsigned char (&sB0)[TS * 128], unsigned char (&sB1)[TS * 128],
+                                          unsigned char (&sA2)[tile_shape<TS>::STAGES > 2 ? TS * 128 : 16],
+                                          unsigned char (&sB2)[tile_shape<TS>::STAGES > 2 ? TS * 128 : 16]) {
+  using shape = tile_shape<TS>;
+  constexpr int NTH = shape::NTH, WM = shape::WM, WN = shape::WN, FM = shape::FM, FN = shape::FN, NLOAD = shape::NLOAD;
   const int m0 = tm * TS, n0 = tn * TS;
   const int M = P.M, N = P.N, K = P.K;
   // the operand bases depend on the workgroup only: pin them to scalar registers so that the
@@ -294,7 +309,53 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   }
   const int nk = K / BK;
   int j = 0;
-  if constexpr (!SYMSTORE) {
+  if constexpr (shape::STAGES == 3) {
+    // Three stages, slices requested two ahead: a launch that needs tiles of 64 has few of them, so a slice's
+    // latency is not hidden by other workgroups.  The wait before slice j leaves slice j + 1 in flight.
+    static_assert(!SYMSTORE && NLOAD * 2 < 16, "");
+#define SLICE_STEP3(ca, cb, na, nb)                                       \
+  {                                                                       \
+    asm volatile("" ::: "memory");                                        \
+    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * NLOAD));                     \
+    __builtin_amdgcn_s_barrier();                                         \
+    asm volatile("" ::: "memory");                                        \
+    SHIFT_DIAG(ca, cb, j);                                                \
+    ISSUE(na, nb, min(j + 2, nk - 1));                                    \
+    FETCH(0, ca, cb, 0);                                                  \
+    SB();                                                                 \
+    MMA(1);                                                               \
+    SB();                                                                 \
+    FETCH(1, ca, cb, 1);                                                  \
+    SB();                                                                 \
+    MMA(0);                                                               \
+    SB();                                                                 \
+    FETCH(0, ca, cb, 2);                                                  \
+    SB();                                                                 \
+    MMA(1);                                                               \
+    SB();                                                                 \
+    FETCH(1, ca, cb, 3);                                                  \
+    SB();                                                                 \
+    MMA(0);                                                               \
+    SB();                                                                 \
+    ++j;                                                                  \
+  }
+    // fragment set 1 starts as zeros, so the first step can run its "previous k-step" like any other
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < FN; ++i) fb[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    ISSUE(sA0, sB0, 0);
+    ISSUE(sA1, sB1, min(1, nk - 1));
+    while (j + 3 <= nk) {
+      SLICE_STEP3(sA0, sB0, sA2, sB2);
+      SLICE_STEP3(sA1, sB1, sA0, sB0);
+      SLICE_STEP3(sA2, sB2, sA1, sB1);
+    }
+    if (j < nk) SLICE_STEP3(sA0, sB0, sA2, sB2);
+    if (j < nk) SLICE_STEP3(sA1, sB1, sA0, sB0);
+    SYNC();  // every wave has its last fragments and the requests past the end have landed: the stages are free
+#undef SLICE_STEP3
+  } else if constexpr (!SYMSTORE) {
     ISSUE(sA0, sB0, 0);
     SYNC();
     SHIFT_DIAG(sA0, sB0, 0);
@@ -481,7 +542,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   // upper-only output (sym_store bit 1): the mirrored tile is written only inside a diagonal 256 x 256 block
   const bool mirror = SYM && (tm != tn) && (!(args.sym_store & 2) || (m0 / 256 == n0 / 256));
   // The tile leaves through LDS so that every global store is a 16-byte piece of a row.  The four
-  // stage arrays hold 64 tile rows each (rows of TS * 2 bytes, 16-byte chunk c of row r at slot
+  // stage arrays (the first one at TS = 64) hold 64 tile rows each (rows of TS * 2 bytes, 16-byte chunk c of row r at slot
   // c ^ (r & (CPR - 1))).  The tile is staged once; it is read out row by row for C and, for an
   // off-diagonal tile of a symmetric output, once more column by column (transposing LDS reads)
   // for the mirrored tile.  The R term (a symmetric matrix when the output is) is added at
@@ -580,13 +641,14 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   if (!SYM && P.sign_out) {
     // packed signs of the tile: NTH / TS threads per tile row, each turning CPT consecutive columns
     // of the staged row into CPT / 8 bytes (1 bit) or CPT bytes (int8)
-    constexpr int TPR = NTH / TS, CPT = TS / TPR, NCH = CPT / 8;
+    constexpr int TPR = (TS == 64) ? 2 : NTH / TS, CPT = TS / TPR, NCH = CPT / 8;  // TS = 64: half of the threads
     const int row = etid / TPR, part = etid % TPR;
     const int gr = m0 + row, gc0 = n0 + part * CPT;
     const unsigned char* sp = stage(row >> 6) + (row & 63) * RB;
     unsigned char* so = reinterpret_cast<unsigned char*>(P.sign_out) + (long long)b * P.sign_stride;
     const long long e0 = (long long)gr * P.sign_cols + gc0;  // first entry; a multiple of 32
     unsigned word = 0;
+    if (row < TS)
 #pragma unroll
     for (int q = 0; q < NCH; ++q) {
       const u32x4 w = *reinterpret_cast<const u32x4*>(sp + (((part * NCH + q) ^ (row & (CPR - 1))) << 4));
@@ -621,7 +683,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     // leaves lane i with 8 consecutive elements of row (column block + i) of the mirrored tile.
     // The four groups of a wave take neighbouring row chunks, i.e. 64 contiguous bytes per row.
     constexpr int NRC = TS / 8;         // 8-row chunks in the tile
-    constexpr int CPI = 32 / NRC;       // 16-column blocks covered per iteration by the 32 groups
+    constexpr int CPI = NTH / 16 / NRC; // 16-column blocks covered per iteration by the NTH / 16 groups
     const int G = etid >> 4, i16 = etid & 15;
     const int rchunk = G % NRC;
     const unsigned char* sp = stage((8 * (ewv * 4 % NRC)) >> 6);  // (8 * rchunk) >> 6 is wave-uniform
@@ -705,10 +767,12 @@ __host__ __device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n
 // KIND 2: symmetric output, half-precision operands, both KC.
 // KIND 3: as 2, with operands of which only the blocks on and above the diagonal are valid.
 template <int KIND, int TS>
-__global__ void __launch_bounds__(NTH) sm_ns_gemm_kernel(const sm_gemm_args args) {
+__global__ void __launch_bounds__(tile_shape<TS>::NTH) sm_ns_gemm_kernel(const sm_gemm_args args) {
   constexpr bool SYM = (KIND != 1);
   __shared__ __attribute__((aligned(1024))) unsigned char sA0[TS * 128], sA1[TS * 128];
   __shared__ __attribute__((aligned(1024))) unsigned char sB0[TS * 128], sB1[TS * 128];
+  constexpr int THIRD = tile_shape<TS>::STAGES > 2 ? TS * 128 : 16;
+  __shared__ __attribute__((aligned(1024))) unsigned char sA2[THIRD], sB2[THIRD];
 
   // Persistent workgroups: the grid is one (TS = 256) or two (TS = 128) workgroups per CU and each
   // walks a list of tiles, so the global stores of one tile drain while the next tile is loaded
@@ -740,20 +804,20 @@ __global__ void __launch_bounds__(NTH) sm_ns_gemm_kernel(const sm_gemm_args args
     const sm_gemm_prob& P = args.p[pi];
     int tm, tn;
     tile_of<SYM, (TS == 256 ? 4 : 8)>(t, P.tiles_m, P.tiles_n, tm, tn);
-    if (KIND == 0) {
+    if constexpr (KIND == 0) {
       if (P.layout == 0)
-        gemm_tile<TS, false, false, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
+        gemm_tile<TS, false, false, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
       else
-        gemm_tile<TS, true, true, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
-    } else if (KIND == 1) {
+        gemm_tile<TS, true, true, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+    } else if constexpr (KIND == 1) {
       if (P.layout == 0)
-        gemm_tile<TS, false, false, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
+        gemm_tile<TS, false, false, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
       else
-        gemm_tile<TS, false, true, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
-    } else if (KIND == 2) {
-      gemm_tile<TS, false, false, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
+        gemm_tile<TS, false, true, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+    } else if constexpr (KIND == 2) {
+      gemm_tile<TS, false, false, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     } else {
-      gemm_tile<TS, false, false, true, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1);
+      gemm_tile<TS, false, false, true, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     }
   }
 }
@@ -844,6 +908,25 @@ extern "C" int signmuon_debug_tile_of(int t, int tiles_m, int tiles_n, int sym, 
   return 0;
 }
 
+void sm_tile_count::add(int M, int N, int batch, bool sym) {
+  for (int i = 0; i < 3; ++i) {
+    const int t = 64 << i;
+    const double tm = (M + t - 1) / t, tn = (N + t - 1) / t;
+    tiles[i] += (sym ? tm * (tm + 1) / 2 : tm * tn) * batch;
+  }
+}
+
+int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
+  const int opt = ctx->opt[SM_OPT_GEMM_TILE];
+  if (opt) return opt;
+  // 256 x 256 tiles once there are enough of them to keep 256 CUs busy for several rounds, unless the
+  // matrices fill them badly (a 384-wide matrix covers one and a half: the small tile then computes a
+  // third less)
+  if (c.tiles[2] >= 1024 && 4.0 * c.tiles[2] <= 1.15 * c.tiles[1]) return 256;
+  // 64 x 64 tiles while tiles of 128 would leave half of the CUs without one
+  return (c.tiles[1] <= 0.5 * ctx->n_cu) ? 64 : 128;
+}
+
 // Per problem, P.layout bit 0: A is MN-contiguous, bit 1: B is MN-contiguous.  sym: symmetric
 // output, layout 0 or 3 (A and B may differ as long as the product is symmetric).  Otherwise
 // layout 0 or 2.  K multiple of 64.
@@ -881,31 +964,18 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
     if (a_ext * 2 >= 0x7FFFFFFFLL || b_ext * 2 >= 0x7FFFFFFFLL)
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM operand larger than 2 GiB");
   }
-  int ts = ctx->opt[SM_OPT_GEMM_TILE];
-  if (ts != 128 && ts != 256) {
-    // 256 x 256 tiles once there are enough of them to keep 256 CUs busy for several rounds, unless the
-    // matrices fill them badly (a 384-wide matrix covers one and a half: the small tile then computes a
-    // third less)
-    auto tile_area = [&](int t) {
-      double area = 0.0;
-      for (int i = 0; i < args.n_prob; ++i) {
-        const sm_gemm_prob& P = args.p[i];
-        const double tm = (P.M + t - 1) / t, tn = (P.N + t - 1) / t;
-        area += (gram ? tm * (tm + 1) / 2 : tm * tn) * (double)t * t * P.batch;
-      }
-      return area;
-    };
-    fill_tiles(args, gram, 256);
-    ts = (args.total_tiles >= 1024 && tile_area(256) <= 1.15 * tile_area(128)) ? 256 : 128;
-  }
+  sm_tile_count tc;
+  for (int i = 0; i < args.n_prob; ++i) tc.add(args.p[i].M, args.p[i].N, args.p[i].batch, gram);
+  int ts = sm_gemm_tile(ctx, tc);
+  if (ts == 64 && args.sym_store) ts = 128;
   const int most = fill_tiles(args, gram, ts);
   if (args.total_tiles == 0) return SM_OK;
   args.reverse = ctx->gemm_flip;
   ctx->gemm_flip ^= 1;
-  // persistent grid: one workgroup per CU (two for the small tile), a multiple of 8, never more than tiles
-  int wgs = ctx->n_cu * (ts == 128 ? 2 : 1);
+  // persistent grid: as many workgroups per CU as fit (LDS), a multiple of 8, never more than tiles
+  int wgs = ctx->n_cu * (ts == 64 ? 3 : ts == 128 ? 2 : 1);
   wgs = std::max(1, std::min(wgs / 8, most)) * 8;
-  const dim3 grid(wgs), block(NTH);
+  const dim3 grid(wgs), block(ts == 64 ? tile_shape<64>::NTH : tile_shape<256>::NTH);
   if ((ctx->profiling >> klass) & 1u) {
     for (int i = 0; i < args.n_prob; ++i) {
       const sm_gemm_prob& P = args.p[i];
@@ -937,22 +1007,19 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
   }
   {
     sm_launch_scope sc(ctx, klass);
-    if (args.in_f16 && (args.sym_store & 1) && ts == 256)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<3, 256>), grid, block, 0, ctx->stream, args);
-    else if (args.in_f16 && (args.sym_store & 1))
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<3, 128>), grid, block, 0, ctx->stream, args);
-    else if (args.in_f16 && ts == 256)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<2, 256>), grid, block, 0, ctx->stream, args);
-    else if (args.in_f16)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<2, 128>), grid, block, 0, ctx->stream, args);
-    else if (gram && ts == 256)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<0, 256>), grid, block, 0, ctx->stream, args);
-    else if (gram)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<0, 128>), grid, block, 0, ctx->stream, args);
-    else if (ts == 256)
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<1, 256>), grid, block, 0, ctx->stream, args);
-    else
-      hipLaunchKernelGGL((sm_ns_gemm_kernel<1, 128>), grid, block, 0, ctx->stream, args);
+    const int kind = args.in_f16 ? ((args.sym_store & 1) ? 3 : 2) : gram ? 0 : 1;
+#define GEMM_LAUNCH(KIND, TS) hipLaunchKernelGGL((sm_ns_gemm_kernel<KIND, TS>), grid, block, 0, ctx->stream, args)
+#define GEMM_TILES(KIND)                                                                                   \
+  if (ts == 256) GEMM_LAUNCH(KIND, 256); else if (ts == 128) GEMM_LAUNCH(KIND, 128); else GEMM_LAUNCH(KIND, 64)
+    switch (kind) {
+      case 0: GEMM_TILES(0); break;
+      case 1: GEMM_TILES(1); break;
+      case 2: GEMM_TILES(2); break;
+      default:  // upper-block operands: not built for tiles of 64
+        if (ts == 256) GEMM_LAUNCH(3, 256); else GEMM_LAUNCH(3, 128);
+    }
+#undef GEMM_TILES
+#undef GEMM_LAUNCH
   }
   SM_HIP(ctx, hipGetLastError());
   return SM_OK;

@@ -32,14 +32,15 @@ __device__ __forceinline__ unsigned ge0_f32(unsigned u) { return (u <= 0x7F80000
 __device__ __forceinline__ unsigned ge0_bf16(unsigned h) { return (h <= 0x7F80u) | (h == 0x8000u); }
 
 // ------------------------------------------------------------------ momentum
-// start[k]: the block that holds workgroup (k << shift) of the launch, so that a workgroup finds its
-// block in a step or two instead of comparing all starts (workgroups are short: that would show).
+// start: byte k is the block that holds workgroup (k << shift) of the launch, so that a workgroup finds its
+// block in a step or two instead of comparing all starts (workgroups are short: that would show).  Bytes are
+// taken out of words: there is no scalar byte load, and a vector load of the arguments goes to host memory.
 struct mom_args {
   int n, M;
   float beta, omb, wd;
   int shift;
   sm_starts<SM_MOM_MAX_GROUP> begin;
-  unsigned char start[64];
+  unsigned start[16];
   sm_mom_desc d[SM_MOM_MAX_GROUP];
 };
 static_assert(sizeof(mom_args) <= 4096, "kernel arguments are limited to 4 KB");
@@ -52,7 +53,11 @@ __device__ __forceinline__ float mom_one(float m, float g, float w, const mom_ar
 template <bool VEC>
 __global__ void __launch_bounds__(TPB) sm_momentum_kernel(const mom_args a) {
   __shared__ float red[4];
-  int bi = a.start[blockIdx.x >> a.shift];
+  int bi = 0;
+  if (a.n > 1) {
+    const unsigned k = blockIdx.x >> a.shift;
+    bi = (a.start[k >> 2] >> (8 * (k & 3))) & 0xFFu;
+  }
   while (bi + 1 < a.n && (int)blockIdx.x >= a.begin.v[bi + 1]) ++bi;
   const sm_mom_desc& D = a.d[bi];
   const int local = blockIdx.x - a.begin.v[bi];
@@ -642,9 +647,10 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "momentum: too many entries for one launch");
     a.shift = 0;
     while ((blocks >> a.shift) >= 64) ++a.shift;
+    for (unsigned& w : a.start) w = 0;
     for (int k = 0, bi = 0; k < 64; ++k) {
       while (bi + 1 < g && ((long long)k << a.shift) >= a.begin.v[bi + 1]) ++bi;
-      a.start[k] = (unsigned char)bi;
+      a.start[k >> 2] |= (unsigned)bi << (8 * (k & 3));
     }
     if (blocks > 0) {
       sm_launch_scope sc(ctx, SM_K_MOMENTUM);
