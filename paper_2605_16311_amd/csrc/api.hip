@@ -28,10 +28,10 @@ struct ns_class {
   // off_q[0], later A_k in off_a / off_q[1], T in off_t, P_k in off_p[0/1].
   size_t off_q[2] = {0, 0}, off_a = 0, off_t = 0, off_p[2] = {0, 0};
   int chunks = 0;          // momentum chunks per worker
-  // internal sign buffers of the class: [block][worker] rows of sign_stride bytes
+  // internal sign buffers of the class: [block][worker] buffers of sign_stride bytes, each matrix row by row with
+  // rows padded to cp entries (bits or int8): the apply writes whole words whatever the shape
   size_t off_signs = 0;
   long long sign_stride = 0;
-  bool fuse_signs = false;  // the last apply of the pre-vote iteration can write the signs itself
 };
 
 struct ns_plan {
@@ -92,7 +92,7 @@ int get_plan(signmuon_ctx* ctx, int slot, int n, const int* rows, const int* col
       c.s = c.wide ? c.rp : c.cp;
       c.l = c.wide ? c.cp : c.rp;
       c.mat = (long long)c.rp * c.cp;
-      c.chunks = (int)(((long long)rows[i] * cols[i] + SM_MOM_CHUNK - 1) / SM_MOM_CHUNK);
+      c.chunks = (int)sm_mom_chunks(rows[i], cols[i], c.cp);
       pl->classes.push_back(c);
       k = (int)pl->classes.size() - 1;
     }
@@ -128,11 +128,9 @@ int get_plan(signmuon_ctx* ctx, int slot, int n, const int* rows, const int* col
   pl->off_signs.resize(n);
   pl->sign_stride.resize(n);
   for (auto& c : pl->classes) {
-    const long long d = (long long)c.rows * c.cols;
-    c.sign_stride = (sign_fmt == SM_SIGN_INT8) ? sm_round_up(d, 16) : 8 * ((d + 63) / 64);
+    const long long d = (long long)c.rows * c.cp;
+    c.sign_stride = (sign_fmt == SM_SIGN_INT8) ? d : d / 8;
     c.off_signs = (sign_fmt < 0) ? 0 : take((size_t)c.sign_stride * M * c.count);
-    // whole 32-bit words per 32 columns and no tail bits: the GEMM can emit the packed signs
-    c.fuse_signs = sign_fmt >= 0 && c.cols % 32 == 0 && d % 64 == 0;
   }
   for (int i = 0; i < n; ++i) {
     const ns_class& c = pl->classes[pl->class_of[i]];
@@ -193,7 +191,7 @@ int launch_over_classes(signmuon_ctx* ctx, ns_plan* pl, const gemm_params& gp, i
         P[j].layout = 0;
         P[j].sign_out = nullptr;
         P[j].sign_stride = 0;
-        P[j].sign_rows = P[j].sign_cols = P[j].sign_fmt = P[j].mate = 0;
+        P[j].sign_rows = P[j].sign_ld = P[j].sign_fmt = P[j].mate = 0;
         P[j].mu = P[j].nu = P[j].ku = 0;
       }
       fill(pl->classes[c0 + i], P);
@@ -234,11 +232,11 @@ struct ns_sign_req {
 void apply_to_y(signmuon_ctx* ctx, ns_class& cl, sm_gemm_prob& P, const bf16_t* sm, const bf16_t* y, bf16_t* yout,
                 int batch, const ns_sign_req* signs) {
   const long long ss = (long long)cl.s * cl.s;
-  if (signs && cl.fuse_signs) {
+  if (signs) {
     P.sign_out = at<void>(ctx, cl.off_signs);
     P.sign_stride = cl.sign_stride;
     P.sign_rows = cl.rows;
-    P.sign_cols = cl.cols;
+    P.sign_ld = cl.cp;
     P.sign_fmt = signs->fmt;
     if (!signs->write_y) yout = nullptr;
   }
@@ -566,7 +564,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
 // bounded by a^(2 (SM_NS_SEGMENT - 1)) < 26); other coefficients take the step-by-step form.
 // Option SM_OPT_NS_PATH forces the latter (SM_NS_PATH_STEPWISE) or the recurrence one step at a
 // time (SM_NS_PATH_SINGLE: three products per step), for comparisons.
-// signs (optional): the last apply also emits the packed signs of the classes marked fuse_signs.
+// signs (optional): the last apply also emits the packed signs.
 int run_ns(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, bool use_scale, int* cur_io,
            const ns_sign_req* signs = nullptr) {
   const bool force_stepwise = ctx->opt[SM_OPT_NS_PATH] == SM_NS_PATH_STEPWISE;
@@ -627,28 +625,6 @@ int class_inv_sigma(signmuon_ctx* ctx, ns_plan* pl, int items, int mode, float e
   return sm_launch_sigma_group(ctx, d.data(), (int)d.size(), eps);
 }
 
-// Zeroes the padding of the first `items` matrices per block-count unit of buffer `buf` of every padded class:
-// items_per_class(cl) matrices starting at the buffer's base.
-template <typename F>
-int clear_padding(signmuon_ctx* ctx, ns_plan* pl, int buf, F items_per_class) {
-  std::vector<sm_pad_desc> d;
-  for (auto& cl : pl->classes) {
-    if (cl.rp == cl.rows && cl.cp == cl.cols) continue;
-    sm_pad_desc D;
-    D.x = at<bf16_t>(ctx, cl.off_x[buf]);
-    D.stride = cl.mat;
-    D.rows = cl.rows;
-    D.cols = cl.cols;
-    D.rp = cl.rp;
-    D.cp = cl.cp;
-    D.items = items_per_class(cl);
-    D.blocks_per_item = 0;
-    d.push_back(D);
-  }
-  if (d.empty()) return SM_OK;
-  return sm_launch_pad_clear(ctx, d.data(), (int)d.size());
-}
-
 bool bad_coeffs(const float* c) { return !c || !isfinite(c[0]) || !isfinite(c[1]) || !isfinite(c[2]); }
 
 }  // namespace
@@ -670,9 +646,8 @@ static int momentum_one(signmuon_ctx* ctx, float* mom, const float* grad, const 
   D.d = d;
   D.x_stride = d;
   D.cols = cols;
-  D.ld = cols;
   D.chunks = chunks;
-  D.pad_ = 0;
+  D.quads = sm_div{0, 0};
   int rc = sm_launch_momentum(ctx, &D, 1, M, beta, weight_decay);
   if (rc != SM_OK) return rc;
   if (sumsq) return sm_launch_reduce_partials(ctx, partial_buf, chunks, M, sumsq);
@@ -744,22 +719,18 @@ int signmuon_polar_ns(signmuon_ctx* ctx, void* x, int dtype, int batch, int rows
   int rc = get_plan(ctx, SM_WS_NS, 1, &rows, &cols, batch, -1, &pl);
   if (rc != SM_OK) return rc;
   ns_class& cl = pl->classes[0];
-  rc = sm_launch_copy_in(ctx, x, dtype, batch, rows, cols, at<bf16_t>(ctx, cl.off_x[0]), cl.cp, cl.mat);
-  if (rc != SM_OK) return rc;
-  rc = clear_padding(ctx, pl, 0, [&](ns_class&) { return batch; });
+  rc = sm_launch_copy_in(ctx, x, dtype, batch, rows, cols, at<bf16_t>(ctx, cl.off_x[0]), cl.cp, cl.mat,
+                         scale == SM_SCALE_FRO ? at<float>(ctx, cl.off_partial) : nullptr);
   if (rc != SM_OK) return rc;
   bool use_scale = false;
   if (scale == SM_SCALE_FRO) {
-    rc = sm_launch_sumsq(ctx, x, dtype, (long long)rows * cols, batch, at<float>(ctx, cl.off_partial),
-                         at<float>(ctx, cl.off_sig));
-    if (rc != SM_OK) return rc;
-    rc = sm_launch_inv_sigma(ctx, at<float>(ctx, cl.off_sig), batch, eps, true, at<float>(ctx, cl.off_inv));
+    rc = class_inv_sigma(ctx, pl, batch, 0, eps);
     if (rc != SM_OK) return rc;
     use_scale = true;
   } else if (scale == SM_SCALE_SPECTRAL) {
     rc = spectral_sigma(ctx, pl, 0, batch, batch, &v0, power_iters, eps);
     if (rc != SM_OK) return rc;
-    rc = sm_launch_inv_sigma(ctx, at<float>(ctx, cl.off_sig), batch, eps, false, at<float>(ctx, cl.off_inv));
+    rc = class_inv_sigma(ctx, pl, batch, 1, eps);
     if (rc != SM_OK) return rc;
     use_scale = true;
   }
@@ -791,7 +762,7 @@ int signmuon_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, i
     // split long rows into 2-D with cols a multiple of 64 when possible
     return sm_fail(ctx, SM_EUNSUPPORTED, "sign_pack: n >= 2^31 per row");
   }
-  return sm_launch_sign_pack(ctx, u, dtype, batch, 1, (int)n, (int)n, n, fmt, out, out_stride_bytes);
+  return sm_launch_sign_pack(ctx, u, dtype, batch, n, fmt, out, out_stride_bytes);
 }
 
 int signmuon_majority_vote(signmuon_ctx* ctx, const void* signs, int fmt, int M, int64_t n, int64_t stride_bytes,
@@ -822,8 +793,6 @@ int signmuon_majority_vote(signmuon_ctx* ctx, const void* signs, int fmt, int M,
   a.stride_bytes = stride_bytes;
   a.voted = voted;
   a.vfmt = vfmt;
-  a.cols = 1;
-  a.ld = 1;
   a.counts = counts;
   a.w = w;
   a.lr_scaled = lr_scaled;
@@ -878,20 +847,14 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     D.d = (long long)cl.rows * cl.cols;
     D.x_stride = cl.mat;
     D.cols = cl.cols;
-    D.ld = cl.cp;
     D.chunks = cl.chunks;
-    D.pad_ = 0;
+    D.quads = (cl.cp == cl.cols) ? sm_div{0, 0} : sm_div_by((unsigned)(cl.cols + 3) / 4);
   }
   rc = sm_launch_momentum(ctx, descs.data(), n, M, s->beta, s->weight_decay);
   if (rc != SM_OK) return rc;
   // the first GEMM launch (the Gram of Y) walks its tile ranges backwards: it starts with the blocks whose
   // bf16 copies the momentum kernel wrote last
   ctx->gemm_flip = 1;
-  // the momentum kernel writes the logical entries of X only: restore the zero padding, which an
-  // earlier call with a non-finite matrix may have turned into NaN
-  rc = clear_padding(ctx, pl, 0, [&](ns_class& cl) { return cl.count * M; });
-  if (rc != SM_OK) return rc;
-
   // a2: sigma per (block, worker)
   bool use_scale = false;
   if (s->ns_steps > 0 || (s->u_out != nullptr)) {
@@ -909,54 +872,58 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
   }
 
   // a3 + a4: K Newton-Schulz steps on all (block, worker) matrices
-  // When the iteration has at least one step, its last apply writes the packed signs (a5) of
-  // every class whose rows pack into whole words; U itself is then only written if a tap asks.
+  // When the iteration has at least one step, its last apply writes the packed signs (a5); U itself is then only
+  // written if a tap asks for it, or for signs whose rows are not those of the internal buffer.
   ns_sign_req sreq;
   sreq.fmt = s->sign_fmt;
   sreq.write_y = false;
   if (s->u_out)
     for (int i = 0; i < n; ++i) sreq.write_y = sreq.write_y || (s->u_out[i] != nullptr);
+  if (s->signs_out)
+    for (int i = 0; i < n; ++i) sreq.write_y = sreq.write_y || (s->signs_out[i] != nullptr && s->cols[i] % 64 != 0);
   const bool fused = s->ns_steps > 0;
   int cur = 0;
   rc = run_ns(ctx, pl, M, s->ns_steps, s->coeffs, use_scale, &cur, fused ? &sreq : nullptr);
   if (rc != SM_OK) return rc;
 
   const int Kp = s->local_polar_steps;
-  // a5 + a6 (+ a8 when there is no local polar step): one sign-pack launch and one vote launch
-  // over all blocks
-  std::vector<sm_sp_desc> sp;
-  sp.reserve(n);
+  // a5 + a6 (+ a8 when there is no local polar step): one vote launch over all blocks, after a sign-pack launch where
+  // no apply has written the signs, and another for the taps of signs with rows that are not whole words
+  std::vector<sm_sp_desc> sp, sp_tap;
   std::vector<sm_vote_desc> vd(n);
   for (int i = 0; i < n; ++i) {
     ns_class& cl = pl->classes[pl->class_of[i]];
     const int idx = pl->index_in_class[i];
     const long long d = (long long)cl.rows * cl.cols;
+    const bool padded = cl.cp != cl.cols;
     const bf16_t* u = at<bf16_t>(ctx, cl.off_x[cur]) + (long long)idx * M * cl.mat;
     if (s->u_out && s->u_out[i]) {
       rc = sm_launch_copy_out(ctx, u, cl.cp, cl.mat, M, cl.rows, cl.cols, s->u_out[i], SM_BF16,
                               (s->ns_steps == 0 && use_scale) ? at<float>(ctx, cl.off_inv) + (long long)idx * M : nullptr);
       if (rc != SM_OK) return rc;
     }
-    const bool tap = s->signs_out && s->signs_out[i];
-    const bool in_gemm = fused && cl.fuse_signs;  // already in the internal buffer
-    void* signs = (tap && !in_gemm) ? s->signs_out[i] : at<void>(ctx, pl->off_signs[i]);
-    const long long stride =
-        (tap && !in_gemm) ? ((s->sign_fmt == SM_SIGN_INT8) ? d : 8 * ((d + 63) / 64)) : pl->sign_stride[i];
-    if (in_gemm) {
-      // d is a multiple of 64 here, so the tap's rows have the internal stride
-      if (tap) SM_HIP(ctx, hipMemcpyAsync(s->signs_out[i], signs, (size_t)stride * M, hipMemcpyDeviceToDevice, ctx->stream));
-    } else {
-      sm_sp_desc S;
-      S.u = u;
+    void* signs = at<void>(ctx, pl->off_signs[i]);
+    const long long stride = pl->sign_stride[i];
+    sm_sp_desc S;
+    S.u = u;
+    S.batch_stride = cl.mat;
+    S.blocks_per_row = S.pad_ = 0;
+    if (!fused) {  // the rows of u with their padding are the rows of the internal buffer
       S.out = signs;
-      S.n = d;
-      S.batch_stride = cl.mat;
+      S.n = (long long)cl.rows * cl.cp;
       S.out_stride = stride;
-      S.bytes_per_row = 0;
+      S.cols = S.ld = cl.cp;
+      sp.push_back(S);
+    }
+    if (s->signs_out && s->signs_out[i] && (padded || !fused)) {
+      S.out = s->signs_out[i];
+      S.n = d;
+      S.out_stride = (s->sign_fmt == SM_SIGN_INT8) ? d : 8 * ((d + 63) / 64);
       S.cols = cl.cols;
       S.ld = cl.cp;
-      S.blocks_per_row = S.pad_ = 0;
-      sp.push_back(S);
+      sp_tap.push_back(S);
+    } else if (s->signs_out && s->signs_out[i]) {
+      SM_HIP(ctx, hipMemcpyAsync(s->signs_out[i], signs, (size_t)stride * M, hipMemcpyDeviceToDevice, ctx->stream));
     }
     float step = s->lr;
     if (s->update_rsqrt_mn == 1) step = s->lr / sqrtf((float)cl.rows * (float)cl.cols);
@@ -967,23 +934,25 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     V.counts = (s->counts_out) ? s->counts_out[i] : nullptr;
     V.lr = step;
     V.M = M;
+    V.cols = cl.cols;
+    V.sld = padded ? cl.cp : 0;
     if (Kp == 0 && !op_norm) {
       V.voted = nullptr;
       V.vfmt = SM_VOTE_BF16;
-      V.cols = V.ld = 1;
+      V.ld = cl.cols;
       V.w = s->w[i];
     } else {
       // the voted +-1 matrix becomes item `idx` of the class's post-vote batch, in the
       // buffer that does not hold the workers' U
       V.voted = at<bf16_t>(ctx, cl.off_x[cur ^ 1]) + (long long)idx * cl.mat;
       V.vfmt = SM_VOTE_BF16;
-      V.cols = cl.cols;
       V.ld = cl.cp;
       V.w = nullptr;
     }
   }
-  if (!sp.empty()) {
-    rc = sm_launch_sign_pack_group(ctx, sp.data(), (int)sp.size(), SM_BF16, s->sign_fmt, M);
+  for (auto* list : {&sp, &sp_tap}) {
+    if (list->empty()) continue;
+    rc = sm_launch_sign_pack_group(ctx, list->data(), (int)list->size(), SM_BF16, s->sign_fmt, M);
     if (rc != SM_OK) return rc;
   }
   rc = sm_launch_vote_group(ctx, vd.data(), n, s->sign_fmt);
@@ -994,7 +963,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
       sm_vote_desc t = vd[i];
       t.voted = s->d_out[i];
       t.vfmt = SM_VOTE_BF16;
-      t.cols = t.ld = 1;
+      t.ld = t.cols;
       t.counts = nullptr;
       t.w = nullptr;
       rc = sm_launch_vote_group(ctx, &t, 1, s->sign_fmt);
@@ -1002,10 +971,6 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     }
   }
   if (Kp == 0 && !op_norm) return SM_OK;
-  // the voted matrices took over slots that held some workers' matrices before the vote: zero their padding
-  rc = clear_padding(ctx, pl, cur ^ 1, [&](ns_class& cl) { return cl.count; });
-  if (rc != SM_OK) return rc;
-
   // a7: local polar step on the voted sign matrices (one per block), or their operator norm for
   // the normalized-sign update (worker 0's start vector serves the voted matrix of each block)
   bool use_scale2 = false;

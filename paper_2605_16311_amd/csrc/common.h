@@ -116,20 +116,62 @@ __device__ __forceinline__ int sm_find(const sm_starts<N>& s, int n, int bx) {
   return at;
 }
 
+// ---------------------------------------------------------------- unaligned vectors, division
+// Vectors of which only the elements are aligned: a row of odd length starts anywhere, and global memory takes
+// 8- and 16-byte accesses at any address of this part.
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
+typedef u32x4 u32x4_u __attribute__((aligned(1)));
+typedef u32x2 u32x2_u __attribute__((aligned(1)));
+typedef unsigned u32_u __attribute__((aligned(1)));
+typedef bf16x4 bf16x4_u __attribute__((aligned(2)));
+typedef i32x4 i32x4_u __attribute__((aligned(4)));
+
+// Division of 0 <= n < 2^31 by a divisor the host knows: multiply and shift (64-bit division is a call of some
+// hundred instructions, which is what bounded the copies of rows of odd length).
+struct sm_div {
+  unsigned mul, shift;
+};
+static inline sm_div sm_div_by(unsigned d) {
+  unsigned s = 0;
+  while ((1ull << s) < d) ++s;
+  return sm_div{(unsigned)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
+}
+__device__ __forceinline__ unsigned sm_quot(const sm_div& v, unsigned n) {
+  return (unsigned)(((unsigned long long)n * v.mul) >> v.shift);
+}
+// Row and column of entry `at` (any size) of rows of d entries (v = sm_div_by(d)).
+__device__ __forceinline__ void sm_row_of(const sm_div& v, int d, long long at, long long& row, int& col) {
+  if (at < 0x7FFFFFFFLL) {
+    const unsigned q = sm_quot(v, (unsigned)at);
+    row = q;
+    col = (int)((unsigned)at - q * (unsigned)d);
+  } else {
+    row = at / d;
+    col = (int)(at - row * d);
+  }
+}
+
 // ---------------------------------------------------------------- streaming kernels (stream.hip)
 // Descriptor of one weight block for the grouped momentum launch.
 struct sm_mom_desc {
   float* mom;          // [M][d]
   const float* grad;   // [M][d]
   const float* w;      // [d] or null
-  bf16_t* x;           // [M][rows_p][ld] padded bf16 copy, or null
+  bf16_t* x;           // [M] bf16 copies, flat or with padded rows, or null
   float* partial;      // [M][chunks] per-chunk sums of squares, or null
   long long d;         // rows*cols
   long long x_stride;  // elements between workers in x
-  int cols, ld;        // logical row length and padded row length of x
-  int chunks;          // chunks per worker
-  int pad_;
+  int cols;            // row length
+  int chunks;          // chunks per worker (sm_mom_chunks)
+  sm_div quads;        // by the number of 4-entry groups per row where the rows of x are padded to whole 64 entries;
+                       // shift 0: x is as flat as mom
 };
+// Chunks of SM_MOM_CHUNK entries per worker.  A matrix that goes into padded rows (ld != cols) is cut into groups
+// of four entries row by row, so that a group never straddles rows; otherwise it is one flat run.
+static inline long long sm_mom_chunks(long long rows, long long cols, long long ld) {
+  const long long n = (ld == cols) ? rows * cols : rows * ((cols + 3) / 4 * 4);
+  return (n + 1024 - 1) / 1024;
+}
 constexpr int SM_MOM_MAX_GROUP = 48;  // blocks per launch: the table rides in the kernel arguments (4 KB at most)
 constexpr int SM_MOM_CHUNK = 1024;  // elements per workgroup: one 16-byte piece per thread (short-lived workgroups
                                     // keep the four streams of the momentum update close together in memory)
@@ -137,9 +179,7 @@ constexpr int SM_MOM_CHUNK = 1024;  // elements per workgroup: one 16-byte piece
 int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M, float beta, float wd);
 // sumsq[i] = sum_j partial[i*chunks + j], i < count (fixed order)
 int sm_launch_reduce_partials(signmuon_ctx* ctx, const float* partial, int chunks, int count, float* sumsq);
-// inv_sigma[i] = 1 / max(sqrt(sumsq[i]), eps)   (from_sq) or 1 / max(sumsq[i], eps)
-int sm_launch_inv_sigma(signmuon_ctx* ctx, const float* sig, int count, float eps, bool from_sq, float* inv_sigma);
-// Grouped form over a table of matrix classes, one launch: per class `count` items with
+// Inverse scales over a table of matrix classes, one launch: per class `count` items with
 //   mode 0: sig = sum of the item's `chunks` partial sums of squares, inv = 1 / max(sqrt(sig), eps)
 //   mode 1: inv = 1 / max(sig, eps)          mode 2: inv = value
 struct sm_sigma_desc {
@@ -159,23 +199,27 @@ struct sm_sp_desc {
   long long n;              // rows * cols
   long long batch_stride;   // elements between workers in u
   long long out_stride;     // bytes
-  long long bytes_per_row;  // filled by the launcher
-  int cols, ld;
-  int blocks_per_row;  // filled by the launcher
+  int cols, ld;             // ld == cols: u is flat
+  sm_div by_cols;           // filled by the launcher
+  int blocks_per_row;       // filled by the launcher
   int pad_;
 };
 constexpr int SM_SP_MAX_GROUP = 48;
 int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n, int dtype, int fmt, int M);
 
-// Grouped expanding vote (+ fused update): one launch over a table of matrices.
+// Grouped vote with expanded outputs (+ fused update): one launch over a table of matrices.  The signs of a worker
+// are rows of `sld` entries of which `cols` count, sld a multiple of 64, or (sld == 0) one run of n entries.
 struct sm_vote_desc {
   const void* signs;
-  long long n, stride_bytes;
+  long long n, stride_bytes;  // n: rows * cols
   void* voted;       // non-bit formats only (SM_VOTE_INT8/BF16/F32), or null
-  int32_t* counts;
-  float* w;
+  int32_t* counts;   // flat, or null
+  float* w;          // flat, or null
   float lr;
-  int M, vfmt, cols, ld;
+  int M, vfmt;
+  int cols, sld;
+  int ld;            // row length of voted: sld (then the columns beyond cols are written as zeros; bf16 only) or cols
+  sm_div by_row;     // by the words (1 bit) or groups of four (int8) of a row of sld; filled by the launcher
 };
 constexpr int SM_VOTE_MAX_GROUP = 48;
 int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, int fmt);
@@ -187,53 +231,35 @@ struct sm_upd_desc {
   const float* kappa;  // optional device scalar multiplied into step
   int rows, cols, ld;
   float step;
+  sm_div quads;        // by the 4-entry groups of a row; filled by the launcher
 };
 constexpr int SM_UPD_MAX_GROUP = 64;
 int sm_launch_update_group(signmuon_ctx* ctx, const sm_upd_desc* descs, int n);
 
-// sign pack from a (possibly padded) 2-D source: u[batch][rows][ld] -> flat row-major bits
-int sm_launch_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, int rows, int cols,
-                        int ld, long long batch_stride, int fmt, void* out, long long out_stride_bytes);
+// sign pack of a flat source: u[batch][n] -> rows of bits or int8
+int sm_launch_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, long long n, int fmt, void* out,
+                        long long out_stride_bytes);
 
 struct sm_vote_args {
   const void* signs;
   int fmt, M;
   long long n, stride_bytes;
   void* voted;
-  int vfmt;          // SM_VOTE_*; for BF16/F32 the destination may be 2-D padded:
-  int cols, ld;      // voted element i goes to (i / cols) * ld + (i % cols); ld == cols: flat
+  int vfmt;          // SM_VOTE_*
   int32_t* counts;
   float* w;
   float lr_scaled;
 };
 int sm_launch_vote(signmuon_ctx* ctx, const sm_vote_args& a);
 
-// w[r][c] -= step * d[r][ld] (bf16 d)
-int sm_launch_update(signmuon_ctx* ctx, float* w, const bf16_t* d, int rows, int cols, int ld, float step);
-
 // ---------------------------------------------------------------- layout helpers (layout.hip)
-// dst[b][rows_p][ld] (bf16, padding untouched) <- src[b][rows][cols] (f32 or bf16)
+// dst[b][rows_p][ld] (bf16, padding not touched) <- src[b][rows][cols] (f32 or bf16); with partial also the sums of
+// squares of the source per chunk, partial[b * sm_mom_chunks(rows, cols, ld) + chunk]
 int sm_launch_copy_in(signmuon_ctx* ctx, const void* src, int dtype, int batch, int rows, int cols,
-                      bf16_t* dst, int ld, long long dst_stride);
+                      bf16_t* dst, int ld, long long dst_stride, float* partial);
 // dst[b][rows][cols] (f32 or bf16) <- scale[b] * src[b][rows][ld]; scale may be null
 int sm_launch_copy_out(signmuon_ctx* ctx, const bf16_t* src, int ld, long long src_stride, int batch, int rows,
                        int cols, void* dst, int dtype, const float* scale);
-// Writes zeros over the padding (columns cols..cp, rows rows..rp) of `items` matrices [rp][cp], `stride`
-// elements apart: the working layout relies on padding that reads as zero, and a non-finite input would
-// otherwise leave NaN there for every later call (0 * NaN in a product's padded rows).
-struct sm_pad_desc {
-  bf16_t* x;
-  long long stride;
-  int rows, cols, rp, cp;
-  int items;
-  int blocks_per_item;  // filled by the launcher
-};
-constexpr int SM_PAD_MAX_GROUP = 64;
-int sm_launch_pad_clear(signmuon_ctx* ctx, const sm_pad_desc* descs, int n);
-// sumsq[b] = sum of squares of x[b][0..n) (f32 or bf16; two stages, fixed order);
-// scratch: batch * ceil(n / SM_MOM_CHUNK) floats
-int sm_launch_sumsq(signmuon_ctx* ctx, const void* x, int dtype, long long n_per_batch, int batch, float* scratch,
-                    float* sumsq);
 
 // ---------------------------------------------------------------- GEMM (ns_gemm.hip)
 // C[b] = rnd(rnd(alpha * scale[b]^scale_pow * (A' * B'^T) + diag * I) + gamma * R[b]),
@@ -256,18 +282,19 @@ struct sm_gemm_prob {
   int tiles_m, tiles_n;  // filled by the launcher
   int layout;            // bit 0: A stored [K][M] (lda = its row length), bit 1: B stored [K][N]
   // Optional sign output of a general (non-symmetric) bf16 product: the signs (x >= 0) of the
-  // leading sign_rows x sign_cols part of C[b], packed row-major into
-  // sign_out + b * sign_stride as in signmuon_sign_pack (sign_cols a multiple of 32).  C may
-  // then be null.
+  // leading sign_rows x sign_ld part of C[b], packed row by row (sign_ld a multiple of 64) into
+  // sign_out + b * sign_stride as in signmuon_sign_pack.  C may then be null.
   void* sign_out;
   long long sign_stride;
-  int sign_rows, sign_cols;
+  int sign_rows, sign_ld;
   int sign_fmt;
   // Index (> own index) of a second problem of equal M, N, K and batch whose tiles are dealt item by
   // item right after this problem's (item b of this one, item b of the mate, item b + 1, ...), so
   // that operands the two share are read from HBM once; 0 = none.  The mate owns no tiles itself.
   int mate;
-  // logical (unpadded) M, N, K for the work accounting of the timing taps; 0 = as M, N, K
+  // logical (unpadded) M, N, K, for the work accounting of the timing taps; 0 = as M, N, K.  A general product also
+  // writes zeros to the entries of C beyond mu x nu, whatever the product has there (0 * NaN where an operand is not
+  // finite): the padding of the working layout reads as zero for every later call.
   int mu, nu, ku;
 };
 constexpr int SM_GEMM_MAX_PROB = 24;

@@ -532,8 +532,8 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
           unsigned w = ((x & 0xFu) | ((x & 0xF0u) << 4) | ((x & 0xF00u) << 8) | ((x & 0xF000u) << 12)) << (4 * fg);
           w |= __shfl_xor(w, 32, 64);
           const int c0 = n0 + e_n * WN + jn * 32;
-          if ((jn & 1) == fg && mg < P.sign_rows && c0 < P.sign_cols)  // sign_cols % 32 == 0: a word is live as a whole
-            *reinterpret_cast<unsigned*>(so + (((long long)mg * P.sign_cols + c0) >> 3)) = w;
+          if ((jn & 1) == fg && mg < P.sign_rows && c0 < P.sign_ld)  // sign_ld % 64 == 0: a word is live as a whole
+            *reinterpret_cast<unsigned*>(so + (((long long)mg * P.sign_ld + c0) >> 3)) = w;
         }
       }
       return;
@@ -626,12 +626,20 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
         if (gr < M && gc < N) rv[k] = *reinterpret_cast<const u32x4*>(R + (long long)gr * P.ldc + gc);
       }
     }
+    // a general product stores zeros beyond the logical matrix (see sm_gemm_prob::mu)
+    const int mu = SYM ? M : P.mu, nu = SYM ? N : P.nu;
+    const bool edge = !SYM && (m0 + TS > mu || n0 + TS > nu);
 #pragma unroll
     for (int k = 0; k < PASSES; ++k) {
       const int row = rr + RPP * k;  // tile row; (row >> 6) == (RPP * k) >> 6 is a constant
       const unsigned char* sp = stage((RPP * k) >> 6);
-      const u32x4 v = *reinterpret_cast<const u32x4*>(sp + (row & 63) * RB + ((rc ^ (row & (CPR - 1))) << 4));
+      u32x4 v = *reinterpret_cast<const u32x4*>(sp + (row & 63) * RB + ((rc ^ (row & (CPR - 1))) << 4));
       const int gr = m0 + row;
+      if (edge) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          v[q] &= (gr < mu && gc + 2 * q < nu ? 0xFFFFu : 0u) | (gr < mu && gc + 2 * q + 1 < nu ? 0xFFFF0000u : 0u);
+      }
       if (gr < M && gc < N) {
         const long long off = (long long)gr * P.ldc + gc;
         *reinterpret_cast<u32x4*>(C + off) = R ? add_r(v, rv[k]) : v;
@@ -646,7 +654,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     const int gr = m0 + row, gc0 = n0 + part * CPT;
     const unsigned char* sp = stage(row >> 6) + (row & 63) * RB;
     unsigned char* so = reinterpret_cast<unsigned char*>(P.sign_out) + (long long)b * P.sign_stride;
-    const long long e0 = (long long)gr * P.sign_cols + gc0;  // first entry; a multiple of 32
+    const long long e0 = (long long)gr * P.sign_ld + gc0;  // first entry; a multiple of 32
     unsigned word = 0;
     if (row < TS)
 #pragma unroll
@@ -656,11 +664,11 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
 #pragma unroll
       for (int h = 0; h < 4; ++h)
         bits |= (ge0_bf16(w[h] & 0xFFFFu) << (2 * h)) | (ge0_bf16(w[h] >> 16) << (2 * h + 1));
-      const bool live = gr < P.sign_rows && gc0 + 8 * q < P.sign_cols;
+      const bool live = gr < P.sign_rows && gc0 + 8 * q < P.sign_ld;
       if (P.sign_fmt == SM_SIGN_1BIT) {
         word |= bits << (8 * (q & 3));
         if ((q & 3) == 3) {
-          // 32 columns per store; sign_cols is a multiple of 32, so a word is live as a whole
+          // 32 columns per store; sign_ld is a multiple of 64, so a word is live as a whole
           if (live) *reinterpret_cast<unsigned*>(so + ((e0 + 8 * (q - 3)) >> 3)) = word;
           word = 0;
         }
@@ -940,6 +948,8 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
     if (gram ? (P.layout != 0 && P.layout != 3) : (P.layout != 0 && P.layout != 2))
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM layout combination not built");
     if (!sm_aligned(P.R, 16)) return sm_fail(ctx, SM_EINVAL, "internal: GEMM R term misaligned");
+    if (!sym && (P.mu < 1 || P.nu < 1 || P.mu > P.M || P.nu > P.N))
+      return sm_fail(ctx, SM_EINVAL, "internal: GEMM logical size");
     if (!P.C && (sym || !P.sign_out)) return sm_fail(ctx, SM_EINVAL, "internal: GEMM without an output");
     if (P.mate) {
       if (P.mate <= i || P.mate >= args.n_prob) return sm_fail(ctx, SM_EINVAL, "internal: GEMM mate index");
@@ -947,9 +957,9 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
       if (Q.mate || Q.M != P.M || Q.N != P.N || Q.K != P.K || Q.batch != P.batch)
         return sm_fail(ctx, SM_EINVAL, "internal: GEMM mate of a different shape");
     }
-    if (P.sign_out && (sym || args.out_f16 || P.R || P.sign_cols % 32 || P.sign_stride % 8 || !sm_aligned(P.sign_out, 8) ||
+    if (P.sign_out && (sym || args.out_f16 || P.R || P.sign_ld % 64 || P.sign_stride % 8 || !sm_aligned(P.sign_out, 8) ||
                        (P.sign_fmt != SM_SIGN_1BIT && P.sign_fmt != SM_SIGN_INT8)))
-      return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM sign output needs a general bf16 product and cols % 32 == 0");
+      return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM sign output needs a general bf16 product and whole words per row");
     if ((args.a_diag != 0.f || args.b_diag != 0.f) && !args.in_f16)
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: operand identity shift needs half-precision operands");
     if (args.in_f16 && (!sym || P.layout != 0))

@@ -50,8 +50,12 @@ __device__ __forceinline__ float mom_one(float m, float g, float w, const mom_ar
   return __fadd_rn(__fmul_rn(a.beta, m), __fmul_rn(a.omb, g));
 }
 
-template <bool VEC>
+// A thread owns four consecutive entries, of one row where the rows of x are padded (then the group that ends a row
+// also writes x's zeros up to the next multiple of four).  Rows and workers of odd length make the vectors unaligned,
+// which costs a ninth line per wave and load; one path serves every size (the scalar one it replaces, with a 64-bit
+// division per entry, took 61 us where the traffic is worth 28: 1000x2047 and smaller blocks, three workers).
 __global__ void __launch_bounds__(TPB) sm_momentum_kernel(const mom_args a) {
+  static_assert(SM_MOM_CHUNK == TPB * 4, "one group of four entries per thread");
   __shared__ float red[4];
   int bi = 0;
   if (a.n > 1) {
@@ -63,52 +67,54 @@ __global__ void __launch_bounds__(TPB) sm_momentum_kernel(const mom_args a) {
   const int local = blockIdx.x - a.begin.v[bi];
   const int p = local / D.chunks, ch = local - p * D.chunks;
   const long long d = D.d;
-  float* mom = D.mom + (long long)p * d;
-  const float* grad = D.grad + (long long)p * d;
-  const float* w = D.w;
-  bf16_t* x = D.x ? D.x + (long long)p * D.x_stride : nullptr;
-  const bool has_wd = (w != nullptr) && (a.wd != 0.f);
-  const bool flat = (D.ld == D.cols);
-  const long long base = (long long)ch * SM_MOM_CHUNK;
+  const bool has_wd = (D.w != nullptr) && (a.wd != 0.f);
+  long long i = (long long)ch * SM_MOM_CHUNK + threadIdx.x * 4;  // first entry of the group
+  long long xi = i;
+  int live = 4;
+  if (D.quads.shift) {
+    long long r;
+    int c;
+    sm_row_of(D.quads, (D.cols + 3) >> 2, (long long)ch * TPB + threadIdx.x, r, c);
+    c *= 4;
+    i = r * D.cols + c;
+    xi = r * ((D.cols + 63) & ~63) + c;
+    live = min(4, D.cols - c);
+  }
+  if (i >= d) live = 0;
+  else if (d - i < live) live = (int)(d - i);
   float ss = 0.f;
-  if (VEC) {
-#pragma unroll
-    for (int it = 0; it < SM_MOM_CHUNK / (TPB * 4); ++it) {
-      const long long i = base + (long long)it * (TPB * 4) + threadIdx.x * 4;
-      if (i >= d) break;  // d % 4 == 0 on this path
-      f32x4 m = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(mom + i));
-      const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(grad + i));
+  if (live > 0) {
+    float* mom = D.mom + (long long)p * d + i;
+    const float* grad = D.grad + (long long)p * d + i;
+    f32x4 m = {0.f, 0.f, 0.f, 0.f};
+    if (live == 4) {
+      m = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(mom));
+      const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(grad));
       f32x4 ww = {0.f, 0.f, 0.f, 0.f};
-      if (has_wd) ww = *reinterpret_cast<const f32x4*>(w + i);
-      m.x = mom_one(m.x, g.x, ww.x, a, has_wd);
-      m.y = mom_one(m.y, g.y, ww.y, a, has_wd);
-      m.z = mom_one(m.z, g.z, ww.z, a, has_wd);
-      m.w = mom_one(m.w, g.w, ww.w, a, has_wd);
+      if (has_wd) ww = *reinterpret_cast<const f32x4_u*>(D.w + i);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m[k] = mom_one(m[k], g[k], ww[k], a, has_wd);
       // neither the momentum nor its bf16 copy is read again before it has left the caches
-      __builtin_nontemporal_store(m, reinterpret_cast<f32x4*>(mom + i));
-      ss += (m.x * m.x + m.y * m.y) + (m.z * m.z + m.w * m.w);
-      if (x) {
-        if (flat || (D.cols & 3) == 0) {
-          const long long xi = flat ? i : (i / D.cols) * D.ld + (i % D.cols);
-          bf16x4 h = {(bf16_t)m.x, (bf16_t)m.y, (bf16_t)m.z, (bf16_t)m.w};
-          __builtin_nontemporal_store(h, reinterpret_cast<bf16x4*>(x + xi));
-        } else {
-          const float mv[4] = {m.x, m.y, m.z, m.w};
-          for (int k = 0; k < 4; ++k) {
-            const long long e = i + k;
-            x[(e / D.cols) * D.ld + (e % D.cols)] = (bf16_t)mv[k];
-          }
+      __builtin_nontemporal_store(m, reinterpret_cast<f32x4_u*>(mom));
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < live) {
+          m[k] = mom_one(mom[k], grad[k], has_wd ? D.w[i + k] : 0.f, a, has_wd);
+          mom[k] = m[k];
         }
-      }
     }
-  } else {
-    for (int it = 0; it < SM_MOM_CHUNK / TPB; ++it) {
-      const long long i = base + (long long)it * TPB + threadIdx.x;
-      if (i >= d) break;
-      const float m = mom_one(mom[i], grad[i], has_wd ? w[i] : 0.f, a, has_wd);
-      mom[i] = m;
-      ss += m * m;
-      if (x) x[flat ? i : (i / D.cols) * D.ld + (i % D.cols)] = (bf16_t)m;
+    ss = (m[0] * m[0] + m[1] * m[1]) + (m[2] * m[2] + m[3] * m[3]);
+    if (D.x) {
+      bf16_t* x = D.x + (long long)p * D.x_stride + xi;
+      const bf16x4 h = {(bf16_t)m[0], (bf16_t)m[1], (bf16_t)m[2], (bf16_t)m[3]};
+      if (live == 4 || D.quads.shift) {
+        __builtin_nontemporal_store(h, reinterpret_cast<bf16x4_u*>(x));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          if (k < live) x[k] = h[k];
+      }
     }
   }
   if (D.partial) {
@@ -125,14 +131,6 @@ __global__ void __launch_bounds__(TPB) sm_reduce_partials_kernel(const float* pa
   for (int j = threadIdx.x; j < chunks; j += TPB) s += src[j];
   const float tot = block_sum(s, red);
   if (threadIdx.x == 0) sumsq[blockIdx.x] = tot;
-}
-
-__global__ void sm_inv_sigma_kernel(const float* sig, int count, float eps, int from_sq, float* inv) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  float s = sig[i];
-  if (from_sq) s = sqrtf(s);
-  inv[i] = 1.0f / fmaxf(s, eps);
 }
 
 struct sigma_args {
@@ -163,9 +161,6 @@ __global__ void __launch_bounds__(TPB) sm_sigma_group_kernel(const sigma_args a)
 }
 
 // ------------------------------------------------------------------ sign pack
-// One thread = one output byte = 8 consecutive entries of the flattened matrix.
-// Source row index / padded leading dimension are resolved per byte (cols % 8 == 0
-// on the fast path so a byte never straddles rows).
 // One launch covers a table of matrices (all workers of each): workgroup -> (matrix, worker, chunk).
 struct sp_args {
   int n;
@@ -174,129 +169,166 @@ struct sp_args {
   sm_sp_desc d[SM_SP_MAX_GROUP];
 };
 
-template <int DT, int FMT, bool FAST>
-__global__ void __launch_bounds__(TPB) sm_sign_pack_kernel(const sp_args a) {
-  const int di = sm_find(a.begin, a.n, blockIdx.x);
-  const sm_sp_desc& D = a.d[di];
-  const int local = blockIdx.x - a.begin.v[di];
-  const int b = local / D.blocks_per_row, bx = local - b * D.blocks_per_row;
-  const long long n = D.n, bytes_per_row = D.bytes_per_row;
-  const int cols = D.cols, ld = D.ld;
-  const unsigned short* ub = reinterpret_cast<const unsigned short*>(D.u) + (DT == SM_BF16 ? (long long)b * D.batch_stride : 0);
-  const unsigned* uf = reinterpret_cast<const unsigned*>(D.u) + (DT == SM_F32 ? (long long)b * D.batch_stride : 0);
-  unsigned char* o = reinterpret_cast<unsigned char*>(D.out) + (long long)b * D.out_stride;
-  constexpr int UNROLL = 4;
-  const long long q0 = ((long long)bx * UNROLL) * TPB + threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < UNROLL; ++j) {
-    const long long q = q0 + (long long)j * TPB;  // byte index
-    if (q >= bytes_per_row) break;
-    const long long e0 = q * 8;
-    unsigned bits = 0;
-    if (FAST && e0 + 8 <= n) {
-      const long long src = (ld == cols) ? e0 : (e0 / cols) * ld + (e0 % cols);
-      if (DT == SM_BF16) {
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ub + src));
-        const unsigned wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          bits |= ge0_bf16(wv[k] & 0xFFFFu) << (2 * k);
-          bits |= ge0_bf16(wv[k] >> 16) << (2 * k + 1);
-        }
-      } else {
-        const u32x4 v0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(uf + src));
-        const u32x4 v1 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(uf + src + 4));
-        const unsigned wv[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) bits |= ge0_f32(wv[k]) << k;
-      }
-      if (FMT == SM_SIGN_INT8) {
-        // +1 = 0x01, -1 = 0xFF
-        unsigned lo = 0, hi = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          lo |= (((bits >> k) & 1u) ? 0x01u : 0xFFu) << (8 * k);
-          hi |= (((bits >> (k + 4)) & 1u) ? 0x01u : 0xFFu) << (8 * k);
-        }
-        *reinterpret_cast<uint2*>(o + e0) = make_uint2(lo, hi);
-        continue;
-      }
-    } else {
-      for (int k = 0; k < 8; ++k) {
-        const long long e = e0 + k;
-        if (e >= n) break;
-        const long long src = (ld == cols) ? e : (e / cols) * ld + (e % cols);
-        const unsigned g = (DT == SM_BF16) ? ge0_bf16(ub[src]) : ge0_f32(uf[src]);
-        bits |= g << k;
-        if (FMT == SM_SIGN_INT8) o[e] = g ? 0x01 : 0xFF;
-      }
-      if (FMT == SM_SIGN_INT8) continue;
-    }
-    o[q] = (unsigned char)bits;
-  }
+template <int DT>
+__device__ __forceinline__ unsigned ge0_at(const void* u, long long i) {
+  return DT == SM_BF16 ? ge0_bf16(reinterpret_cast<const unsigned short*>(u)[i])
+                       : ge0_f32(reinterpret_cast<const unsigned*>(u)[i]);
 }
 
-// 1-bit output when every matrix of the launch can be read in whole 8-entry groups and its output is
-// 4-byte aligned: SPB_UNROLL bytes per thread, all loads issued before the first use, and the
-// bytes of four neighbouring lanes leave as one 32-bit store (byte stores cost a full store slot each).
-constexpr int SPB_UNROLL = 2;
+// Entry e of the flattened matrix in the source, which has padded rows (ROWS) or is flat; room: entries left in its row.
+template <bool ROWS>
+__device__ __forceinline__ long long sp_source(const sm_sp_desc& D, long long e, int& room) {
+  if (!ROWS) {
+    room = 0x7FFFFFFF;
+    return e;
+  }
+  long long r;
+  int c;
+  sm_row_of(D.by_cols, D.cols, e, r, c);
+  room = D.cols - c;
+  return r * D.ld + c;
+}
+
+// Bits of entries e0 .. e0 + E - 1 one at a time: the group that ends a matrix, or one that straddles rows of a
+// padded source.  Bits beyond entry n - 1 are zero.
+template <int DT, int E, bool ROWS>
+__device__ __forceinline__ unsigned sp_slow(const sm_sp_desc& D, const void* u, long long e0) {
+  unsigned bits = 0;
+  for (int k = 0; k < E; ++k) {
+    if (e0 + k >= D.n) break;
+    int room;
+    bits |= ge0_at<DT>(u, sp_source<ROWS>(D, e0 + k, room)) << k;
+  }
+  return bits;
+}
 
 template <int DT>
+__device__ __forceinline__ const void* sp_row(const sm_sp_desc& D, int b) {
+  return DT == SM_BF16 ? (const void*)(reinterpret_cast<const unsigned short*>(D.u) + (long long)b * D.batch_stride)
+                       : (const void*)(reinterpret_cast<const unsigned*>(D.u) + (long long)b * D.batch_stride);
+}
+
+// 1-bit output: a thread turns 8 entries into a byte, SP_UNROLL times; all loads are issued before the first use, and
+// the bytes of four neighbouring lanes leave as one 32-bit store (byte stores cost a full store slot each).  Rows of
+// the source may start at any element (odd lengths), rows of the output at any multiple of 8 bytes.
+constexpr int SP_UNROLL = 2;
+
+template <int DT, bool ROWS>
 __global__ void __launch_bounds__(TPB) sm_sign_pack_bits_kernel(const sp_args a) {
   const int di = sm_find(a.begin, a.n, blockIdx.x);
   const sm_sp_desc& D = a.d[di];
   const int local = blockIdx.x - a.begin.v[di];
   const int b = local / D.blocks_per_row, bx = local - b * D.blocks_per_row;
-  const long long n = D.n, bytes_per_row = D.bytes_per_row;  // a multiple of 8: a 4-lane group is in range as a whole
-  const int cols = D.cols, ld = D.ld;
-  const unsigned short* ub = reinterpret_cast<const unsigned short*>(D.u) + (DT == SM_BF16 ? (long long)b * D.batch_stride : 0);
-  const unsigned* uf = reinterpret_cast<const unsigned*>(D.u) + (DT == SM_F32 ? (long long)b * D.batch_stride : 0);
+  const long long n = D.n, bytes_per_row = 8 * ((n + 63) / 64);  // a multiple of 8: a 4-lane group is in range as a whole
+  const void* u = sp_row<DT>(D, b);
   unsigned char* o = reinterpret_cast<unsigned char*>(D.out) + (long long)b * D.out_stride;
-  const long long q0 = ((long long)bx * SPB_UNROLL) * TPB + threadIdx.x;
-  u32x4 v0[SPB_UNROLL], v1[SPB_UNROLL];
+  const long long q0 = ((long long)bx * SP_UNROLL) * TPB + threadIdx.x;
+  u32x4 v0[SP_UNROLL], v1[SP_UNROLL];
+  bool whole[SP_UNROLL];
 #pragma unroll
-  for (int j = 0; j < SPB_UNROLL; ++j) {
+  for (int j = 0; j < SP_UNROLL; ++j) {
     const long long e0 = (q0 + (long long)j * TPB) * 8;
     v0[j] = v1[j] = u32x4{0u, 0u, 0u, 0u};
+    whole[j] = false;
     if (e0 + 8 <= n) {
-      const long long src = (ld == cols) ? e0 : (e0 / cols) * ld + (e0 % cols);
-      if (DT == SM_BF16) {
-        v0[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ub + src));
-      } else {
-        v0[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(uf + src));
-        v1[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(uf + src + 4));
+      int room;
+      const long long src = sp_source<ROWS>(D, e0, room);
+      whole[j] = room >= 8;
+      if (whole[j]) {
+        if (DT == SM_BF16) {
+          v0[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(reinterpret_cast<const unsigned short*>(u) + src));
+        } else {
+          v0[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(reinterpret_cast<const unsigned*>(u) + src));
+          v1[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(reinterpret_cast<const unsigned*>(u) + src + 4));
+        }
       }
     }
   }
 #pragma unroll
-  for (int j = 0; j < SPB_UNROLL; ++j) {
+  for (int j = 0; j < SP_UNROLL; ++j) {
     const long long q = q0 + (long long)j * TPB;  // byte index
-    const long long e0 = q * 8;
     unsigned bits = 0;
-    if (e0 + 8 <= n) {
+    if (whole[j]) {
       if (DT == SM_BF16) {
-        const unsigned wv[4] = {v0[j].x, v0[j].y, v0[j].z, v0[j].w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          bits |= ge0_bf16(wv[k] & 0xFFFFu) << (2 * k);
-          bits |= ge0_bf16(wv[k] >> 16) << (2 * k + 1);
+          bits |= ge0_bf16(v0[j][k] & 0xFFFFu) << (2 * k);
+          bits |= ge0_bf16(v0[j][k] >> 16) << (2 * k + 1);
         }
       } else {
-        const unsigned wv[8] = {v0[j].x, v0[j].y, v0[j].z, v0[j].w, v1[j].x, v1[j].y, v1[j].z, v1[j].w};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) bits |= ge0_f32(wv[k]) << k;
+        for (int k = 0; k < 4; ++k) bits |= (ge0_f32(v0[j][k]) << k) | (ge0_f32(v1[j][k]) << (k + 4));
       }
-    } else {  // the group that holds entry n - 1, and the zero padding after it
-      for (int k = 0; k < 8; ++k) {
-        const long long e = e0 + k;
-        if (e >= n) break;
-        const long long src = (ld == cols) ? e : (e / cols) * ld + (e % cols);
-        bits |= ((DT == SM_BF16) ? ge0_bf16(ub[src]) : ge0_f32(uf[src])) << k;
-      }
+    } else {
+      bits = sp_slow<DT, 8, ROWS>(D, u, q * 8);
     }
     bits |= __shfl_down(bits, 1, 64) << 8;
     bits |= __shfl_down(bits, 2, 64) << 16;
     if ((threadIdx.x & 3) == 0 && q < bytes_per_row) __builtin_nontemporal_store(bits, reinterpret_cast<unsigned*>(o + q));
+  }
+}
+
+// Four signs as int8: +1 = 0x01, -1 = 0xFF.
+__device__ __forceinline__ unsigned pm1_bytes(unsigned bits) {
+  unsigned v = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v |= (((bits >> k) & 1u) ? 0x01u : 0xFFu) << (8 * k);
+  return v;
+}
+
+// int8 output: a thread turns 16 bytes of the source (8 bf16 or 4 f32 entries) into as many signs, SP8_UNROLL times,
+// loads first.  Rows of source and output may start at any element.
+constexpr int SP8_UNROLL = 4;
+
+template <int DT, bool ROWS>
+__global__ void __launch_bounds__(TPB) sm_sign_pack_int8_kernel(const sp_args a) {
+  constexpr int E = (DT == SM_BF16) ? 8 : 4;
+  const int di = sm_find(a.begin, a.n, blockIdx.x);
+  const sm_sp_desc& D = a.d[di];
+  const int local = blockIdx.x - a.begin.v[di];
+  const int b = local / D.blocks_per_row, bx = local - b * D.blocks_per_row;
+  const long long n = D.n;
+  const void* u = sp_row<DT>(D, b);
+  unsigned char* o = reinterpret_cast<unsigned char*>(D.out) + (long long)b * D.out_stride;
+  const long long q0 = ((long long)bx * SP8_UNROLL) * TPB + threadIdx.x;
+  u32x4 v[SP8_UNROLL];
+  bool whole[SP8_UNROLL];
+#pragma unroll
+  for (int j = 0; j < SP8_UNROLL; ++j) {
+    const long long e0 = (q0 + (long long)j * TPB) * E;
+    v[j] = u32x4{0u, 0u, 0u, 0u};
+    whole[j] = false;
+    if (e0 + E <= n) {
+      int room;
+      const long long src = sp_source<ROWS>(D, e0, room);
+      whole[j] = room >= E;
+      if (whole[j])
+        v[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(
+            DT == SM_BF16 ? (const void*)(reinterpret_cast<const unsigned short*>(u) + src)
+                          : (const void*)(reinterpret_cast<const unsigned*>(u) + src)));
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < SP8_UNROLL; ++j) {
+    const long long e0 = (q0 + (long long)j * TPB) * E;
+    if (e0 >= n) break;
+    if (whole[j]) {
+      unsigned bits = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (DT == SM_BF16)
+          bits |= (ge0_bf16(v[j][k] & 0xFFFFu) << (2 * k)) | (ge0_bf16(v[j][k] >> 16) << (2 * k + 1));
+        else
+          bits |= ge0_f32(v[j][k]) << k;
+      }
+      if (DT == SM_BF16)
+        *reinterpret_cast<u32x2_u*>(o + e0) = u32x2{pm1_bytes(bits), pm1_bytes(bits >> 4)};
+      else
+        *reinterpret_cast<u32_u*>(o + e0) = pm1_bytes(bits);
+    } else {
+      const unsigned bits = sp_slow<DT, E, ROWS>(D, u, e0);
+      for (int k = 0; k < E && e0 + k < n; ++k) o[e0 + k] = ((bits >> k) & 1u) ? 0x01 : 0xFF;
+    }
   }
 }
 
@@ -404,26 +436,6 @@ __global__ void __launch_bounds__(TPB) sm_vote_bits_kernel(const unsigned long l
   }
 }
 
-// Voted bits for any M (used beyond 255 workers): one thread = one byte.
-__global__ void __launch_bounds__(TPB) sm_vote_bits_generic_kernel(const unsigned char* __restrict__ signs, int M,
-                                                                   long long n, long long stride_bytes,
-                                                                   unsigned char* __restrict__ voted,
-                                                                   long long bytes_out) {
-  const long long q = (long long)blockIdx.x * TPB + threadIdx.x;
-  if (q >= bytes_out) return;
-  int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int p = 0; p < M; ++p) {
-    const unsigned b = signs[(long long)p * stride_bytes + q];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) c[k] += (b >> k) & 1u;
-  }
-  unsigned bits = 0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    if (q * 8 + k < n && 2 * c[k] >= M) bits |= 1u << k;
-  voted[q] = (unsigned char)bits;
-}
-
 typedef sm_vote_desc vote_x_args;
 struct vote_g_args {
   int n;
@@ -432,127 +444,95 @@ struct vote_g_args {
   sm_vote_desc d[SM_VOTE_MAX_GROUP];
 };
 
-// Expanding vote: one thread = 4 consecutive entries.  FMT selects the input
-// transport; outputs (voted in a non-bit format, counts, fused W update) are all
-// optional.  n4 = ceil(n/4) threads in total.
-template <int FMT>
-__global__ void __launch_bounds__(TPB) sm_vote_expand_kernel(const vote_g_args g) {
-  const int di = sm_find(g.begin, g.n, blockIdx.x);
-  const vote_x_args& a = g.d[di];
-  const long long t = (long long)(blockIdx.x - g.begin.v[di]) * TPB + threadIdx.x;
-  const long long e0 = t * 4;
-  if (e0 >= a.n) return;
-  int c[4] = {0, 0, 0, 0};
-  if (FMT == SM_SIGN_1BIT) {
-    const unsigned* base = reinterpret_cast<const unsigned*>(a.signs) + (e0 >> 5);
-    const int sh = (int)(e0 & 31);
-    const long long stride_w = a.stride_bytes >> 2;
-    int p = 0;
-    while (p < a.M) {
-      const int lim = min(a.M, p + 255);
-      unsigned acc = 0;
-      for (; p < lim; ++p) {
-        const unsigned nib = (base[(long long)p * stride_w] >> sh) & 0xFu;
-        acc += (nib * 0x00204081u) & 0x01010101u;
-      }
+// Stores of up to four consecutive results; `live` of them exist.
+__device__ __forceinline__ void step4(float* w, float lr, const f32x4 old, unsigned bits, int live) {
+  f32x4 o;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] += (acc >> (8 * k)) & 0xFF;
+  for (int k = 0; k < 4; ++k) o[k] = __fsub_rn(old[k], __fmul_rn(lr, ((bits >> k) & 1u) ? 1.0f : -1.0f));
+  if (live == 4) {
+    __builtin_nontemporal_store(o, reinterpret_cast<f32x4_u*>(w));
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < live) w[k] = o[k];
+  }
+}
+__device__ __forceinline__ f32x4 load4(const float* w, int live) {
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  if (live == 4) {
+    o = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(w));
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < live) o[k] = w[k];
+  }
+  return o;
+}
+__device__ __forceinline__ void counts4(int32_t* c, const i32x4 v, int live) {
+  if (live == 4) {
+    *reinterpret_cast<i32x4_u*>(c) = v;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < live) c[k] = v[k];
+  }
+}
+__device__ __forceinline__ unsigned pm1_bf16(unsigned two) {
+  return ((two & 1u) ? 0x3F80u : 0xBF80u) | ((two & 2u) ? 0x3F800000u : 0xBF800000u);
+}
+// four voted entries in format vfmt at entry `at` of the output
+__device__ __forceinline__ void voted4(void* voted, int vfmt, long long at, unsigned bits, int live) {
+  if (vfmt == SM_VOTE_INT8) {
+    unsigned char* o = reinterpret_cast<unsigned char*>(voted) + at;
+    const unsigned v = pm1_bytes(bits);
+    if (live == 4) {
+      *reinterpret_cast<u32_u*>(o) = v;
+    } else {
+      for (int k = 0; k < live; ++k) o[k] = (unsigned char)(v >> (8 * k));
+    }
+  } else if (vfmt == SM_VOTE_BF16) {
+    unsigned short* o = reinterpret_cast<unsigned short*>(voted) + at;
+    const u32x2 v = {pm1_bf16(bits), pm1_bf16(bits >> 2)};
+    if (live == 4) {
+      *reinterpret_cast<u32x2_u*>(o) = v;
+    } else {
+      for (int k = 0; k < live; ++k) o[k] = (unsigned short)(v[k >> 1] >> (16 * (k & 1)));
     }
   } else {
-    const signed char* base = reinterpret_cast<const signed char*>(a.signs) + e0;
-    if (e0 + 4 <= a.n && (a.stride_bytes & 3) == 0 && (reinterpret_cast<uintptr_t>(a.signs) & 3) == 0) {
-      for (int p = 0; p < a.M; ++p) {
-        const unsigned v = __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(base + (long long)p * a.stride_bytes));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c[k] += (int)(signed char)(v >> (8 * k));
-      }
-    } else {
-      for (int p = 0; p < a.M; ++p)
-        for (int k = 0; k < 4; ++k)
-          if (e0 + k < a.n) c[k] += base[(long long)p * a.stride_bytes + k];
-    }
-  }
-  float s[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const bool plus = (FMT == SM_SIGN_1BIT) ? (2 * c[k] >= a.M) : (c[k] >= 0);
-    s[k] = plus ? 1.0f : -1.0f;
-  }
-  const bool full = (e0 + 4 <= a.n);
-  if (a.counts) {
-    if (full) {
-      *reinterpret_cast<int4*>(a.counts + e0) = make_int4(c[0], c[1], c[2], c[3]);
-    } else {
-      for (int k = 0; k < 4 && e0 + k < a.n; ++k) a.counts[e0 + k] = c[k];
-    }
-  }
-  if (a.w) {
-    if (full) {
-      float4 wv = *reinterpret_cast<float4*>(a.w + e0);
-      wv.x = __fsub_rn(wv.x, __fmul_rn(a.lr, s[0]));
-      wv.y = __fsub_rn(wv.y, __fmul_rn(a.lr, s[1]));
-      wv.z = __fsub_rn(wv.z, __fmul_rn(a.lr, s[2]));
-      wv.w = __fsub_rn(wv.w, __fmul_rn(a.lr, s[3]));
-      *reinterpret_cast<float4*>(a.w + e0) = wv;
-    } else {
-      for (int k = 0; k < 4 && e0 + k < a.n; ++k) a.w[e0 + k] = __fsub_rn(a.w[e0 + k], __fmul_rn(a.lr, s[k]));
-    }
-  }
-  if (a.voted) {
-    const bool flat = (a.ld == a.cols);
-    if (a.vfmt == SM_VOTE_INT8) {
-      signed char* o = reinterpret_cast<signed char*>(a.voted);
-      if (full) {
-        unsigned v = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v |= (s[k] > 0.f ? 0x01u : 0xFFu) << (8 * k);
-        *reinterpret_cast<unsigned*>(o + e0) = v;
-      } else {
-        for (int k = 0; k < 4 && e0 + k < a.n; ++k) o[e0 + k] = s[k] > 0.f ? 1 : -1;
-      }
-    } else if (a.vfmt == SM_VOTE_BF16) {
-      bf16_t* o = reinterpret_cast<bf16_t*>(a.voted);
-      if (full && (flat || (a.cols & 3) == 0)) {
-        const long long di = flat ? e0 : (e0 / a.cols) * a.ld + (e0 % a.cols);
-        bf16x4 h = {(bf16_t)s[0], (bf16_t)s[1], (bf16_t)s[2], (bf16_t)s[3]};
-        *reinterpret_cast<bf16x4*>(o + di) = h;
-      } else {
-        for (int k = 0; k < 4 && e0 + k < a.n; ++k) {
-          const long long e = e0 + k;
-          o[flat ? e : (e / a.cols) * a.ld + (e % a.cols)] = (bf16_t)s[k];
-        }
-      }
-    } else if (a.vfmt == SM_VOTE_F32) {
-      float* o = reinterpret_cast<float*>(a.voted);
-      if (full && (flat || (a.cols & 3) == 0)) {
-        const long long di = flat ? e0 : (e0 / a.cols) * a.ld + (e0 % a.cols);
-        *reinterpret_cast<float4*>(o + di) = make_float4(s[0], s[1], s[2], s[3]);
-      } else {
-        for (int k = 0; k < 4 && e0 + k < a.n; ++k) {
-          const long long e = e0 + k;
-          o[flat ? e : (e / a.cols) * a.ld + (e % a.cols)] = s[k];
-        }
-      }
-    }
+    float* o = reinterpret_cast<float*>(voted) + at;
+    for (int k = 0; k < live; ++k) o[k] = ((bits >> k) & 1u) ? 1.0f : -1.0f;
   }
 }
 
-// Packs +-1 int32 sums (int8 transport) into voted bits: one thread = one byte.
+// Voted bits from int8 signs: a thread sums 8 consecutive entries over the workers and makes a byte of them; the bytes
+// of four lanes leave as one 32-bit store.
 __global__ void __launch_bounds__(TPB) sm_vote_int8_bits_kernel(const signed char* __restrict__ signs, int M,
                                                                 long long n, long long stride_bytes,
                                                                 unsigned char* __restrict__ voted,
                                                                 long long bytes_out) {
   const long long q = (long long)blockIdx.x * TPB + threadIdx.x;
-  if (q >= bytes_out) return;
+  const long long e0 = q * 8;
+  int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   unsigned bits = 0;
-  for (int k = 0; k < 8; ++k) {
-    const long long e = q * 8 + k;
-    if (e >= n) break;
-    int s = 0;
-    for (int p = 0; p < M; ++p) s += signs[(long long)p * stride_bytes + e];
-    bits |= (s >= 0 ? 1u : 0u) << k;
+  if (e0 + 8 <= n) {
+#pragma unroll 4
+    for (int p = 0; p < M; ++p) {
+      const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2_u*>(signs + (long long)p * stride_bytes + e0));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) c[k] += (int)(signed char)(v[k >> 2] >> (8 * (k & 3)));
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) bits |= (c[k] >= 0 ? 1u : 0u) << k;
+  } else {
+    for (int k = 0; k < 8 && e0 + k < n; ++k) {
+      int t = 0;
+      for (int p = 0; p < M; ++p) t += signs[(long long)p * stride_bytes + e0 + k];
+      bits |= (t >= 0 ? 1u : 0u) << k;
+    }
   }
-  voted[q] = (unsigned char)bits;
+  bits |= __shfl_down(bits, 1, 64) << 8;
+  bits |= __shfl_down(bits, 2, 64) << 16;
+  if ((threadIdx.x & 3) == 0 && q < bytes_out) *reinterpret_cast<unsigned*>(voted + q) = bits;  // bytes_out % 8 == 0
 }
 
 // ------------------------------------------------------------------ update after a local polar step
@@ -563,10 +543,10 @@ struct upd_args {
   sm_upd_desc d[SM_UPD_MAX_GROUP];
 };
 
-// A workgroup owns UPD_ITERS * TPB * 4 consecutive entries of one block: UPD_ITERS rounds of 4 entries per
-// thread, all loads of a round set issued before the first store.
+// A workgroup owns UPD_ITERS * TPB groups of four entries, each inside a row (the last group of a row may be short),
+// UPD_ITERS per thread; all loads are issued before the first store.
 constexpr int UPD_ITERS = 4;
-constexpr int UPD_CHUNK = UPD_ITERS * TPB * 4;
+constexpr int UPD_CHUNK = UPD_ITERS * TPB;  // groups
 
 __global__ void __launch_bounds__(TPB) sm_update_kernel(const upd_args g) {
   const int di = sm_find(g.begin, g.n, blockIdx.x);
@@ -575,47 +555,42 @@ __global__ void __launch_bounds__(TPB) sm_update_kernel(const upd_args g) {
   const bf16_t* __restrict__ d = D.d;
   const int cols = D.cols, ld = D.ld;
   const float step = D.kappa ? __fmul_rn(D.step, D.kappa[0]) : D.step;
-  const long long n = (long long)D.rows * cols;
-  const long long base = (long long)(blockIdx.x - g.begin.v[di]) * UPD_CHUNK + threadIdx.x * 4;
-  if ((cols & 3) == 0 && base - threadIdx.x * 4 + UPD_CHUNK <= n) {  // a full chunk of whole groups of 4
-    bf16x4 h[UPD_ITERS];
-    f32x4 wv[UPD_ITERS];
+  const int q = (cols + 3) >> 2;
+  const long long groups = (long long)D.rows * q;
+  const long long base = (long long)(blockIdx.x - g.begin.v[di]) * UPD_CHUNK + threadIdx.x;
+  bf16x4 h[UPD_ITERS];
+  f32x4 wv[UPD_ITERS];
+  long long at[UPD_ITERS];
+  int live[UPD_ITERS];
 #pragma unroll
-    for (int it = 0; it < UPD_ITERS; ++it) {
-      const long long e0 = base + (long long)it * (TPB * 4);
-      const long long di4 = (ld == cols) ? e0 : (e0 / cols) * ld + (e0 % cols);
-      h[it] = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(d + di4));
-      wv[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(w + e0));
-    }
-#pragma unroll
-    for (int it = 0; it < UPD_ITERS; ++it) {
-      const long long e0 = base + (long long)it * (TPB * 4);
-      wv[it].x = __fsub_rn(wv[it].x, __fmul_rn(step, (float)h[it][0]));
-      wv[it].y = __fsub_rn(wv[it].y, __fmul_rn(step, (float)h[it][1]));
-      wv[it].z = __fsub_rn(wv[it].z, __fmul_rn(step, (float)h[it][2]));
-      wv[it].w = __fsub_rn(wv[it].w, __fmul_rn(step, (float)h[it][3]));
-      __builtin_nontemporal_store(wv[it], reinterpret_cast<f32x4*>(w + e0));
-    }
-    return;
-  }
   for (int it = 0; it < UPD_ITERS; ++it) {
-    const long long e0 = base + (long long)it * (TPB * 4);
-    if (e0 >= n) return;
-    if (e0 + 4 <= n && (cols & 3) == 0) {
-      const long long di4 = (ld == cols) ? e0 : (e0 / cols) * ld + (e0 % cols);
-      const bf16x4 h = *reinterpret_cast<const bf16x4*>(d + di4);
-      float4 wv = *reinterpret_cast<float4*>(w + e0);
-      wv.x = __fsub_rn(wv.x, __fmul_rn(step, (float)h[0]));
-      wv.y = __fsub_rn(wv.y, __fmul_rn(step, (float)h[1]));
-      wv.z = __fsub_rn(wv.z, __fmul_rn(step, (float)h[2]));
-      wv.w = __fsub_rn(wv.w, __fmul_rn(step, (float)h[3]));
-      *reinterpret_cast<float4*>(w + e0) = wv;
+    const long long t = base + it * TPB;
+    h[it] = bf16x4{0, 0, 0, 0};
+    wv[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    at[it] = 0;
+    live[it] = 0;
+    if (t < groups) {
+      long long r;
+      int c;
+      sm_row_of(D.quads, q, t, r, c);
+      c *= 4;
+      at[it] = r * cols + c;
+      live[it] = min(4, cols - c);
+      h[it] = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(d + r * ld + c));
+      wv[it] = load4(w + at[it], live[it]);
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < UPD_ITERS; ++it) {
+    if (live[it] == 0) break;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wv[it][k] = __fsub_rn(wv[it][k], __fmul_rn(step, (float)h[it][k]));
+    if (live[it] == 4) {
+      __builtin_nontemporal_store(wv[it], reinterpret_cast<f32x4_u*>(w + at[it]));
     } else {
-      for (int k = 0; k < 4 && e0 + k < n; ++k) {
-        const long long e = e0 + k;
-        const float dv = (float)d[(e / cols) * ld + (e % cols)];
-        w[e] = __fsub_rn(w[e], __fmul_rn(step, dv));
-      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < live[it]) w[at[it] + k] = wv[it][k];
     }
   }
 }
@@ -635,14 +610,10 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
     a.omb = 1.0f - beta;
     a.wd = wd;
     long long blocks = 0;
-    bool vec = true;
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
       a.begin.v[i] = (int)blocks;
       blocks += (long long)M * a.d[i].chunks;
-      const sm_mom_desc& D = a.d[i];
-      vec = vec && (D.d % 4 == 0) && sm_aligned(D.mom, 16) && sm_aligned(D.grad, 16) &&
-            (!D.w || sm_aligned(D.w, 16)) && (!D.x || (sm_aligned(D.x, 8) && D.ld % 4 == 0 && D.x_stride % 4 == 0));
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "momentum: too many entries for one launch");
     a.shift = 0;
@@ -654,10 +625,7 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
     }
     if (blocks > 0) {
       sm_launch_scope sc(ctx, SM_K_MOMENTUM);
-      if (vec)
-        hipLaunchKernelGGL(sm_momentum_kernel<true>, dim3((unsigned)blocks), dim3(TPB), 0, ctx->stream, a);
-      else
-        hipLaunchKernelGGL(sm_momentum_kernel<false>, dim3((unsigned)blocks), dim3(TPB), 0, ctx->stream, a);
+      hipLaunchKernelGGL(sm_momentum_kernel, dim3((unsigned)blocks), dim3(TPB), 0, ctx->stream, a);
     }
     SM_HIP(ctx, hipGetLastError());
     done += g;
@@ -668,14 +636,6 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
 int sm_launch_reduce_partials(signmuon_ctx* ctx, const float* partial, int chunks, int count, float* sumsq) {
   sm_launch_scope sc(ctx, SM_K_OTHER);
   hipLaunchKernelGGL(sm_reduce_partials_kernel, dim3(count), dim3(TPB), 0, ctx->stream, partial, chunks, sumsq);
-  SM_HIP(ctx, hipGetLastError());
-  return SM_OK;
-}
-
-int sm_launch_inv_sigma(signmuon_ctx* ctx, const float* sig, int count, float eps, bool from_sq, float* inv_sigma) {
-  sm_launch_scope sc(ctx, SM_K_OTHER);
-  hipLaunchKernelGGL(sm_inv_sigma_kernel, dim3((count + 255) / 256), dim3(256), 0, ctx->stream, sig, count, eps,
-                     from_sq ? 1 : 0, inv_sigma);
   SM_HIP(ctx, hipGetLastError());
   return SM_OK;
 }
@@ -712,48 +672,30 @@ int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n,
     sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
-    int blocks = 0;
-    bool fast_ok = true;
+    // entries per workgroup
+    const int per_block = TPB * (fmt == SM_SIGN_1BIT ? 8 * SP_UNROLL : (dtype == SM_BF16 ? 8 : 4) * SP8_UNROLL);
+    long long blocks = 0;
+    bool rows = false;
     for (int i = 0; i < g; ++i) {
       sm_sp_desc& D = a.d[i];
       D = descs[done + i];
-      D.bytes_per_row = (fmt == SM_SIGN_1BIT) ? 8 * ((D.n + 63) / 64) : (D.n + 7) / 8;  // threads per row
-      // the fast path reads whole 8-entry groups with 16-byte loads
-      fast_ok = fast_ok && (D.ld == D.cols || (D.cols % 8 == 0 && D.ld % 8 == 0)) && sm_aligned(D.u, 16) &&
-                (D.batch_stride % 8 == 0) &&
-                (fmt == SM_SIGN_1BIT ? (sm_aligned(D.out, 4) && D.out_stride % 4 == 0)
-                                     : (sm_aligned(D.out, 8) && D.out_stride % 8 == 0));
+      D.by_cols = sm_div_by((unsigned)D.cols);
+      rows = rows || D.ld != D.cols;
+      D.blocks_per_row = (int)(((D.n + 63) / 64 * 64 + per_block - 1) / per_block);
+      a.begin.v[i] = (int)blocks;
+      blocks += (long long)D.blocks_per_row * M;
     }
-    const int per_block = TPB * ((fmt == SM_SIGN_1BIT && fast_ok) ? SPB_UNROLL : 4);  // output bytes (threads' groups)
-    for (int i = 0; i < g; ++i) {
-      sm_sp_desc& D = a.d[i];
-      D.blocks_per_row = (int)((D.bytes_per_row + per_block - 1) / per_block);
-      a.begin.v[i] = blocks;
-      blocks += D.blocks_per_row * M;
-    }
+    if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "sign pack: too many entries for one launch");
     if (blocks > 0) {
-      const dim3 grid(blocks);
+      const dim3 grid((unsigned)blocks), block(TPB);
       sm_launch_scope sc(ctx, SM_K_SIGN_PACK);
-#define SP_LAUNCH(DT, FMT, FAST) hipLaunchKernelGGL((sm_sign_pack_kernel<DT, FMT, FAST>), grid, dim3(TPB), 0, ctx->stream, a)
-      if (dtype == SM_BF16) {
-        if (fmt == SM_SIGN_1BIT) {
-          if (fast_ok)
-            hipLaunchKernelGGL((sm_sign_pack_bits_kernel<SM_BF16>), grid, dim3(TPB), 0, ctx->stream, a);
-          else
-            SP_LAUNCH(SM_BF16, SM_SIGN_1BIT, false);
-        } else {
-          if (fast_ok) SP_LAUNCH(SM_BF16, SM_SIGN_INT8, true); else SP_LAUNCH(SM_BF16, SM_SIGN_INT8, false);
-        }
-      } else {
-        if (fmt == SM_SIGN_1BIT) {
-          if (fast_ok)
-            hipLaunchKernelGGL((sm_sign_pack_bits_kernel<SM_F32>), grid, dim3(TPB), 0, ctx->stream, a);
-          else
-            SP_LAUNCH(SM_F32, SM_SIGN_1BIT, false);
-        } else {
-          if (fast_ok) SP_LAUNCH(SM_F32, SM_SIGN_INT8, true); else SP_LAUNCH(SM_F32, SM_SIGN_INT8, false);
-        }
-      }
+#define SP_LAUNCH(KERNEL, DT)                                                                                  \
+  if (rows) hipLaunchKernelGGL((KERNEL<DT, true>), grid, block, 0, ctx->stream, a);                            \
+  else hipLaunchKernelGGL((KERNEL<DT, false>), grid, block, 0, ctx->stream, a)
+      if (fmt == SM_SIGN_1BIT && dtype == SM_BF16) { SP_LAUNCH(sm_sign_pack_bits_kernel, SM_BF16); }
+      else if (fmt == SM_SIGN_1BIT) { SP_LAUNCH(sm_sign_pack_bits_kernel, SM_F32); }
+      else if (dtype == SM_BF16) { SP_LAUNCH(sm_sign_pack_int8_kernel, SM_BF16); }
+      else { SP_LAUNCH(sm_sign_pack_int8_kernel, SM_F32); }
 #undef SP_LAUNCH
     }
     SM_HIP(ctx, hipGetLastError());
@@ -762,18 +704,17 @@ int sm_launch_sign_pack_group(signmuon_ctx* ctx, const sm_sp_desc* descs, int n,
   return SM_OK;
 }
 
-int sm_launch_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, int rows, int cols, int ld,
-                        long long batch_stride, int fmt, void* out, long long out_stride_bytes) {
+int sm_launch_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, long long n, int fmt, void* out,
+                        long long out_stride_bytes) {
   sm_sp_desc D;
   D.u = u;
   D.out = out;
-  D.n = (long long)rows * cols;
-  D.batch_stride = batch_stride;
+  D.n = n;
+  D.batch_stride = n;
   D.out_stride = out_stride_bytes;
-  D.bytes_per_row = 0;
-  D.cols = cols;
-  D.ld = ld;
+  D.cols = D.ld = (int)n;
   D.blocks_per_row = 0;
+  D.pad_ = 0;
   return sm_launch_sign_pack_group(ctx, &D, 1, dtype, fmt, batch);
 }
 
@@ -795,9 +736,7 @@ int sm_launch_vote(signmuon_ctx* ctx, const sm_vote_args& v) {
       else if (v.M < 256)
         hipLaunchKernelGGL(sm_vote_bits_kernel<8>, grid, dim3(TPB), 0, ctx->stream, sp, v.M, words, v.stride_bytes / 8, n, vp);
       else
-        hipLaunchKernelGGL(sm_vote_bits_generic_kernel, dim3((unsigned)((words * 8 + TPB - 1) / TPB)), dim3(TPB), 0,
-                           ctx->stream, reinterpret_cast<const unsigned char*>(v.signs), v.M, n, v.stride_bytes,
-                           reinterpret_cast<unsigned char*>(v.voted), words * 8);
+        hipLaunchKernelGGL(sm_vote_bits_kernel<31>, grid, dim3(TPB), 0, ctx->stream, sp, v.M, words, v.stride_bytes / 8, n, vp);
     } else {
       const long long bytes_out = 8 * ((n + 63) / 64);
       hipLaunchKernelGGL(sm_vote_int8_bits_kernel, dim3((unsigned)((bytes_out + TPB - 1) / TPB)), dim3(TPB), 0,
@@ -817,109 +756,134 @@ int sm_launch_vote(signmuon_ctx* ctx, const sm_vote_args& v) {
     a.lr = v.lr_scaled;
     a.M = v.M;
     a.vfmt = v.vfmt;
-    a.cols = v.cols;
-    a.ld = v.ld;
+    a.cols = a.sld = a.ld = 0;
     return sm_launch_vote_group(ctx, &a, 1, v.fmt);
   }
   return SM_OK;
 }
 
-// Expanding vote over 1-bit signs, wide form: a lane takes one 32-bit word of every worker's
-// buffer per run, counted bit-sliced (PLANES binary counter planes, M < 2^PLANES) and compared with
-// ceil(M/2) as in sm_vote_bits_kernel.  The 2048 votes of a run are then spread over the wave's
-// lanes so that every store (and every load of W) covers consecutive addresses: lane l
-// writes 8 consecutive bf16 per store (4 stores), and steps 4 consecutive weights per load
-// and store (8 of each).  For tables whose entries have n % 32 == 0, no counts output and, if
-// a voted matrix is asked for, the flat bf16 form.
-// A wave takes VW_GROUPS runs of 64 consecutive words; the loads of all runs (eight workers at a time) are
-// issued before the first is counted.  Measured: one run per wave is fastest (fused W update on 85 M entries,
-// M = 8: 125 us against 136 us with two or four runs); what matters is that the eight loads are in flight together.
-constexpr int VW_GROUPS = 1;
-
-template <int PLANES>
+// Expanding vote over 1-bit signs: a lane takes one 32-bit word of every worker's buffer, counted bit-sliced
+// (PLANES binary counter planes, M < 2^PLANES) and compared with ceil(M/2) as in sm_vote_bits_kernel.  The 2048 votes
+// of a wave are then spread over its lanes so that every store (and every load of W) covers consecutive addresses:
+// lane l writes 8 consecutive bf16 per store, and takes 4 consecutive weights or counts at a time.  The loads of eight
+// workers, and the eight loads of W, are in flight together (fused W update on 85 M entries, M = 8: 125 us; two or four
+// runs of words per wave: 136 us).
+// ROWS: the signs are rows of sld entries, so a word also has a row and a number of entries that count; the flat
+// outputs then start at any element.  Otherwise one run of n entries, whose last word may be partial.
+template <int PLANES, bool ROWS>
 __global__ void __launch_bounds__(TPB) sm_vote_wide_kernel(const vote_g_args g) {
   const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
-  const long long words = a.n >> 5;
+  const long long words = (a.n + 31) >> 5;
   const int lane = threadIdx.x & 63;
-  // the wave's first word: a workgroup covers TPB * VW_GROUPS words
-  const long long wbase = ((long long)(blockIdx.x - g.begin.v[di]) * TPB + (threadIdx.x & ~63)) * VW_GROUPS;
+  const long long w0 = (long long)(blockIdx.x - g.begin.v[di]) * TPB + (threadIdx.x & ~63);  // the wave's first word
+  if (w0 >= words) return;
   const long long stride_w = a.stride_bytes >> 2;
-  const unsigned* sbase = reinterpret_cast<const unsigned*>(a.signs);
-  unsigned plane[VW_GROUPS][PLANES];
+  const unsigned* sbase = reinterpret_cast<const unsigned*>(a.signs) + w0 + lane;
+  const bool in = w0 + lane < words;
+  unsigned plane[PLANES];
 #pragma unroll
-  for (int r = 0; r < VW_GROUPS; ++r)
-#pragma unroll
-    for (int k = 0; k < PLANES; ++k) plane[r][k] = 0;
+  for (int k = 0; k < PLANES; ++k) plane[k] = 0;
   for (int pb = 0; pb < a.M; pb += VOTE_GROUP) {
-    unsigned x[VW_GROUPS][VOTE_GROUP];
+    unsigned x[VOTE_GROUP];
 #pragma unroll
-    for (int r = 0; r < VW_GROUPS; ++r) {
-      const long long wi = wbase + 64 * r + lane;
-#pragma unroll
-      for (int q = 0; q < VOTE_GROUP; ++q) {
-        x[r][q] = 0;
-        if (wi < words && pb + q < a.M) x[r][q] = __builtin_nontemporal_load(sbase + (long long)(pb + q) * stride_w + wi);
-      }
+    for (int q = 0; q < VOTE_GROUP; ++q) {
+      x[q] = 0;
+      if (in && pb + q < a.M) x[q] = __builtin_nontemporal_load(sbase + (long long)(pb + q) * stride_w);
     }
 #pragma unroll
-    for (int r = 0; r < VW_GROUPS; ++r)
-#pragma unroll
-      for (int q = 0; q < VOTE_GROUP; ++q) planes_add<PLANES>(plane[r], x[r][q]);
+    for (int q = 0; q < VOTE_GROUP; ++q) planes_add<PLANES>(plane, x[q]);
   }
-  const unsigned T = (unsigned)((a.M + 1) / 2);
+  const unsigned v = planes_ge<PLANES>(plane, (unsigned)((a.M + 1) / 2));
+  int row = 0, live = 0;  // of the lane's own word
+  if (ROWS && in) {
+    long long r;
+    int c;
+    sm_row_of(a.by_row, a.sld >> 5, w0 + lane, r, c);
+    row = (int)r;
+    live = min(32, a.cols - 32 * c);
+  }
+  // entries that count in word t of the wave, and where its first entry lies in a flat output
+  auto live_of = [&](int t) {
+    if (ROWS) return __shfl(live, t, 64);
+    const long long rem = a.n - 32 * (w0 + t);
+    return (int)(rem < 0 ? 0 : rem > 32 ? 32 : rem);
+  };
+  auto flat_of = [&](int t) {
+    const long long e = 32 * (w0 + t);
+    return ROWS ? e - (long long)__shfl(row, t, 64) * (a.sld - a.cols) : e;
+  };
+  if (a.voted && a.vfmt == SM_VOTE_BF16) {
+    const bool padded = ROWS && a.ld == a.sld;
+    unsigned short* o = reinterpret_cast<unsigned short*>(a.voted);
 #pragma unroll
-  for (int r = 0; r < VW_GROUPS; ++r) {
-    const long long w0 = wbase + 64 * r;  // the run's first word
-    if (w0 >= words) break;               // wave-uniform
-    const unsigned v = (w0 + lane < words) ? planes_ge<PLANES>(plane[r], T) : 0u;
-    if (a.voted) {
-      bf16_t* o = reinterpret_cast<bf16_t*>(a.voted) + w0 * 32;
+    for (int k = 0; k < 4; ++k) {
+      // chunk 64 k + lane of the wave's 256 chunks of 8 entries: byte (lane & 3) of word 16 k + lane / 4
+      const int t = 16 * k + (lane >> 2), e = 8 * (lane & 3);
+      const unsigned bits = (__shfl(v, t, 64) >> e) & 0xFFu;
+      const int lv = live_of(t) - e;
+      const long long flat = flat_of(t) + e;
+      u32x4 h;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        // chunk 64 k + lane of the run's 256 chunks of 8 entries: byte (lane & 3) of word 16 k + lane / 4
-        const unsigned word = __shfl(v, 16 * k + (lane >> 2), 64);
-        const unsigned bits = (word >> (8 * (lane & 3))) & 0xFFu;
-        if (w0 + 16 * k + (lane >> 2) < words) {
-          u32x4 h;
+      for (int q = 0; q < 4; ++q) h[q] = pm1_bf16(bits >> (2 * q));
+      if (padded) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            h[q] = (((bits >> (2 * q)) & 1u) ? 0x3F80u : 0xBF80u) | ((((bits >> (2 * q + 1)) & 1u) ? 0x3F80u : 0xBF80u) << 16);
-          *reinterpret_cast<u32x4*>(o + (64 * k + lane) * 8) = h;
-        }
+        for (int q = 0; q < 4; ++q) h[q] &= (2 * q < lv ? 0xFFFFu : 0u) | (2 * q + 1 < lv ? 0xFFFF0000u : 0u);
+        if (w0 + t < words) *reinterpret_cast<u32x4*>(o + 32 * (w0 + t) + e) = h;
+      } else if (lv >= 8) {
+        *reinterpret_cast<u32x4_u*>(o + flat) = h;
+      } else if (lv > 0) {
+        for (int q = 0; q < lv; ++q) o[flat + q] = (unsigned short)(pm1_bf16(bits >> q));
       }
     }
-    if (a.w) {
-      float* wp = a.w + w0 * 32;
-      // group 64 k + lane of the run's 512 groups of 4 entries: nibble (lane & 7) of word 8 k + lane / 8;
-      // the eight loads are issued before the first store
-      f32x4 wv[8];
+  } else if (a.voted) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        wv[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (w0 + 8 * k + (lane >> 3) < words)
-          wv[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(wp + (64 * k + lane) * 4));
-      }
+    for (int k = 0; k < 8; ++k) {
+      const int t = 8 * k + (lane >> 3), e = 4 * (lane & 7);
+      const unsigned bits = (__shfl(v, t, 64) >> e) & 0xFu;
+      const int lv = live_of(t) - e;
+      const long long flat = flat_of(t) + e;
+      if (lv > 0) voted4(a.voted, a.vfmt, flat, bits, min(lv, 4));
+    }
+  }
+  if (a.counts) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const unsigned word = __shfl(v, 8 * k + (lane >> 3), 64);
-        const unsigned bits = (word >> (4 * (lane & 7))) & 0xFu;
-        if (w0 + 8 * k + (lane >> 3) < words) {
-          f32x4 o = wv[k];
-          o.x = __fsub_rn(o.x, __fmul_rn(a.lr, (bits & 1u) ? 1.0f : -1.0f));
-          o.y = __fsub_rn(o.y, __fmul_rn(a.lr, (bits & 2u) ? 1.0f : -1.0f));
-          o.z = __fsub_rn(o.z, __fmul_rn(a.lr, (bits & 4u) ? 1.0f : -1.0f));
-          o.w = __fsub_rn(o.w, __fmul_rn(a.lr, (bits & 8u) ? 1.0f : -1.0f));
-          __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(wp + (64 * k + lane) * 4));
-        }
+    for (int k = 0; k < 8; ++k) {
+      const int t = 8 * k + (lane >> 3), e = 4 * (lane & 7);
+      i32x4 c = {0, 0, 0, 0};
+#pragma unroll
+      for (int b = 0; b < PLANES; ++b) {
+        const unsigned x = __shfl(plane[b], t, 64) >> e;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c[q] += (int)((x >> q) & 1u) << b;
       }
+      const int lv = live_of(t) - e;
+      const long long flat = flat_of(t) + e;
+      if (lv > 0) counts4(a.counts + flat, c, min(lv, 4));
+    }
+  }
+  if (a.w) {
+    f32x4 wv[8];
+    int lv[8];
+    long long at[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int t = 8 * k + (lane >> 3), e = 4 * (lane & 7);
+      lv[k] = min(live_of(t) - e, 4);
+      at[k] = flat_of(t) + e;
+      wv[k] = load4(a.w + at[k], lv[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const unsigned bits = (__shfl(v, 8 * k + (lane >> 3), 64) >> (4 * (lane & 7))) & 0xFu;
+      if (lv[k] > 0) step4(a.w + at[k], a.lr, wv[k], bits, lv[k]);
     }
   }
 }
 
-// Expanding vote over int8 signs, wide form: one thread = 16 consecutive entries (one 16-byte load per
-// worker), int32 sums, then any of: counts, voted int8 / bf16 (flat), fused W update.  For tables whose
-// entries have n % 16 == 0 and 16-byte aligned rows.
+// Expanding vote over int8 signs, one thread = 16 consecutive entries (one 16-byte load per worker), for voted
+// matrices alone (int8 or flat bf16) of n % 16 == 0 entries in 16-byte aligned rows: the form the step with a local
+// polar step uses.
 __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_args g) {
   const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
@@ -937,44 +901,99 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_arg
 #pragma unroll
       for (int k = 0; k < 4; ++k) c[4 * q + k] += (int)(signed char)(v[q] >> (8 * k));
   }
-  if (a.counts) {
+  unsigned bits = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<int4*>(a.counts + e0 + 4 * q) = make_int4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
-  }
-  if (a.w) {
+  for (int k = 0; k < 16; ++k) bits |= (c[k] >= 0 ? 1u : 0u) << k;
+  if (a.vfmt == SM_VOTE_INT8) {
+    u32x4 o;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float4 wv = *reinterpret_cast<float4*>(a.w + e0 + 4 * q);
-      wv.x = __fsub_rn(wv.x, __fmul_rn(a.lr, c[4 * q] >= 0 ? 1.0f : -1.0f));
-      wv.y = __fsub_rn(wv.y, __fmul_rn(a.lr, c[4 * q + 1] >= 0 ? 1.0f : -1.0f));
-      wv.z = __fsub_rn(wv.z, __fmul_rn(a.lr, c[4 * q + 2] >= 0 ? 1.0f : -1.0f));
-      wv.w = __fsub_rn(wv.w, __fmul_rn(a.lr, c[4 * q + 3] >= 0 ? 1.0f : -1.0f));
-      *reinterpret_cast<float4*>(a.w + e0 + 4 * q) = wv;
-    }
-  }
-  if (a.voted) {
-    if (a.vfmt == SM_VOTE_INT8) {
+    for (int q = 0; q < 4; ++q) o[q] = pm1_bytes(bits >> (4 * q));
+    *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(a.voted) + e0) = o;
+  } else {
+    bf16_t* ob = reinterpret_cast<bf16_t*>(a.voted) + e0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
       u32x4 o;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        unsigned v4 = 0;
+      for (int q = 0; q < 4; ++q) o[q] = pm1_bf16(bits >> (8 * h + 2 * q));
+      *reinterpret_cast<u32x4*>(ob + 8 * h) = o;
+    }
+  }
+}
+
+// Expanding vote over int8 signs, any form: groups of four consecutive entries, VI_UNROLL per thread a workgroup's width
+// apart, so that the 4-byte loads of the workers and the 16-byte accesses of weights and counts are all consecutive
+// across lanes; int32 sums.  ROWS as in sm_vote_wide_kernel.
+constexpr int VI_UNROLL = 4;
+
+template <bool ROWS>
+__global__ void __launch_bounds__(TPB) sm_vote_int8_kernel(const vote_g_args g) {
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
+  const vote_x_args& a = g.d[di];
+  const signed char* signs = reinterpret_cast<const signed char*>(a.signs);
+  const long long t0 = (long long)(blockIdx.x - g.begin.v[di]) * (TPB * VI_UNROLL) + threadIdx.x;
+  int c[VI_UNROLL][4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v4 |= (c[4 * q + k] >= 0 ? 0x01u : 0xFFu) << (8 * k);
-        o[q] = v4;
+  for (int u = 0; u < VI_UNROLL; ++u)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[u][k] = 0;
+  if (4 * (t0 - threadIdx.x + TPB * VI_UNROLL) <= a.n) {  // every group of the workgroup is whole
+#pragma unroll 4
+    for (int p = 0; p < a.M; ++p)
+#pragma unroll
+      for (int u = 0; u < VI_UNROLL; ++u) {
+        const unsigned x = __builtin_nontemporal_load(reinterpret_cast<const u32_u*>(signs + (long long)p * a.stride_bytes + 4 * (t0 + u * TPB)));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[u][k] += (int)(signed char)(x >> (8 * k));
       }
-      *reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(a.voted) + e0) = o;
-    } else {  // bf16, flat
-      bf16_t* ob = reinterpret_cast<bf16_t*>(a.voted) + e0;
+  } else {
+    for (int p = 0; p < a.M; ++p)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        u32x4 o;
+      for (int u = 0; u < VI_UNROLL; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          o[q] = (c[8 * h + 2 * q] >= 0 ? 0x3F80u : 0xBF80u) | ((c[8 * h + 2 * q + 1] >= 0 ? 0x3F80u : 0xBF80u) << 16);
-        *reinterpret_cast<u32x4*>(ob + 8 * h) = o;
+        for (int k = 0; k < 4; ++k) {
+          const long long e = 4 * (t0 + u * TPB) + k;
+          if (e < a.n) c[u][k] += signs[(long long)p * a.stride_bytes + e];
+        }
+  }
+  f32x4 wv[VI_UNROLL];
+  int live[VI_UNROLL];
+  long long at[VI_UNROLL];
+#pragma unroll
+  for (int u = 0; u < VI_UNROLL; ++u) {
+    const long long t = t0 + u * TPB;
+    live[u] = 0;
+    at[u] = 4 * t;
+    if (4 * t < a.n) {
+      if (ROWS) {
+        long long r;
+        int q;
+        sm_row_of(a.by_row, a.sld >> 2, t, r, q);
+        live[u] = max(0, min(4, a.cols - 4 * q));
+        at[u] = r * a.cols + 4 * q;
+      } else {
+        live[u] = (int)(a.n - 4 * t < 4 ? a.n - 4 * t : 4);
       }
     }
+    if (a.w) wv[u] = load4(a.w + at[u], live[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < VI_UNROLL; ++u) {
+    const long long t = t0 + u * TPB;
+    if (4 * t >= a.n) break;
+    unsigned bits = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bits |= (c[u][k] >= 0 ? 1u : 0u) << k;
+    if (a.voted && ROWS && a.ld == a.sld) {  // bf16 with padded rows: zeros beyond cols
+      const int lv = live[u];
+      const u32x2 h = {pm1_bf16(bits) & ((0 < lv ? 0xFFFFu : 0u) | (1 < lv ? 0xFFFF0000u : 0u)),
+                       pm1_bf16(bits >> 2) & ((2 < lv ? 0xFFFFu : 0u) | (3 < lv ? 0xFFFF0000u : 0u))};
+      *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(a.voted) + 4 * t) = h;
+    }
+    if (live[u] == 0) continue;
+    if (a.voted && !(ROWS && a.ld == a.sld)) voted4(a.voted, a.vfmt, at[u], bits, live[u]);
+    if (a.counts) counts4(a.counts + at[u], i32x4{c[u][0], c[u][1], c[u][2], c[u][3]}, live[u]);
+    if (a.w) step4(a.w + at[u], a.lr, wv[u], bits, live[u]);
   }
 }
 
@@ -986,48 +1005,52 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
     sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
-    // the wide kernel serves tables made only of whole 32-entry words, bf16 flat outputs, no counts
-    bool wide = (fmt == SM_SIGN_1BIT);
+    bool rows = false;
     int max_m = 0;
-    for (int i = 0; i < g && wide; ++i) {
-      const sm_vote_desc& d = descs[done + i];
-      wide = d.n % 32 == 0 && !d.counts && d.M < 256 && d.stride_bytes % 4 == 0 && sm_aligned(d.signs, 4) &&
-             (!d.voted || (d.vfmt == SM_VOTE_BF16 && d.ld == d.cols && sm_aligned(d.voted, 16))) &&
-             (!d.w || sm_aligned(d.w, 16));
-      max_m = std::max(max_m, d.M);
-    }
-    // the wide int8 kernel: whole 16-entry groups, 16-byte aligned rows and outputs, int8 or flat bf16 votes
+    // the 16-entry int8 kernel: whole groups, aligned rows and outputs, voted matrices alone
     bool wide8 = (fmt == SM_SIGN_INT8);
-    for (int i = 0; i < g && wide8; ++i) {
+    for (int i = 0; i < g; ++i) {
       const sm_vote_desc& d = descs[done + i];
-      wide8 = d.n % 16 == 0 && d.stride_bytes % 16 == 0 && sm_aligned(d.signs, 16) &&
-              (!d.voted || (d.vfmt == SM_VOTE_INT8 && sm_aligned(d.voted, 16)) ||
-               (d.vfmt == SM_VOTE_BF16 && d.ld == d.cols && sm_aligned(d.voted, 16))) &&
-              (!d.w || sm_aligned(d.w, 16)) && (!d.counts || sm_aligned(d.counts, 16));
+      rows = rows || d.sld != 0;
+      max_m = std::max(max_m, d.M);
+      wide8 = wide8 && !d.sld && !d.w && !d.counts && d.n % 16 == 0 && d.stride_bytes % 16 == 0 && sm_aligned(d.signs, 16) &&
+              d.voted && sm_aligned(d.voted, 16) && (d.vfmt == SM_VOTE_INT8 || d.vfmt == SM_VOTE_BF16);
     }
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
-      a.d[i] = descs[done + i];
+      sm_vote_desc& D = a.d[i];
+      D = descs[done + i];
+      if (rows) {
+        // a flat matrix among padded ones has rows of whole words: rows without padding
+        if (!D.sld) D.sld = D.ld = D.cols;
+        if (D.cols < 1 || D.sld % 64 || D.n % D.cols) return sm_fail(ctx, SM_EINVAL, "internal: vote rows");
+        D.n = D.n / D.cols * D.sld;  // entries of the source
+        D.by_row = sm_div_by((unsigned)(fmt == SM_SIGN_1BIT ? D.sld / 32 : D.sld / 4));
+      }
       a.begin.v[i] = (int)blocks;
-      const long long threads = wide ? (a.d[i].n / 32 + VW_GROUPS - 1) / VW_GROUPS : wide8 ? a.d[i].n / 16 : (a.d[i].n + 3) / 4;
-      blocks += (threads + TPB - 1) / TPB;
+      const long long per_wg = fmt == SM_SIGN_1BIT ? 32 * TPB : wide8 ? 16 * TPB : 4 * TPB * VI_UNROLL;
+      blocks += (D.n + per_wg - 1) / per_wg;
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "vote: too many entries for one launch");
     if (blocks > 0) {
       sm_launch_scope sc(ctx, SM_K_VOTE);
       const dim3 grid((unsigned)blocks), block(TPB);
-      if (wide && max_m < 8)
-        hipLaunchKernelGGL(sm_vote_wide_kernel<3>, grid, block, 0, ctx->stream, a);
-      else if (wide && max_m < 32)
-        hipLaunchKernelGGL(sm_vote_wide_kernel<5>, grid, block, 0, ctx->stream, a);
-      else if (wide)
-        hipLaunchKernelGGL(sm_vote_wide_kernel<8>, grid, block, 0, ctx->stream, a);
-      else if (wide8)
+#define VOTE_WIDE(PLANES)                                                                                     \
+  if (rows) hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, true>), grid, block, 0, ctx->stream, a);          \
+  else hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, false>), grid, block, 0, ctx->stream, a)
+      if (fmt == SM_SIGN_1BIT) {
+        if (max_m < 8) { VOTE_WIDE(3); }
+        else if (max_m < 32) { VOTE_WIDE(5); }
+        else if (max_m < 256) { VOTE_WIDE(8); }
+        else { VOTE_WIDE(31); }
+      } else if (wide8) {
         hipLaunchKernelGGL(sm_vote_int8_wide_kernel, grid, block, 0, ctx->stream, a);
-      else if (fmt == SM_SIGN_1BIT)
-        hipLaunchKernelGGL(sm_vote_expand_kernel<SM_SIGN_1BIT>, grid, block, 0, ctx->stream, a);
-      else
-        hipLaunchKernelGGL(sm_vote_expand_kernel<SM_SIGN_INT8>, grid, block, 0, ctx->stream, a);
+      } else if (rows) {
+        hipLaunchKernelGGL((sm_vote_int8_kernel<true>), grid, block, 0, ctx->stream, a);
+      } else {
+        hipLaunchKernelGGL((sm_vote_int8_kernel<false>), grid, block, 0, ctx->stream, a);
+      }
+#undef VOTE_WIDE
     }
     SM_HIP(ctx, hipGetLastError());
     done += g;
@@ -1047,7 +1070,9 @@ int sm_launch_update_group(signmuon_ctx* ctx, const sm_upd_desc* descs, int n) {
     for (int i = 0; i < g; ++i) {
       a.d[i] = descs[done + i];
       a.begin.v[i] = (int)blocks;
-      blocks += ((long long)a.d[i].rows * a.d[i].cols + UPD_CHUNK - 1) / UPD_CHUNK;
+      const int q = (a.d[i].cols + 3) / 4;
+      a.d[i].quads = sm_div_by((unsigned)q);
+      blocks += ((long long)a.d[i].rows * q + UPD_CHUNK - 1) / UPD_CHUNK;
     }
     if (blocks > 0) {
       sm_launch_scope sc(ctx, SM_K_UPDATE);
@@ -1059,14 +1084,3 @@ int sm_launch_update_group(signmuon_ctx* ctx, const sm_upd_desc* descs, int n) {
   return SM_OK;
 }
 
-int sm_launch_update(signmuon_ctx* ctx, float* w, const bf16_t* d, int rows, int cols, int ld, float step) {
-  sm_upd_desc D;
-  D.w = w;
-  D.d = d;
-  D.rows = rows;
-  D.cols = cols;
-  D.ld = ld;
-  D.kappa = nullptr;
-  D.step = step;
-  return sm_launch_update_group(ctx, &D, 1);
-}
