@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libsignmuon.so")
 # stand-alone measurement tool: the register-resident MFMA loop (practical ceiling of the matrix cores)
 TOOLS = {"mfma_peak": os.path.join("tools", "mfma_peak.hip")}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = ["ctx.hip", "stream.hip", "layout.hip", "poweriter.hip", "ns_gemm.hip", "api.hip"]
+SOURCES = ["ctx.hip", "stream.hip", "layout.hip", "poweriter.hip", "ns_gemm.hip", "ns_chain.hip", "api.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function"]

@@ -369,6 +369,58 @@ pair_coeffs pair_coefficients(float a, float b) {
   return c;
 }
 
+// Whether the products of a segment run as one launch of one workgroup per matrix (ns_chain.hip).  Measured for K = 5
+// against one launch per product: s = 64, 128: 17 and 21 us against 45 for one matrix (18, 24 against 70 and more for
+// 256); s = 256: 61 us against 48 for one matrix, 65 against 85 for 64, 81 against 180 for 256.
+bool chain_serves(const signmuon_ctx* ctx, const ns_plan* pl, int mult) {
+  if (ctx->opt[SM_OPT_GEMM_TILE] || ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL) return false;
+  int most = 0;
+  long long mats = 0;
+  for (auto& cl : pl->classes) {
+    most = std::max(most, cl.s);
+    mats += (long long)cl.count * mult;
+  }
+  return most <= 128 || (most <= SM_CHAIN_MAX_S && mats >= 40);
+}
+
+// The products of a segment of kk >= 2 steps: A_0 in off_q[0], packed; P_kk to off_p[0].
+int run_chain(signmuon_ctx* ctx, ns_plan* pl, int mult, int kk, float a, float b) {
+  const pair_coeffs pc = pair_coefficients(a, b);
+  const size_t ncls = pl->classes.size();
+  for (size_t c0 = 0; c0 < ncls; c0 += SM_CHAIN_MAX_CLASSES) {
+    chain_args ca;
+    sm_starts_clear(ca.begin);
+    ca.n_ops = 0;
+    auto add = [&](int pre, int x, int y, float alpha, float cA, float cP, float cL, float diag, int put, int keep) {
+      ca.op[ca.n_ops++] = chain_op{x, y, pre, put, keep, alpha, cA, cP, cL, diag};
+    };
+    int pre = 0;
+    for (int left = kk; left >= 2; left -= 2) {
+      const bool first = left == kk;
+      add(pre, 0, 0, 1.f, pc.h, 0.f, 0.f, 0.f, 1, 0);                              // E = A A + h A
+      add(0, 1, 1, pc.b4, pc.g, 0.f, pc.b4 * pc.u, pc.a2, 1, first ? 2 : 0);       // q = b4 (E E + u E) + g A + a2 I
+      if (left > 2) {
+        add(0, 1, 0, 1.f, 0.f, 0.f, 0.f, 0.f, 0, 0);                               // V = q A
+        add(0, 1, 0, 1.f, 0.f, 0.f, 0.f, 0.f, first ? 0 : -1, 1);                  // A' = q V
+      }
+      if (!first) add(2, 1, 0, 1.f, 0.f, 0.f, 0.f, 0.f, -1, 2);                    // P' = q P  (at first q is P_2 itself)
+      pre = first ? 0 : 1;
+    }
+    if (kk % 2) add(pre | 4, 0, 1, b, 0.f, a, 0.f, 0.f, -1, 0);                    // P' = b A P + a P
+    ca.n = (int)std::min(ncls - c0, (size_t)SM_CHAIN_MAX_CLASSES);
+    int blocks = 0;
+    for (int i = 0; i < ca.n; ++i) {
+      ns_class& cl = pl->classes[c0 + i];
+      ca.begin.v[i] = blocks;
+      blocks += cl.count * mult;
+      ca.c[i] = chain_class{at<unsigned char>(ctx, cl.off_q[0]), at<unsigned char>(ctx, cl.off_p[0]), cl.s, 0};
+    }
+    const int rc = sm_launch_chain(ctx, ca, blocks);
+    if (rc != SM_OK) return rc;
+  }
+  return SM_OK;
+}
+
 int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, bool use_scale,
                       int* cur_io, const ns_sign_req* signs, bool pairs) {
   int cur = *cur_io;
@@ -382,6 +434,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
   sm_tile_count tc;
   for (auto& cl : pl->classes) tc.add(cl.s, cl.s, cl.count * mult, true);
   const int ss = (ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL || sm_gemm_tile(ctx, tc) == 64) ? 0 : 3;
+  const bool chain = pairs && chain_serves(ctx, pl, mult);
   int done = 0;
   while (done < steps) {
     const int kk = std::min(SM_NS_SEGMENT, steps - done);
@@ -394,7 +447,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
     g.klass = SM_K_NS_GRAM;
     g.scale_pow = sc ? 2 : 0;
     g.out_f16 = (kk > 1);
-    g.sym_store = (kk > 1) ? (ss & 2) : 0;  // A_0 is only read by the products below
+    g.sym_store = (kk > 1) ? (chain ? 4 : ss & 2) : 0;  // A_0 is only read by the products below
     if (kk == 1) {  // only P_1 = Q_0 is needed, in bf16
       g.alpha = b;
       g.diag = a;
@@ -415,7 +468,11 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
     qq.alpha = b * b;
     qq.b_diag = a / b;
     int p_final = -1;  // -1: P_1 = Q_0 (bf16, in off_q[0]); else index into off_p
-    if (pairs && kk >= 3) {
+    if (chain && kk >= 2) {
+      rc = run_chain(ctx, pl, mult, kk, a, b);
+      if (rc != SM_OK) return rc;
+      p_final = 0;
+    } else if (pairs && kk >= 3) {
       // Two steps at a time.  With x an eigenvalue of A_k, Q_{k+1} Q_k is the quartic
       //   q(x) = (a + b x)(a + b x (a + b x)^2) = b^4 E (E + u) + g x + a^2,
       //   E = x (x + h),  h = 3a / 2b,  u = 3a^2 / 4b^2,  g = a b - a^3 b / 8,

@@ -108,10 +108,10 @@ static inline void sm_starts_clear(sm_starts<N>& s) {
 template <int N>
 __device__ __forceinline__ int sm_find(const sm_starts<N>& s, int n, int bx) {
   if (n == 1) return 0;
-  int at = -1;
+  int at = 0;
   for (int i = 0; i < n; i += 16) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) at += (bx >= s.v[i + k]) ? 1 : 0;
+    for (int k = 0; k < 16; ++k) at = (bx >= s.v[i + k]) ? i + k : at;
   }
   return at;
 }
@@ -309,7 +309,8 @@ struct sm_gemm_args {
   float a_diag, b_diag;  // 0 = none
   int in_f16, out_f16, r_f16;
   int sym_store;     // bit 0: the operands hold valid data only in their 256 x 256 blocks on and above the diagonal
-                     // (symmetric matrices; half precision, M == N == K); bit 1: write the output that way
+                     // (symmetric matrices; half precision, M == N == K); bit 1: write the output that way; bit 2:
+                     // write the output as packed 32 x 32 blocks on and above the diagonal (ns_chain.hip)
   int reverse;       // an XCD walks its range of the tile list from the end (set by the launcher: every other launch)
   sm_gemm_prob p[SM_GEMM_MAX_PROB];
 };
@@ -325,6 +326,31 @@ int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c);
 // layout 0 or 2.  Half-precision operands need sym and layout 0.  klass is the profiling class
 // the launch is booked under.
 int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass);
+
+// ---------------------------------------------------------------- chain of s x s products (ns_chain.hip)
+// From A_0 (half precision, packed 32 x 32 blocks) to P_K (bf16, whole row-major matrix), one workgroup per matrix.
+// Two matrices are in LDS (0: A_0 at first, and 1) and two in registers (A: A_0 at first, and P).  An op does, in order:
+// pre (bits: 1 LDS 0 <- A, 2 LDS 0 <- P, 4 LDS 1 <- P); c = alpha X Y + ca A + cp P + cl (LDS 1) + diag I with X, Y the
+// LDS matrices x, y; LDS put <- c (put >= 0); keep (bits: 1 A <- c, 2 P <- c).  The last op's c is the result.
+constexpr int SM_CHAIN_MAX_S = 256;
+struct chain_class {
+  const unsigned char* in;  // of the class's first matrix; s * s 16-bit elements per matrix
+  unsigned char* out;
+  int s, pad_;
+};
+struct chain_op {
+  int x, y, pre, put, keep;
+  float alpha, ca, cp, cl, diag;
+};
+constexpr int SM_CHAIN_MAX_CLASSES = 64, SM_CHAIN_MAX_OPS = 10;
+struct chain_args {
+  sm_starts<SM_CHAIN_MAX_CLASSES> begin;  // first workgroup of every class
+  int n, n_ops;
+  chain_op op[SM_CHAIN_MAX_OPS];
+  chain_class c[SM_CHAIN_MAX_CLASSES];
+};
+static_assert(sizeof(chain_args) <= 4096, "kernel arguments are limited to 4 KB");
+int sm_launch_chain(signmuon_ctx* ctx, chain_args& a, int blocks);
 
 // ---------------------------------------------------------------- power iteration (poweriter.hip)
 // sigma[item] = PowerIter(X[item], P, eps, v0[item]) for the `items` matrices of each table entry.

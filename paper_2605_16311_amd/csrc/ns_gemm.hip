@@ -540,7 +540,8 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     }
   }
   // upper-only output (sym_store bit 1): the mirrored tile is written only inside a diagonal 256 x 256 block
-  const bool mirror = SYM && (tm != tn) && (!(args.sym_store & 2) || (m0 / 256 == n0 / 256));
+  const bool packed = SYM && (args.sym_store & 4);
+  const bool mirror = SYM && (tm != tn) && !packed && (!(args.sym_store & 2) || (m0 / 256 == n0 / 256));
   // The tile leaves through LDS so that every global store is a 16-byte piece of a row.  The four
   // stage arrays (the first one at TS = 64) hold 64 tile rows each (rows of TS * 2 bytes, 16-byte chunk c of row r at slot
   // c ^ (r & (CPR - 1))).  The tile is staged once; it is read out row by row for C and, for an
@@ -641,7 +642,12 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
           v[q] &= (gr < mu && gc + 2 * q < nu ? 0xFFFFu : 0u) | (gr < mu && gc + 2 * q + 1 < nu ? 0xFFFF0000u : 0u);
       }
       if (gr < M && gc < N) {
-        const long long off = (long long)gr * P.ldc + gc;
+        long long off = (long long)gr * P.ldc + gc;
+        if (packed) {
+          const int rb = gr >> 5, cb = gc >> 5;
+          if (rb > cb) continue;
+          off = (long long)(cb * (cb + 1) / 2 + rb) * 1024 + (gr & 31) * 32 + (gc & 31);
+        }
         *reinterpret_cast<u32x4*>(C + off) = R ? add_r(v, rv[k]) : v;
       }
     }
@@ -966,6 +972,7 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: half-precision GEMM operands need a symmetric K-contiguous product");
     if ((args.sym_store & 1) && (!args.in_f16 || P.M != P.K || P.N != P.K))
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: upper-block operands need a square half-precision product");
+    if ((args.sym_store & 4) && (!sym || P.R)) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: packed output");
     if ((args.sym_store & 2) && !sym)
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: upper-block output needs a symmetric product");
     // buffer offsets are 32-bit
@@ -977,7 +984,7 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
   sm_tile_count tc;
   for (int i = 0; i < args.n_prob; ++i) tc.add(args.p[i].M, args.p[i].N, args.p[i].batch, gram);
   int ts = sm_gemm_tile(ctx, tc);
-  if (ts == 64 && args.sym_store) ts = 128;
+  if (ts == 64 && (args.sym_store & 3)) ts = 128;
   const int most = fill_tiles(args, gram, ts);
   if (args.total_tiles == 0) return SM_OK;
   args.reverse = ctx->gemm_flip;

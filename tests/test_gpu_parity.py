@@ -344,6 +344,35 @@ def test_polar_ns_against_fp32_oracle(P, vctx, batch, r, c, steps, scale, coeffs
         ns_check(got[b], ref, f"{(batch, r, c, steps, scale, dt)} item {b}")
 
 
+@pytest.mark.parametrize("batch,r,c", [(1, 1, 1), (3, 60, 70), (2, 200, 65), (2, 128, 300), (40, 129, 150), (41, 256, 192),
+                                       (40, 250, 256)])
+@pytest.mark.parametrize("steps", [2, 3, 4, 5, 7])
+def test_polar_ns_one_workgroup_per_matrix(P, ctx, batch, r, c, steps):
+    """Small matrices, whose products of a segment run in one launch: every length of a segment, short sides at and
+    around the sizes of its two kernels (128, 256) and of its 32-blocks."""
+    x = wl.normal((batch, r, c), stream=61, block=r, worker=steps)
+    xd = dev(x)
+    P.signmuon_polar_ns(ctx, xd, steps)
+    got = xd.cpu().numpy()
+    for b in (0, batch - 1):
+        ref = O.polar_ns(x[b], steps, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32)
+        ns_check(got[b], ref, f"{(batch, r, c, steps)} item {b}")
+
+
+@pytest.mark.parametrize("ns_path", ["pairs", "stepwise"])
+@pytest.mark.parametrize("r,c", [(64, 64), (100, 333), (333, 100), (448, 192), (192, 448)])
+def test_polar_ns_with_tiles_of_64(P, ns_path, r, c):
+    x = wl.normal((2, r, c), stream=62, block=r, worker=c)
+    xd = dev(x)
+    cc = P.Context(gemm_tile=64, ns_path=ns_path)
+    P.signmuon_polar_ns(cc, xd, 5)
+    got = xd.cpu().numpy()
+    cc.close()
+    for b in range(2):
+        ref = O.polar_ns(x[b], 5, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32)
+        ns_check(got[b], ref, f"{(r, c, ns_path)} item {b}")
+
+
 @pytest.mark.parametrize("opts", [dict(gemm_tile=128), dict(gemm_tile=256), dict(gemm_tile=256, ns_store="full"),
                                   dict(gemm_tile=128, ns_path="stepwise")])
 @pytest.mark.parametrize("r,c", [(1152, 1408), (1408, 1152)])
@@ -449,6 +478,17 @@ def test_step_mixed_set(P, vctx, sign_fmt, Kp):
     # (100, 72): rows that do not pack into whole words (separate sign-pack launch)
     shapes = [(64, 192), (192, 64), (64, 192), (128, 128), (100, 72), (64, 192), (200, 160), (96, 224)]
     run_step_case(P, ctx, shapes, 3, sign_fmt=sign_fmt, Kp=Kp, wd=0.1, rsqrt=(Kp > 0))
+
+
+@pytest.mark.parametrize("sign_fmt", ["1bit", "int8"])
+@pytest.mark.parametrize("Kp", [0, 3])
+@pytest.mark.parametrize("K", [0, 5])
+def test_step_with_rows_of_any_length(P, sign_fmt, Kp, K):
+    """Signs in padded rows, votes, updates and copies of rows that are no multiple of anything, next to whole rows."""
+    for opts in (dict(), dict(gemm_tile=64)):
+        c = P.Context(**opts)
+        run_step_case(P, c, [(129, 101), (64, 128), (67, 33), (1, 7), (5, 1)], 3, sign_fmt=sign_fmt, Kp=Kp, K=K, wd=0.1)
+        c.close()
 
 
 @pytest.mark.parametrize("special", [False, True])
