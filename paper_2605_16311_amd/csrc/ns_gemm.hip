@@ -15,7 +15,8 @@
 // the packed signs of its result (Alg. 3's encoding) besides or instead of the result itself.
 //
 // Structure.  A workgroup of 8 waves (2 per SIMD) owns a TS x TS tile of C (TS = 256, or 128
-// for launches with little work); each wave a (TS/2) x (TS/4) sub-tile held as accumulators of
+// for launches with little work; TS = 64 with four waves and three stages for launches of few
+// tiles, see SLICE_STEP3); each wave a (TS/2) x (TS/4) sub-tile held as accumulators of
 // v_mfma_f32_32x32x16_bf16 (or _f16).  K advances in slices of 64 (four MFMA k-steps), so that every
 // global->LDS request covers a whole 128-byte line of a K-contiguous operand: the per-CU
 // L2 -> LDS path is limited by the number of outstanding requests, not by bytes.
@@ -540,7 +541,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     }
   }
   // upper-only output (sym_store bit 1): the mirrored tile is written only inside a diagonal 256 x 256 block
-  const bool packed = SYM && (args.sym_store & 4);
+  const bool packed = SYM && !F16 && (args.sym_store & 4);
   const bool mirror = SYM && (tm != tn) && !packed && (!(args.sym_store & 2) || (m0 / 256 == n0 / 256));
   // The tile leaves through LDS so that every global store is a 16-byte piece of a row.  The four
   // stage arrays (the first one at TS = 64) hold 64 tile rows each (rows of TS * 2 bytes, 16-byte chunk c of row r at slot
@@ -627,28 +628,39 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
         if (gr < M && gc < N) rv[k] = *reinterpret_cast<const u32x4*>(R + (long long)gr * P.ldc + gc);
       }
     }
-    // a general product stores zeros beyond the logical matrix (see sm_gemm_prob::mu)
-    const int mu = SYM ? M : P.mu, nu = SYM ? N : P.nu;
-    const bool edge = !SYM && (m0 + TS > mu || n0 + TS > nu);
-#pragma unroll
-    for (int k = 0; k < PASSES; ++k) {
+    auto staged = [&](int k) {
       const int row = rr + RPP * k;  // tile row; (row >> 6) == (RPP * k) >> 6 is a constant
-      const unsigned char* sp = stage((RPP * k) >> 6);
-      u32x4 v = *reinterpret_cast<const u32x4*>(sp + (row & 63) * RB + ((rc ^ (row & (CPR - 1))) << 4));
-      const int gr = m0 + row;
-      if (edge) {
+      return *reinterpret_cast<const u32x4*>(stage((RPP * k) >> 6) + (row & 63) * RB + ((rc ^ (row & (CPR - 1))) << 4));
+    };
+    // One loop per form of the output, so that the usual one has no test per piece: a general product stores zeros
+    // beyond the logical matrix (see sm_gemm_prob::mu), a Gram matrix may leave as packed blocks.  (Tests inside a single
+    // loop: 256 registers and spills instead of 221 in the products, 2.88 instead of 2.85 ms per step of the 768-wide
+    // set.  mu and nu stay in locals: read through P inside the loop, the arguments were copied to scratch memory, 3.9 KB
+    // per lane, and that step took 7.35 instead of 6.85 ms.)
+    const int mu = SYM ? M : P.mu, nu = SYM ? N : P.nu;
+    if (!SYM && (m0 + TS > mu || n0 + TS > nu)) {
+#pragma unroll
+      for (int k = 0; k < PASSES; ++k) {
+        u32x4 v = staged(k);
+        const int gr = m0 + rr + RPP * k;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           v[q] &= (gr < mu && gc + 2 * q < nu ? 0xFFFFu : 0u) | (gr < mu && gc + 2 * q + 1 < nu ? 0xFFFF0000u : 0u);
+        if (gr < M && gc < N) *reinterpret_cast<u32x4*>(C + (long long)gr * P.ldc + gc) = R ? add_r(v, rv[k]) : v;
       }
-      if (gr < M && gc < N) {
-        long long off = (long long)gr * P.ldc + gc;
-        if (packed) {
-          const int rb = gr >> 5, cb = gc >> 5;
-          if (rb > cb) continue;
-          off = (long long)(cb * (cb + 1) / 2 + rb) * 1024 + (gr & 31) * 32 + (gc & 31);
-        }
-        *reinterpret_cast<u32x4*>(C + off) = R ? add_r(v, rv[k]) : v;
+    } else if (packed) {
+#pragma unroll
+      for (int k = 0; k < PASSES; ++k) {
+        const int gr = m0 + rr + RPP * k, rb = gr >> 5, cb = gc >> 5;
+        if (gr < M && gc < N && rb <= cb)
+          *reinterpret_cast<u32x4*>(C + (long long)(cb * (cb + 1) / 2 + rb) * 1024 + (gr & 31) * 32 + (gc & 31)) = staged(k);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < PASSES; ++k) {
+        const u32x4 v = staged(k);
+        const int gr = m0 + rr + RPP * k;
+        if (gr < M && gc < N) *reinterpret_cast<u32x4*>(C + (long long)gr * P.ldc + gc) = R ? add_r(v, rv[k]) : v;
       }
     }
   }
@@ -972,7 +984,7 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: half-precision GEMM operands need a symmetric K-contiguous product");
     if ((args.sym_store & 1) && (!args.in_f16 || P.M != P.K || P.N != P.K))
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: upper-block operands need a square half-precision product");
-    if ((args.sym_store & 4) && (!sym || P.R)) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: packed output");
+    if ((args.sym_store & 4) && (!sym || P.R || args.in_f16)) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: packed output");
     if ((args.sym_store & 2) && !sym)
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: upper-block output needs a symmetric product");
     // buffer offsets are 32-bit
