@@ -429,11 +429,11 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
   // The s x s matrices between the Gram and the apply are symmetric: only their 256 x 256 blocks on and
   // above the diagonal are written, and a product reads the other blocks as transposes of those
   // (a third fewer bytes to and from memory).  SM_NS_STORE_FULL writes and reads whole matrices.
-  // Launches small enough for tiles of 64 write whole matrices too: they are not bound by bytes, and the loop
-  // over one operand form is the shorter one.
+  // Launches small enough for three LDS stages write whole matrices too: they are not bound by bytes, and the
+  // loop over one operand form is the shorter one.
   sm_tile_count tc;
-  for (auto& cl : pl->classes) tc.add(cl.s, cl.s, cl.count * mult, true);
-  const int ss = (ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL || sm_gemm_tile(ctx, tc) == 64) ? 0 : 3;
+  for (auto& cl : pl->classes) tc.add(cl.s, cl.s, cl.s, cl.count * mult, true);
+  const int ss = (ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL || sm_gemm_stages(ctx, tc) == 3) ? 0 : 3;
   const bool chain = pairs && chain_serves(ctx, pl, mult);
   int done = 0;
   while (done < steps) {

@@ -315,12 +315,14 @@ struct sm_gemm_args {
   sm_gemm_prob p[SM_GEMM_MAX_PROB];
 };
 static_assert(sizeof(sm_gemm_args) <= 4096, "kernel arguments are limited to 4 KB");
-// Output tiles of a launch at tile sizes 64, 128 and 256, and the tile size it gets.
+// Output tiles of a launch at tile sizes 64, 128 and 256 and its longest K; the tile size and LDS stages it gets.
 struct sm_tile_count {
   double tiles[3] = {0, 0, 0};
-  void add(int M, int N, int batch, bool sym);
+  int longest = 0;
+  void add(int M, int N, int K, int batch, bool sym);
 };
 int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c);
+int sm_gemm_stages(const signmuon_ctx* ctx, const sm_tile_count& c);
 // One grouped launch over the problem table.  sym: every problem's output is symmetric (M == N;
 // layout 0 or 3): only the upper triangle of tiles is computed and stored mirrored.  Otherwise
 // layout 0 or 2.  Half-precision operands need sym and layout 0.  klass is the profiling class

@@ -63,7 +63,6 @@ template <int TS>
 struct tile_shape {
   static constexpr int NW = (TS == 64) ? 4 : 8, NTH = NW * 64;
   static constexpr int WM = TS / 2, WN = TS / (NW / 2), FM = WM / 32, FN = WN / 32, NLOAD = TS / 8 / NW;
-  static constexpr int STAGES = (TS == 64) ? 3 : 2;
 };
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
@@ -172,12 +171,12 @@ __device__ __forceinline__ unsigned ge0_bf16(unsigned h) {
 
 // One TS x TS tile of one problem.  The four stage arrays are the kernel's own __shared__
 // variables, passed by reference so that every access keeps its identity after inlining.
-template <int TS, bool A_MN, bool B_MN, bool SYM, bool F16, bool SYMSTORE = false>
+template <int TS, int ST, bool A_MN, bool B_MN, bool SYM, bool F16, bool SYMSTORE = false>
 __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gemm_prob& P, int b, int tm, int tn,
                                           unsigned char (&sA0)[TS * 128], unsigned char (&sA1)[TS * 128],
                                           unsigned char (&sB0)[TS * 128], unsigned char (&sB1)[TS * 128],
-                                          unsigned char (&sA2)[tile_shape<TS>::STAGES > 2 ? TS * 128 : 16],
-                                          unsigned char (&sB2)[tile_shape<TS>::STAGES > 2 ? TS * 128 : 16]) {
+                                          unsigned char (&sA2)[ST > 2 ? TS * 128 : 16],
+                                          unsigned char (&sB2)[ST > 2 ? TS * 128 : 16]) {
   using shape = tile_shape<TS>;
   constexpr int NTH = shape::NTH, WM = shape::WM, WN = shape::WN, FM = shape::FM, FN = shape::FN, NLOAD = shape::NLOAD;
   const int m0 = tm * TS, n0 = tn * TS;
@@ -310,8 +309,8 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   }
   const int nk = K / BK;
   int j = 0;
-  if constexpr (shape::STAGES == 3) {
-    // Three stages, slices requested two ahead: a launch that needs tiles of 64 has few of them, so a slice's
+  if constexpr (ST == 3) {
+    // Three stages, slices requested two ahead: a launch that gets them (sm_gemm_stages) has few tiles, so a slice's
     // latency is not hidden by other workgroups.  The wait before slice j leaves slice j + 1 in flight.
     static_assert(!SYMSTORE && NLOAD * 2 < 16, "");
 #define SLICE_STEP3(ca, cb, na, nb)                                       \
@@ -792,16 +791,16 @@ __host__ __device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n
 // KIND 1: general output, bf16 operands (A is KC; B is KC or MN).
 // KIND 2: symmetric output, half-precision operands, both KC.
 // KIND 3: as 2, with operands of which only the blocks on and above the diagonal are valid.
-template <int KIND, int TS>
+template <int KIND, int TS, int ST>
 __global__ void __launch_bounds__(tile_shape<TS>::NTH) sm_ns_gemm_kernel(const sm_gemm_args args) {
   constexpr bool SYM = (KIND != 1);
   __shared__ __attribute__((aligned(1024))) unsigned char sA0[TS * 128], sA1[TS * 128];
   __shared__ __attribute__((aligned(1024))) unsigned char sB0[TS * 128], sB1[TS * 128];
-  constexpr int THIRD = tile_shape<TS>::STAGES > 2 ? TS * 128 : 16;
+  constexpr int THIRD = ST > 2 ? TS * 128 : 16;
   __shared__ __attribute__((aligned(1024))) unsigned char sA2[THIRD], sB2[THIRD];
 
-  // Persistent workgroups: the grid is one (TS = 256) or two (TS = 128) workgroups per CU and each
-  // walks a list of tiles, so the global stores of one tile drain while the next tile is loaded
+  // Persistent workgroups: the grid is one (TS = 256, or 128 with three stages), two (128) or three
+  // (64) workgroups per CU and each walks a list of tiles, so the global stores of one tile drain while the next tile is loaded
   // and multiplied.  Workgroup ids are dealt round-robin to the 8 XCDs: XCD x owns a contiguous
   // range of the tile list (ranges of equal estimated cost) and its workgroups take neighbouring
   // tiles at any one time, so tiles that share operand panels share an L2.
@@ -832,18 +831,18 @@ __global__ void __launch_bounds__(tile_shape<TS>::NTH) sm_ns_gemm_kernel(const s
     tile_of<SYM, (TS == 256 ? 4 : 8)>(t, P.tiles_m, P.tiles_n, tm, tn);
     if constexpr (KIND == 0) {
       if (P.layout == 0)
-        gemm_tile<TS, false, false, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, false, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
       else
-        gemm_tile<TS, true, true, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, true, true, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     } else if constexpr (KIND == 1) {
       if (P.layout == 0)
-        gemm_tile<TS, false, false, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, false, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
       else
-        gemm_tile<TS, false, true, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, true, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     } else if constexpr (KIND == 2) {
-      gemm_tile<TS, false, false, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+      gemm_tile<TS, ST, false, false, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     } else {
-      gemm_tile<TS, false, false, true, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+      gemm_tile<TS, ST, false, false, true, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
     }
   }
 }
@@ -934,7 +933,8 @@ extern "C" int signmuon_debug_tile_of(int t, int tiles_m, int tiles_n, int sym, 
   return 0;
 }
 
-void sm_tile_count::add(int M, int N, int batch, bool sym) {
+void sm_tile_count::add(int M, int N, int K, int batch, bool sym) {
+  longest = std::max(longest, K);
   for (int i = 0; i < 3; ++i) {
     const int t = 64 << i;
     const double tm = (M + t - 1) / t, tn = (N + t - 1) / t;
@@ -951,6 +951,16 @@ int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
   if (c.tiles[2] >= 1024 && 4.0 * c.tiles[2] <= 1.15 * c.tiles[1]) return 256;
   // 64 x 64 tiles while tiles of 128 would leave half of the CUs without one
   return (c.tiles[1] <= 0.5 * ctx->n_cu) ? 64 : 128;
+}
+
+// Three LDS stages (whole s x s matrices, one workgroup per CU at 128) where the tiles of 128 fit one round, so that no
+// second workgroup of a CU hides a slice's latency, and the longest K is more than ten slices.  One polar factor with
+// K = 5, two stages against three: 2048 x 2048 293 -> 234 us, 4 of 1024 x 2048 206 -> 184, 7 of 768 x 3072 (147 tiles)
+// 223 -> 196, 12 of them (252 tiles) 264 -> 262; with eight slices (25 of 512 x 512, 250 tiles) 152-161 -> 168, so
+// the line.
+int sm_gemm_stages(const signmuon_ctx* ctx, const sm_tile_count& c) {
+  const int ts = sm_gemm_tile(ctx, c);
+  return (ts == 64 || (ts == 128 && c.tiles[1] <= ctx->n_cu && c.longest > 640)) ? 3 : 2;
 }
 
 // Per problem, P.layout bit 0: A is MN-contiguous, bit 1: B is MN-contiguous.  sym: symmetric
@@ -994,15 +1004,19 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM operand larger than 2 GiB");
   }
   sm_tile_count tc;
-  for (int i = 0; i < args.n_prob; ++i) tc.add(args.p[i].M, args.p[i].N, args.p[i].batch, gram);
+  for (int i = 0; i < args.n_prob; ++i) tc.add(args.p[i].M, args.p[i].N, args.p[i].K, args.p[i].batch, gram);
   int ts = sm_gemm_tile(ctx, tc);
-  if (ts == 64 && (args.sym_store & 3)) ts = 128;
+  int stages = sm_gemm_stages(ctx, tc);
+  if (args.sym_store & 3) {
+    if (ts == 64) ts = 128;
+    stages = 2;
+  }
   const int most = fill_tiles(args, gram, ts);
   if (args.total_tiles == 0) return SM_OK;
   args.reverse = ctx->gemm_flip;
   ctx->gemm_flip ^= 1;
   // persistent grid: as many workgroups per CU as fit (LDS), a multiple of 8, never more than tiles
-  int wgs = ctx->n_cu * (ts == 64 ? 3 : ts == 128 ? 2 : 1);
+  int wgs = ctx->n_cu * (ts == 64 ? 3 : ts == 128 && stages == 2 ? 2 : 1);
   wgs = std::max(1, std::min(wgs / 8, most)) * 8;
   const dim3 grid(wgs), block(ts == 64 ? tile_shape<64>::NTH : tile_shape<256>::NTH);
   if ((ctx->profiling >> klass) & 1u) {
@@ -1037,15 +1051,18 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
   {
     sm_launch_scope sc(ctx, klass);
     const int kind = args.in_f16 ? ((args.sym_store & 1) ? 3 : 2) : gram ? 0 : 1;
-#define GEMM_LAUNCH(KIND, TS) hipLaunchKernelGGL((sm_ns_gemm_kernel<KIND, TS>), grid, block, 0, ctx->stream, args)
-#define GEMM_TILES(KIND)                                                                                   \
-  if (ts == 256) GEMM_LAUNCH(KIND, 256); else if (ts == 128) GEMM_LAUNCH(KIND, 128); else GEMM_LAUNCH(KIND, 64)
+#define GEMM_LAUNCH(KIND, TS, ST) hipLaunchKernelGGL((sm_ns_gemm_kernel<KIND, TS, ST>), grid, block, 0, ctx->stream, args)
+#define GEMM_TILES(KIND)                                   \
+  if (ts == 256) GEMM_LAUNCH(KIND, 256, 2);                \
+  else if (ts == 64) GEMM_LAUNCH(KIND, 64, 3);             \
+  else if (stages == 3) GEMM_LAUNCH(KIND, 128, 3);         \
+  else GEMM_LAUNCH(KIND, 128, 2)
     switch (kind) {
       case 0: GEMM_TILES(0); break;
       case 1: GEMM_TILES(1); break;
       case 2: GEMM_TILES(2); break;
-      default:  // upper-block operands: not built for tiles of 64
-        if (ts == 256) GEMM_LAUNCH(3, 256); else GEMM_LAUNCH(3, 128);
+      default:  // upper-block operands: not built with three stages
+        if (ts == 256) GEMM_LAUNCH(3, 256, 2); else GEMM_LAUNCH(3, 128, 2);
     }
 #undef GEMM_TILES
 #undef GEMM_LAUNCH

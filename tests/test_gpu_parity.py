@@ -480,6 +480,24 @@ def test_step_mixed_set(P, vctx, sign_fmt, Kp):
     run_step_case(P, ctx, shapes, 3, sign_fmt=sign_fmt, Kp=Kp, wd=0.1, rsqrt=(Kp > 0))
 
 
+@pytest.mark.parametrize("batch,r,c", [(8, 641, 700), (8, 764, 710), (7, 830, 770), (1, 1990, 2010)])
+def test_polar_ns_in_one_round_of_tiles_of_128(P, ctx, batch, r, c):
+    """Launches of 129 to 256 tiles of 128 with a long K, which take three LDS stages: every remainder of the number of
+    slices by three, last tiles that are half empty, both orientations."""
+    x = wl.normal((batch, r, c), stream=63, block=r, worker=c)
+    xd = dev(x)
+    P.signmuon_polar_ns(ctx, xd, 5)
+    again = dev(x)
+    cc = P.Context(gemm_tile=256)   # two stages
+    P.signmuon_polar_ns(cc, again, 5)
+    cc.close()
+    got, other = xd.cpu().numpy(), again.cpu().numpy()
+    for b in (0, batch - 1):
+        ref = O.polar_ns(x[b], 5, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32)
+        ns_check(got[b], ref, f"{(batch, r, c)} item {b}")
+        ns_check(other[b], ref, f"{(batch, r, c)} item {b}, two stages")
+
+
 @pytest.mark.parametrize("sign_fmt", ["1bit", "int8"])
 @pytest.mark.parametrize("Kp", [0, 3])
 @pytest.mark.parametrize("K", [0, 5])
