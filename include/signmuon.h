@@ -240,7 +240,8 @@ int signmuon_profile_read(signmuon_ctx* ctx, int kernel_class, int64_t* launches
  * flop_dense = 2*M*N*K over the same products as written (what a kernel without the
  *   symmetry saving would execute);
  * bytes = their operands and results, each counted once (its stored share for a
- *   symmetric matrix kept in upper-block storage).
+ *   symmetric matrix of which only blocks on and above the diagonal are stored); of
+ *   products that run in one launch on chip, the first operand and the last result.
  * Zero for the other classes.  Any of the three pointers may be NULL. */
 int signmuon_profile_work(signmuon_ctx* ctx, int kernel_class, double* flop_executed, double* flop_dense,
                           double* bytes);

@@ -413,7 +413,7 @@ int run_chain(signmuon_ctx* ctx, ns_plan* pl, int mult, int kk, float a, float b
       ns_class& cl = pl->classes[c0 + i];
       ca.begin.v[i] = blocks;
       blocks += cl.count * mult;
-      ca.c[i] = chain_class{at<unsigned char>(ctx, cl.off_q[0]), at<unsigned char>(ctx, cl.off_p[0]), cl.s, 0};
+      ca.c[i] = chain_class{at<unsigned char>(ctx, cl.off_q[0]), at<unsigned char>(ctx, cl.off_p[0]), cl.s, std::min(cl.rows, cl.cols)};
     }
     const int rc = sm_launch_chain(ctx, ca, blocks);
     if (rc != SM_OK) return rc;

@@ -338,7 +338,7 @@ constexpr int SM_CHAIN_MAX_S = 256;
 struct chain_class {
   const unsigned char* in;  // of the class's first matrix; s * s 16-bit elements per matrix
   unsigned char* out;
-  int s, pad_;
+  int s, su;                // padded and logical side (the latter for the work accounting alone)
 };
 struct chain_op {
   int x, y, pre, put, keep;

@@ -340,6 +340,16 @@ int sm_launch_chain(signmuon_ctx* ctx, chain_args& a, int blocks) {
     most = std::max(most, a.c[i].s);
   }
   if (a.n < 1 || a.n_ops < 1 || blocks < 1) return sm_fail(ctx, SM_EINVAL, "internal: chain arguments");
+  if ((ctx->profiling >> SM_K_NS_SMALL) & 1u) {
+    for (int i = 0; i < a.n; ++i) {
+      const double s = a.c[i].s, mats = (i + 1 < a.n ? a.begin.v[i + 1] : blocks) - a.begin.v[i];
+      double area = 0.0;  // the 32 x 32 blocks on and above the diagonal, clipped to the logical matrix
+      for (int c = 0; c < a.c[i].su; c += 32) area += (double)std::min(32, a.c[i].su - c) * std::min(c + 32, a.c[i].su);
+      ctx->work_flop[SM_K_NS_SMALL] += 2.0 * area * a.c[i].su * mats * a.n_ops;
+      ctx->work_dense[SM_K_NS_SMALL] += 2.0 * s * s * s * mats * a.n_ops;
+      ctx->work_bytes[SM_K_NS_SMALL] += 2.0 * (s * (s + 32) / 2 + s * s) * mats;  // A_0 packed, P whole
+    }
+  }
   sm_launch_scope sc(ctx, SM_K_NS_SMALL);
   const dim3 grid(blocks), block(NTH);
   if (most <= 128) hipLaunchKernelGGL(sm_ns_chain_kernel<1>, grid, block, 0, ctx->stream, a);

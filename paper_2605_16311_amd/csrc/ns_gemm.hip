@@ -1039,7 +1039,8 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
         return kept / ((double)s * s);
       };
       const double in_share = (args.sym_store & 1) ? upper_share(P.K) : 1.0;
-      const double out_share = (args.sym_store & 2) ? upper_share(P.M) : 1.0;
+      const double packed_share = 0.5 + 16.0 / P.M;  // 32 x 32 blocks on and above the diagonal
+      const double out_share = (args.sym_store & 4) ? packed_share : (args.sym_store & 2) ? upper_share(P.M) : 1.0;
       const double r_share = (args.sym_store & 2) ? out_share : 1.0;  // R is read where the output is written
       ctx->work_bytes[klass] +=
           2.0 * P.batch * (in_share * ((double)P.M * P.K + (same ? 0.0 : (double)P.N * P.K)) +

@@ -359,6 +359,32 @@ def test_polar_ns_one_workgroup_per_matrix(P, ctx, batch, r, c, steps):
         ns_check(got[b], ref, f"{(batch, r, c, steps)} item {b}")
 
 
+@pytest.mark.parametrize("batch,r,c,s,l", [(3, 100, 150, 128, 192), (41, 250, 200, 256, 256)])
+@pytest.mark.parametrize("steps,products", [(2, 2), (3, 5), (4, 7), (5, 10), (8, 15)])
+def test_work_booked_for_products_in_one_launch(P, batch, r, c, s, l, steps, products):
+    """signmuon_profile_work beside the times of a set that runs on chip (s, l: the padded sides): per product the
+    32 x 32 blocks on and above the diagonal, clipped to the matrix; per segment A_0 read and P written once; a Gram
+    launch writes A_0 as packed blocks."""
+    from paper_2605_16311_amd import binding as B
+    segments, su = (steps + 4) // 5, min(r, c)
+    ctx = P.Context()
+    x = dev(wl.normal((batch, r, c), stream=64, block=r, worker=c))
+    P.signmuon_polar_ns(ctx, x, steps)
+    ctx.profile_enable(1 << B.SM_K_NS_SMALL | 1 << B.SM_K_NS_GRAM)
+    ctx.profile_reset()
+    P.signmuon_polar_ns(ctx, x, steps)
+    (small_n, small_ms), (gram_n, _) = ctx.profile_read(B.SM_K_NS_SMALL), ctx.profile_read(B.SM_K_NS_GRAM)
+    small, gram = ctx.profile_work(B.SM_K_NS_SMALL), ctx.profile_work(B.SM_K_NS_GRAM)
+    ctx.close()
+    side = [min(32, su - b) for b in range(0, su, 32)]
+    area = sum(side[i] * side[j] for j in range(len(side)) for i in range(j + 1))
+    packed = s * (s + 32) // 2
+    assert small_n == gram_n == segments and small_ms > 0
+    assert small == (batch * products * 2.0 * area * su, batch * products * 2.0 * s ** 3,
+                     batch * segments * 2.0 * (packed + s * s))
+    assert gram[2] == batch * segments * 2.0 * (s * l + packed)
+
+
 @pytest.mark.parametrize("ns_path", ["pairs", "stepwise"])
 @pytest.mark.parametrize("r,c", [(64, 64), (100, 333), (333, 100), (448, 192), (192, 448)])
 def test_polar_ns_with_tiles_of_64(P, ns_path, r, c):
