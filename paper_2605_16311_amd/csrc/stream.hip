@@ -921,79 +921,91 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_arg
   }
 }
 
-// Expanding vote over int8 signs, any form: groups of four consecutive entries, VI_UNROLL per thread a workgroup's width
-// apart, so that the 4-byte loads of the workers and the 16-byte accesses of weights and counts are all consecutive
-// across lanes; int32 sums.  ROWS as in sm_vote_wide_kernel.
-constexpr int VI_UNROLL = 4;
-
+// Expanding vote over int8 signs, any form.  A wave takes 1024 consecutive entries: a lane sums 16 of them (one 16-byte
+// load per worker, eight workers in flight), the int32 sums change owners through the wave's 4 KB of LDS, and a lane then
+// has four groups of four entries, 256 apart, so that the accesses of weights and counts are consecutive across lanes.
+// The weights are requested before the signs.  (Loads of four bytes per worker, without the exchange, bound the kernel by
+// requests as M grows.  4 M entries, update and counts, M = 4 / 16: 19.4 / 43.8 us then, 13.5 / 23.6 us now, where a lane
+// that also kept its 16 entries for the accesses of weights and counts took 18.5 / 26.6.)  ROWS as in sm_vote_wide_kernel.
 template <bool ROWS>
 __global__ void __launch_bounds__(TPB) sm_vote_int8_kernel(const vote_g_args g) {
+  __shared__ __attribute__((aligned(16))) unsigned char sums[TPB * 64];
   const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
-  const signed char* signs = reinterpret_cast<const signed char*>(a.signs);
-  const long long t0 = (long long)(blockIdx.x - g.begin.v[di]) * (TPB * VI_UNROLL) + threadIdx.x;
-  int c[VI_UNROLL][4];
+  const int lane = threadIdx.x & 63;
+  const long long run = ((long long)(blockIdx.x - g.begin.v[di]) * TPB + (threadIdx.x & ~63)) * 16;
+  if (run >= a.n) return;  // the wave as a whole
+  f32x4 wv[4];
+  int live[4];
+  long long at[4];
 #pragma unroll
-  for (int u = 0; u < VI_UNROLL; ++u)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) c[u][k] = 0;
-  if (4 * (t0 - threadIdx.x + TPB * VI_UNROLL) <= a.n) {  // every group of the workgroup is whole
-#pragma unroll 4
-    for (int p = 0; p < a.M; ++p)
-#pragma unroll
-      for (int u = 0; u < VI_UNROLL; ++u) {
-        const unsigned x = __builtin_nontemporal_load(reinterpret_cast<const u32_u*>(signs + (long long)p * a.stride_bytes + 4 * (t0 + u * TPB)));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c[u][k] += (int)(signed char)(x >> (8 * k));
-      }
-  } else {
-    for (int p = 0; p < a.M; ++p)
-#pragma unroll
-      for (int u = 0; u < VI_UNROLL; ++u)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const long long e = 4 * (t0 + u * TPB) + k;
-          if (e < a.n) c[u][k] += signs[(long long)p * a.stride_bytes + e];
-        }
-  }
-  f32x4 wv[VI_UNROLL];
-  int live[VI_UNROLL];
-  long long at[VI_UNROLL];
-#pragma unroll
-  for (int u = 0; u < VI_UNROLL; ++u) {
-    const long long t = t0 + u * TPB;
-    live[u] = 0;
-    at[u] = 4 * t;
+  for (int k = 0; k < 4; ++k) {
+    const long long t = run / 4 + 64 * k + lane;  // group of four entries
+    live[k] = 0;
+    at[k] = 4 * t;
     if (4 * t < a.n) {
       if (ROWS) {
         long long r;
         int q;
         sm_row_of(a.by_row, a.sld >> 2, t, r, q);
-        live[u] = max(0, min(4, a.cols - 4 * q));
-        at[u] = r * a.cols + 4 * q;
+        live[k] = max(0, min(4, a.cols - 4 * q));
+        at[k] = r * a.cols + 4 * q;
       } else {
-        live[u] = (int)(a.n - 4 * t < 4 ? a.n - 4 * t : 4);
+        live[k] = (int)(a.n - 4 * t < 4 ? a.n - 4 * t : 4);
       }
     }
-    if (a.w) wv[u] = load4(a.w + at[u], live[u]);
+    if (a.w) wv[k] = load4(a.w + at[k], live[k]);
   }
+  int c[16];
 #pragma unroll
-  for (int u = 0; u < VI_UNROLL; ++u) {
-    const long long t = t0 + u * TPB;
-    if (4 * t >= a.n) break;
+  for (int k = 0; k < 16; ++k) c[k] = 0;
+  const long long e0 = run + 16 * lane;
+  const signed char* src = reinterpret_cast<const signed char*>(a.signs) + e0;
+  if (e0 + 16 <= a.n) {
+    for (int pb = 0; pb < a.M; pb += VOTE_GROUP) {
+      u32x4 v[VOTE_GROUP];
+#pragma unroll
+      for (int q = 0; q < VOTE_GROUP; ++q) {
+        v[q] = u32x4{0u, 0u, 0u, 0u};
+        if (pb + q < a.M)
+          v[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(src + (long long)(pb + q) * a.stride_bytes));
+      }
+#pragma unroll
+      for (int q = 0; q < VOTE_GROUP; ++q)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) c[k] += (int)(signed char)(v[q][k >> 2] >> (8 * (k & 3)));
+    }
+  } else {
+    for (int p = 0; p < a.M; ++p)
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (e0 + k < a.n) c[k] += src[(long long)p * a.stride_bytes + k];
+  }
+  // lane l's sums of entries 16 l + 4 j .. + 3 at byte 64 l + 16 (j ^ (l / 4 mod 4)): no bank conflicts either way
+  unsigned char* share = sums + (threadIdx.x & ~63) * 64;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    *reinterpret_cast<i32x4*>(share + 64 * lane + 16 * (j ^ ((lane >> 2) & 3))) = i32x4{c[4 * j], c[4 * j + 1], c[4 * j + 2], c[4 * j + 3]};
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const long long t = run / 4 + 64 * k + lane;
+    const i32x4 s = *reinterpret_cast<const i32x4*>(share + 1024 * k + 64 * (lane >> 2) + 16 * ((lane & 3) ^ ((lane >> 4) & 3)));
     unsigned bits = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bits |= (c[u][k] >= 0 ? 1u : 0u) << k;
+    for (int q = 0; q < 4; ++q) bits |= (s[q] >= 0 ? 1u : 0u) << q;
+    if (4 * t >= a.n) break;
     if (a.voted && ROWS && a.ld == a.sld) {  // bf16 with padded rows: zeros beyond cols
-      const int lv = live[u];
+      const int lv = live[k];
       const u32x2 h = {pm1_bf16(bits) & ((0 < lv ? 0xFFFFu : 0u) | (1 < lv ? 0xFFFF0000u : 0u)),
                        pm1_bf16(bits >> 2) & ((2 < lv ? 0xFFFFu : 0u) | (3 < lv ? 0xFFFF0000u : 0u))};
       *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(a.voted) + 4 * t) = h;
     }
-    if (live[u] == 0) continue;
-    if (a.voted && !(ROWS && a.ld == a.sld)) voted4(a.voted, a.vfmt, at[u], bits, live[u]);
-    if (a.counts) counts4(a.counts + at[u], i32x4{c[u][0], c[u][1], c[u][2], c[u][3]}, live[u]);
-    if (a.w) step4(a.w + at[u], a.lr, wv[u], bits, live[u]);
+    if (live[k] == 0) continue;
+    if (a.voted && !(ROWS && a.ld == a.sld)) voted4(a.voted, a.vfmt, at[k], bits, live[k]);
+    if (a.counts) counts4(a.counts + at[k], s, live[k]);
+    if (a.w) step4(a.w + at[k], a.lr, wv[k], bits, live[k]);
   }
 }
 
@@ -1028,7 +1040,7 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
         D.by_row = sm_div_by((unsigned)(fmt == SM_SIGN_1BIT ? D.sld / 32 : D.sld / 4));
       }
       a.begin.v[i] = (int)blocks;
-      const long long per_wg = fmt == SM_SIGN_1BIT ? 32 * TPB : wide8 ? 16 * TPB : 4 * TPB * VI_UNROLL;
+      const long long per_wg = fmt == SM_SIGN_1BIT ? 32 * TPB : 16 * TPB;
       blocks += (D.n + per_wg - 1) / per_wg;
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "vote: too many entries for one launch");

@@ -240,6 +240,33 @@ def test_vote_int8_sixteen_entry_groups(P, ctx, M, n):
     assert np.array_equal(gv[:n], vote_ref.astype(np.float32)) and np.all(gv[n:] == 5.0)
 
 
+@pytest.mark.parametrize("M", [1, 7, 8, 9, 20])
+@pytest.mark.parametrize("n", [15, 17, 1023, 1024, 1041, 4095, 4097, 8200])
+def test_vote_int8_runs_of_a_wave(P, ctx, M, n):
+    """int8 values of the whole range in rows that start anywhere, around the 16 entries of a lane, the 1024 of a wave
+    and the 4096 of a workgroup, and around groups of eight workers: sums, votes and update in one call and alone."""
+    rng = wl.rng_for(65, block=M, worker=n)
+    S = rng.integers(-128, 128, size=(M, n + 3), dtype=np.int8)
+    tot = S[:, :n].astype(np.int32).sum(axis=0)
+    vote = np.where(tot >= 0, 1, -1)
+    w0, lr = wl.normal((n,), stream=66, block=n), 0.03125
+    w_ref = O.apply_update(w0.reshape(1, n), vote.reshape(1, n), lr, dtype=np.float32).reshape(n)
+    base = dev(np.concatenate([np.zeros(1, np.int8), S.reshape(-1)]))
+    signs = base[1:]                                          # one byte past an aligned address
+    for voted in (None, "int8", "bf16", "f32"):
+        cnt = torch.full((n + 4,), -7, dtype=torch.int32, device="cuda")
+        w = dev(np.concatenate([w0, np.full(4, 3.0, np.float32)]))
+        v = None if voted is None else torch.full((n + 4,), 9, device="cuda", dtype=dict(
+            int8=torch.int8, bf16=torch.bfloat16, f32=torch.float32)[voted])
+        P.signmuon_majority_vote(ctx, signs, "int8", M, n, n + 3, voted=v, vfmt=voted or "bits", counts=cnt, w=w, lr_scaled=lr)
+        assert np.array_equal(cnt.cpu().numpy()[:n], tot) and np.all(cnt.cpu().numpy()[n:] == -7)
+        gw = w.cpu().numpy()
+        assert np.array_equal(gw[:n].view(np.uint32), w_ref.view(np.uint32)) and np.all(gw[n:] == 3.0)
+        if v is not None:
+            gv = v.float().cpu().numpy()
+            assert np.array_equal(gv[:n], vote.astype(np.float32)) and np.all(gv[n:] == 9.0)
+
+
 @pytest.mark.parametrize("snr", [0.25, 1.0])
 def test_majority_vote_sign_error_falls_like_inverse_sqrt_m(P, ctx, snr):
     """Lemma "Majority vote improves sign reliability": with M independent workers whose gradient entries are
