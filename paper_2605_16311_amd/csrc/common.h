@@ -219,7 +219,7 @@ struct sm_vote_desc {
   int M, vfmt;
   int cols, sld;
   int ld;            // row length of voted: sld (then the columns beyond cols are written as zeros; bf16 only) or cols
-  sm_div by_row;     // by the words (1 bit) or groups of four (int8) of a row of sld; filled by the launcher
+  sm_div by_row;     // by the words (sm_vote_wide_kernel) or groups of four (the others) of a row of sld; filled by the launcher
 };
 constexpr int SM_VOTE_MAX_GROUP = 48;
 int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, int fmt);

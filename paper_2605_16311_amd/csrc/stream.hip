@@ -4,6 +4,8 @@
 // once with 16-byte (or 4-byte broadcast) coalesced accesses and written once.
 #include "common.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int TPB = 256;
@@ -364,6 +366,25 @@ __device__ __forceinline__ W planes_ge(const W (&plane)[PLANES], unsigned T) {
 // added, so a thread keeps 8 x 16 bytes in flight (rows beyond M read as zero words, which
 // count nothing).
 constexpr int VOTE_GROUP = 8;
+constexpr int VOTE8_GROUP = 4;  // with 16 bytes per load and 16 sums: eight cost the registers of every other wave
+
+// f(number of workers, first worker) over workers [first, end) in groups of G, the number a constant in each group: the
+// last group is not padded, so a thread does no arithmetic for workers that are not there.
+template <int G, typename F>
+__device__ __forceinline__ void for_workers(int first, int end, F f) {
+  int p = first;
+  for (; p + G <= end; p += G) f(std::integral_constant<int, G>(), p);
+  switch (end - p) {
+    case 1: f(std::integral_constant<int, 1>(), p); break;
+    case 2: f(std::integral_constant<int, 2>(), p); break;
+    case 3: f(std::integral_constant<int, 3>(), p); break;
+    case 4: f(std::integral_constant<int, 4>(), p); break;
+    case 5: f(std::integral_constant<int, 5>(), p); break;
+    case 6: f(std::integral_constant<int, 6>(), p); break;
+    case 7: f(std::integral_constant<int, 7>(), p); break;
+    default: break;
+  }
+}
 
 // A thread owns VB_PAIRS pairs of 64-bit words, TPB pairs apart (rows are 8-byte aligned with any stride: a
 // pair is read with one 16-byte load only where row base and stride allow it).  Measured on 85 M entries, M = 8:
@@ -443,6 +464,7 @@ struct vote_g_args {
   sm_starts<SM_VOTE_MAX_GROUP> begin;
   sm_vote_desc d[SM_VOTE_MAX_GROUP];
 };
+static_assert(sizeof(vote_g_args) <= 4096, "kernel arguments are limited to 4 KB");
 
 // Stores of up to four consecutive results; `live` of them exist.
 __device__ __forceinline__ void step4(float* w, float lr, const f32x4 old, unsigned bits, int live) {
@@ -500,7 +522,16 @@ __device__ __forceinline__ void voted4(void* voted, int vfmt, long long at, unsi
     }
   } else {
     float* o = reinterpret_cast<float*>(voted) + at;
-    for (int k = 0; k < live; ++k) o[k] = ((bits >> k) & 1u) ? 1.0f : -1.0f;
+    f32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = ((bits >> k) & 1u) ? 1.0f : -1.0f;
+    if (live == 4) {
+      *reinterpret_cast<f32x4_u*>(o) = v;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k < live) o[k] = v[k];
+    }
   }
 }
 
@@ -881,9 +912,10 @@ __global__ void __launch_bounds__(TPB) sm_vote_wide_kernel(const vote_g_args g) 
   }
 }
 
-// Expanding vote over int8 signs, one thread = 16 consecutive entries (one 16-byte load per worker), for voted
-// matrices alone (int8 or flat bf16) of n % 16 == 0 entries in 16-byte aligned rows: the form the step with a local
-// polar step uses.
+// Expanding vote over int8 signs, one thread = 16 consecutive entries (one 16-byte load per worker, one worker at a
+// time), for matrices of n % 16 == 0 entries in 16-byte aligned rows, votes int8 or flat bf16: where the signs are nearly
+// all of the bytes, one stream after the other is the better order on rows a power of two apart (counts alone, 32
+// workers of 8.4 M entries: 52 us, 60 in sm_vote_int8_kernel; of 10 M entries 70 and 66).
 __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_args g) {
   const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
@@ -904,6 +936,22 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_arg
   unsigned bits = 0;
 #pragma unroll
   for (int k = 0; k < 16; ++k) bits |= (c[k] >= 0 ? 1u : 0u) << k;
+  if (a.counts) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<i32x4*>(a.counts + e0 + 4 * q) = i32x4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+  }
+  if (a.w) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4* w = reinterpret_cast<f32x4*>(a.w + e0 + 4 * q);
+      f32x4 o = *w;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = __fsub_rn(o[k], __fmul_rn(a.lr, c[4 * q + k] >= 0 ? 1.0f : -1.0f));
+      *w = o;
+    }
+  }
+  if (!a.voted) return;
   if (a.vfmt == SM_VOTE_INT8) {
     u32x4 o;
 #pragma unroll
@@ -921,12 +969,111 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_wide_kernel(const vote_g_arg
   }
 }
 
-// Expanding vote over int8 signs, any form.  A wave takes 1024 consecutive entries: a lane sums 16 of them (one 16-byte
-// load per worker, eight workers in flight), the int32 sums change owners through the wave's 4 KB of LDS, and a lane then
-// has four groups of four entries, 256 apart, so that the accesses of weights and counts are consecutive across lanes.
-// The weights are requested before the signs.  (Loads of four bytes per worker, without the exchange, bound the kernel by
-// requests as M grows.  4 M entries, update and counts, M = 4 / 16: 19.4 / 43.8 us then, 13.5 / 23.6 us now, where a lane
-// that also kept its 16 entries for the accesses of weights and counts took 18.5 / 26.6.)  ROWS as in sm_vote_wide_kernel.
+// Group t of four entries of the source: how many of them count, and where the first lies in a flat output.
+template <bool ROWS>
+__device__ __forceinline__ void vote_place(const vote_x_args& a, long long t, int& live, long long& at) {
+  live = 0;
+  at = 4 * t;
+  if (4 * t >= a.n) return;
+  if (ROWS) {
+    long long r;
+    int q;
+    sm_row_of(a.by_row, a.sld >> 2, t, r, q);
+    live = max(0, min(4, a.cols - 4 * q));
+    at = r * a.cols + 4 * q;
+  } else {
+    live = (int)(a.n - 4 * t < 4 ? a.n - 4 * t : 4);
+  }
+}
+
+// All outputs of group t, which lies inside the source; wv: its weights, where there are any.
+template <bool ROWS>
+__device__ __forceinline__ void vote_out(const vote_x_args& a, long long t, int live, long long at, unsigned bits,
+                                         const i32x4& counts, const f32x4& wv) {
+  if (a.voted && ROWS && a.ld == a.sld) {  // bf16 with padded rows: zeros beyond cols
+    const u32x2 h = {pm1_bf16(bits) & ((0 < live ? 0xFFFFu : 0u) | (1 < live ? 0xFFFF0000u : 0u)),
+                     pm1_bf16(bits >> 2) & ((2 < live ? 0xFFFFu : 0u) | (3 < live ? 0xFFFF0000u : 0u))};
+    *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(a.voted) + 4 * t) = h;
+  }
+  if (live == 0) return;
+  if (a.voted && !(ROWS && a.ld == a.sld)) voted4(a.voted, a.vfmt, at, bits, live);
+  if (a.counts) counts4(a.counts + at, counts, live);
+  if (a.w) step4(a.w + at, a.lr, wv, bits, live);
+}
+
+// Expanding vote, a lane takes four entries: no exchange between lanes, so the chain from the signs to the results is
+// short, and accesses of every output are consecutive across lanes.  1 bit: the entries' bits out of every worker's word
+// (eight lanes read the same one), counted in the four bytes of a register, 248 workers at most before the bytes are
+// taken out.  us, this form / the other form of the transport (sm_vote_wide_kernel, sm_vote_int8_kernel):
+//   1 bit, bf16 votes + counts + update   0.26 M entries, M = 16   4.9 / 7.5      4 M, M = 1   11.6 / 13.0
+//                                         33 M, M = 8   73 / 76                   33 M, M = 32   134 / 94
+//   1 bit, counts                         33 M, M = 8   25 / 32                   1 bit, bf16 votes   8 M, M = 8   7.9 / 6.2
+//   int8, counts                          33 M, M = 8   60 / 75                   4 M, M = 16   18.9 / 17.3
+//   int8, f32 votes                       2 M, M = 8   4.5 / 5.5                  4 M, M = 32   31.5 / 30.2
+// ROWS as in sm_vote_wide_kernel.
+template <int FMT, bool ROWS>
+__global__ void __launch_bounds__(TPB) sm_vote_narrow_kernel(const vote_g_args g) {
+  const int di = sm_find(g.begin, g.n, blockIdx.x);
+  const vote_x_args& a = g.d[di];
+  const long long t = (long long)(blockIdx.x - g.begin.v[di]) * TPB + threadIdx.x;
+  if (4 * t >= a.n) return;
+  int live;
+  long long at;
+  vote_place<ROWS>(a, t, live, at);
+  f32x4 wv = {0.f, 0.f, 0.f, 0.f};
+  if (a.w) wv = load4(a.w + at, live);
+  i32x4 c = {0, 0, 0, 0};
+  unsigned bits = 0;
+  if (FMT == SM_SIGN_1BIT) {
+    const unsigned* base = reinterpret_cast<const unsigned*>(a.signs) + (t >> 3);
+    const int sh = 4 * (int)(t & 7);
+    const long long stride_w = a.stride_bytes >> 2;
+    for (int p0 = 0; p0 < a.M; p0 += 31 * VOTE_GROUP) {
+      unsigned acc = 0;
+      for_workers<VOTE_GROUP>(p0, min(a.M, p0 + 31 * VOTE_GROUP), [&](auto count, int p) {
+        constexpr int N = decltype(count)::value;
+        unsigned x[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) x[q] = base[(long long)(p + q) * stride_w];
+#pragma unroll
+        for (int q = 0; q < N; ++q) acc += (((x[q] >> sh) & 0xFu) * 0x00204081u) & 0x01010101u;
+      });
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] += (int)((acc >> (8 * k)) & 0xFFu);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bits |= (2 * c[k] >= a.M ? 1u : 0u) << k;
+  } else {
+    const signed char* src = reinterpret_cast<const signed char*>(a.signs) + 4 * t;
+    if (4 * t + 4 <= a.n) {
+      for_workers<VOTE_GROUP>(0, a.M, [&](auto count, int p) {
+        constexpr int N = decltype(count)::value;
+        unsigned x[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+          x[q] = __builtin_nontemporal_load(reinterpret_cast<const u32_u*>(src + (long long)(p + q) * a.stride_bytes));
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) c[k] += (int)(signed char)(x[q] >> (8 * k));
+      });
+    } else {
+      for (int p = 0; p < a.M; ++p)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          if (4 * t + k < a.n) c[k] += src[(long long)p * a.stride_bytes + k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bits |= (c[k] >= 0 ? 1u : 0u) << k;
+  }
+  vote_out<ROWS>(a, t, live, at, bits, c, wv);
+}
+
+// Expanding vote over int8 signs for many workers and entries (at least 16 of them).  A wave takes 1024 consecutive
+// entries: a lane sums 16 of them (one 16-byte load per worker, four workers in flight), the int32 sums change owners
+// through the wave's 4 KB of LDS, and a lane then has four groups of four entries, 256 apart, so that the accesses of
+// weights and counts are consecutive across lanes.  The weights are requested before the signs.  The lane at the end of
+// the buffer reads its last 16 bytes and shifts out what lies before its own entries.  ROWS as in sm_vote_wide_kernel.
 template <bool ROWS>
 __global__ void __launch_bounds__(TPB) sm_vote_int8_kernel(const vote_g_args g) {
   __shared__ __attribute__((aligned(16))) unsigned char sums[TPB * 64];
@@ -940,46 +1087,32 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_kernel(const vote_g_args g) 
   long long at[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const long long t = run / 4 + 64 * k + lane;  // group of four entries
-    live[k] = 0;
-    at[k] = 4 * t;
-    if (4 * t < a.n) {
-      if (ROWS) {
-        long long r;
-        int q;
-        sm_row_of(a.by_row, a.sld >> 2, t, r, q);
-        live[k] = max(0, min(4, a.cols - 4 * q));
-        at[k] = r * a.cols + 4 * q;
-      } else {
-        live[k] = (int)(a.n - 4 * t < 4 ? a.n - 4 * t : 4);
-      }
-    }
+    vote_place<ROWS>(a, run / 4 + 64 * k + lane, live[k], at[k]);
     if (a.w) wv[k] = load4(a.w + at[k], live[k]);
   }
   int c[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) c[k] = 0;
   const long long e0 = run + 16 * lane;
-  const signed char* src = reinterpret_cast<const signed char*>(a.signs) + e0;
-  if (e0 + 16 <= a.n) {
-    for (int pb = 0; pb < a.M; pb += VOTE_GROUP) {
-      u32x4 v[VOTE_GROUP];
+  const int past = e0 + 16 <= a.n ? 0 : e0 >= a.n ? 16 : (int)(e0 + 16 - a.n);  // entries of the lane beyond the buffer
+  if (past < 16) {
+    const signed char* src = reinterpret_cast<const signed char*>(a.signs) + e0 - past;
+    for_workers<VOTE8_GROUP>(0, a.M, [&](auto count, int p) {
+      constexpr int N = decltype(count)::value;
+      u32x4 v[N];
 #pragma unroll
-      for (int q = 0; q < VOTE_GROUP; ++q) {
-        v[q] = u32x4{0u, 0u, 0u, 0u};
-        if (pb + q < a.M)
-          v[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(src + (long long)(pb + q) * a.stride_bytes));
+      for (int q = 0; q < N; ++q)
+        v[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_u*>(src + (long long)(p + q) * a.stride_bytes));
+      if (past) {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+          v[q] = __builtin_bit_cast(u32x4, __builtin_bit_cast(unsigned __int128, v[q]) >> (8 * past));
       }
 #pragma unroll
-      for (int q = 0; q < VOTE_GROUP; ++q)
+      for (int q = 0; q < N; ++q)
 #pragma unroll
         for (int k = 0; k < 16; ++k) c[k] += (int)(signed char)(v[q][k >> 2] >> (8 * (k & 3)));
-    }
-  } else {
-    for (int p = 0; p < a.M; ++p)
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-        if (e0 + k < a.n) c[k] += src[(long long)p * a.stride_bytes + k];
+    });
   }
   // lane l's sums of entries 16 l + 4 j .. + 3 at byte 64 l + 16 (j ^ (l / 4 mod 4)): no bank conflicts either way
   unsigned char* share = sums + (threadIdx.x & ~63) * 64;
@@ -996,16 +1129,7 @@ __global__ void __launch_bounds__(TPB) sm_vote_int8_kernel(const vote_g_args g) 
 #pragma unroll
     for (int q = 0; q < 4; ++q) bits |= (s[q] >= 0 ? 1u : 0u) << q;
     if (4 * t >= a.n) break;
-    if (a.voted && ROWS && a.ld == a.sld) {  // bf16 with padded rows: zeros beyond cols
-      const int lv = live[k];
-      const u32x2 h = {pm1_bf16(bits) & ((0 < lv ? 0xFFFFu : 0u) | (1 < lv ? 0xFFFF0000u : 0u)),
-                       pm1_bf16(bits >> 2) & ((2 < lv ? 0xFFFFu : 0u) | (3 < lv ? 0xFFFF0000u : 0u))};
-      *reinterpret_cast<u32x2*>(reinterpret_cast<unsigned short*>(a.voted) + 4 * t) = h;
-    }
-    if (live[k] == 0) continue;
-    if (a.voted && !(ROWS && a.ld == a.sld)) voted4(a.voted, a.vfmt, at[k], bits, live[k]);
-    if (a.counts) counts4(a.counts + at[k], s, live[k]);
-    if (a.w) step4(a.w + at[k], a.lr, wv[k], bits, live[k]);
+    vote_out<ROWS>(a, t, live[k], at[k], bits, s, wv[k]);
   }
 }
 
@@ -1017,17 +1141,30 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
     sm_starts_clear(a.begin);
     a.n = g;
     a.pad_ = 0;
-    bool rows = false;
+    bool rows = false, counts = false;
     int max_m = 0;
-    // the 16-entry int8 kernel: whole groups, aligned rows and outputs, voted matrices alone
-    bool wide8 = (fmt == SM_SIGN_INT8);
+    long long entries = 0, shortest = 16;
+    const long long one_round = (long long)ctx->n_cu * 4 * 8 * 64 * 4;
+    bool whole = true, votes_alone = true;  // what sm_vote_int8_wide_kernel needs
     for (int i = 0; i < g; ++i) {
       const sm_vote_desc& d = descs[done + i];
       rows = rows || d.sld != 0;
+      counts = counts || d.counts;
+      entries += d.n;
+      shortest = std::min(shortest, d.n);
       max_m = std::max(max_m, d.M);
-      wide8 = wide8 && !d.sld && !d.w && !d.counts && d.n % 16 == 0 && d.stride_bytes % 16 == 0 && sm_aligned(d.signs, 16) &&
-              d.voted && sm_aligned(d.voted, 16) && (d.vfmt == SM_VOTE_INT8 || d.vfmt == SM_VOTE_BF16);
+      votes_alone = votes_alone && !d.w && !d.counts;
+      whole = whole && !d.sld && d.n % 16 == 0 && d.stride_bytes % 16 == 0 && sm_aligned(d.signs, 16) && sm_aligned(d.voted, 16) &&
+              sm_aligned(d.w, 16) && sm_aligned(d.counts, 16) && (!d.voted || d.vfmt == SM_VOTE_INT8 || d.vfmt == SM_VOTE_BF16);
     }
+    // Four entries per lane (sm_vote_narrow_kernel, figures there) where the launch is one round of its waves, eight per
+    // SIMD: latency counts.  Beyond, 1-bit signs take it with counts, which the wide form has to gather from other
+    // lanes plane by plane, until the eightfold reads of the words outweigh that (between 16 and 32 workers); int8 signs
+    // up to 8 workers, above which requests of four bytes bound it.  Whole int8 matrices go 16 entries per lane for
+    // votes alone, and for any output where many workers' signs outweigh it.
+    const bool wide8 = fmt == SM_SIGN_INT8 && whole && (votes_alone || (max_m >= 16 && entries >= 2 * one_round));
+    const bool narrow = fmt == SM_SIGN_1BIT ? entries <= one_round || (counts && max_m < 32)
+                                            : !wide8 && (max_m <= 8 || entries <= one_round || shortest < 16);
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
       sm_vote_desc& D = a.d[i];
@@ -1037,10 +1174,10 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
         if (!D.sld) D.sld = D.ld = D.cols;
         if (D.cols < 1 || D.sld % 64 || D.n % D.cols) return sm_fail(ctx, SM_EINVAL, "internal: vote rows");
         D.n = D.n / D.cols * D.sld;  // entries of the source
-        D.by_row = sm_div_by((unsigned)(fmt == SM_SIGN_1BIT ? D.sld / 32 : D.sld / 4));
+        D.by_row = sm_div_by((unsigned)(fmt == SM_SIGN_1BIT && !narrow ? D.sld / 32 : D.sld / 4));
       }
       a.begin.v[i] = (int)blocks;
-      const long long per_wg = fmt == SM_SIGN_1BIT ? 32 * TPB : 16 * TPB;
+      const long long per_wg = narrow ? 4 * TPB : fmt == SM_SIGN_1BIT ? 32 * TPB : 16 * TPB;
       blocks += (D.n + per_wg - 1) / per_wg;
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "vote: too many entries for one launch");
@@ -1050,7 +1187,14 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
 #define VOTE_WIDE(PLANES)                                                                                     \
   if (rows) hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, true>), grid, block, 0, ctx->stream, a);          \
   else hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, false>), grid, block, 0, ctx->stream, a)
-      if (fmt == SM_SIGN_1BIT) {
+#define VOTE_NARROW(FMT)                                                                                      \
+  if (rows) hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, true>), grid, block, 0, ctx->stream, a);           \
+  else hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, false>), grid, block, 0, ctx->stream, a)
+      if (narrow && fmt == SM_SIGN_1BIT) {
+        VOTE_NARROW(SM_SIGN_1BIT);
+      } else if (narrow) {
+        VOTE_NARROW(SM_SIGN_INT8);
+      } else if (fmt == SM_SIGN_1BIT) {
         if (max_m < 8) { VOTE_WIDE(3); }
         else if (max_m < 32) { VOTE_WIDE(5); }
         else if (max_m < 256) { VOTE_WIDE(8); }
@@ -1063,6 +1207,7 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
         hipLaunchKernelGGL((sm_vote_int8_kernel<false>), grid, block, 0, ctx->stream, a);
       }
 #undef VOTE_WIDE
+#undef VOTE_NARROW
     }
     SM_HIP(ctx, hipGetLastError());
     done += g;

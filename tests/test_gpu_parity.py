@@ -267,6 +267,57 @@ def test_vote_int8_runs_of_a_wave(P, ctx, M, n):
             assert np.array_equal(gv[:n], vote.astype(np.float32)) and np.all(gv[n:] == 9.0)
 
 
+ONE_ROUND = 1 << 21    # entries: the line between the vote kernels on a card of 256 compute units
+
+
+@pytest.mark.parametrize("fmt", ["1bit", "int8"])
+@pytest.mark.parametrize("M,n", [(1, ONE_ROUND), (1, ONE_ROUND + 1), (8, ONE_ROUND + 33), (9, ONE_ROUND), (9, ONE_ROUND + 1),
+                                 (12, ONE_ROUND + 1039), (9, 2 * ONE_ROUND + 8), (16, 2 * ONE_ROUND - 16), (16, 2 * ONE_ROUND), (17, 2 * ONE_ROUND + 8), (31, ONE_ROUND + 15), (32, ONE_ROUND + 17),
+                                 (248, 70), (249, 3), (500, 1)])
+def test_vote_on_both_sides_of_the_lines_between_its_kernels(P, ctx, fmt, M, n):
+    """Launches of up to one round of waves and beyond, with and without counts, up to 8 int8 and 31 1-bit workers and
+    more, ends of the buffer at any place in a lane's entries: every format of the votes, sums and update."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M * 31 + n)
+    S = torch.randint(0, 2, (M, n), generator=gen, device="cuda", dtype=torch.int8)
+    w0 = torch.randn((n,), generator=gen, device="cuda")
+    sums = S.sum(0, dtype=torch.int32)
+    vote = torch.where(2 * sums >= M, 1.0, -1.0)
+    if fmt == "1bit":
+        stride = O.packed_stride_bytes(n)
+        bits = torch.zeros((M, 8 * stride), dtype=torch.uint8, device="cuda")
+        bits[:, :n] = S.view(torch.uint8)
+        place = (2 ** torch.arange(8, device="cuda")).to(torch.uint8)
+        signs = (bits.view(M, stride, 8) * place).sum(-1, dtype=torch.uint8).contiguous()
+    else:
+        stride, signs, sums = n, 2 * S - 1, 2 * sums - M
+    lr = 2.0 ** -6
+    w_ref = w0 - lr * vote                                    # lr * vote is exact: one rounding, as in the kernels
+    for counts, update in ((False, False), (True, False), (False, True), (True, True)):
+        for vfmt, dt in ((None, None), ("int8", torch.int8), ("bf16", torch.bfloat16), ("f32", torch.float32)):
+            if not (counts or update or vfmt):
+                continue
+            cnt = torch.full((n + 4,), -7, dtype=torch.int32, device="cuda") if counts else None
+            w = torch.cat([w0, torch.full((4,), 3.0, device="cuda")]) if update else None
+            v = torch.full((n + 4,), 9, dtype=dt, device="cuda") if vfmt else None
+            P.signmuon_majority_vote(ctx, signs, fmt, M, n, stride, voted=v, vfmt=vfmt or "bits", counts=cnt, w=w, lr_scaled=lr)
+            what = (fmt, M, n, counts, update, vfmt)
+            if counts:
+                assert torch.equal(cnt[:n], sums) and bool((cnt[n:] == -7).all()), what
+            if update:
+                assert torch.equal(w[:n], w_ref) and bool((w[n:] == 3.0).all()), what
+            if vfmt:
+                assert torch.equal(v[:n].float(), vote) and bool((v[n:] == 9).all()), what
+
+
+@pytest.mark.parametrize("sign_fmt", ["1bit", "int8"])
+@pytest.mark.parametrize("M,Kp", [(9, 0), (3, 0), (9, 1)])
+def test_step_votes_beyond_one_round_over_padded_rows(P, ctx, sign_fmt, M, Kp):
+    """More entries in a step's vote than one round of the kernel of four entries per lane: rows of odd length, a whole
+    row's matrix and a tiny one in the launch, votes into padded rows (Kp) and flat ones."""
+    run_step_case(P, ctx, [(1100, 1999), (64, 128), (5, 1)], M, sign_fmt=sign_fmt, Kp=Kp, K=0, check_ns_blocks=())
+
+
 @pytest.mark.parametrize("snr", [0.25, 1.0])
 def test_majority_vote_sign_error_falls_like_inverse_sqrt_m(P, ctx, snr):
     """Lemma "Majority vote improves sign reliability": with M independent workers whose gradient entries are
