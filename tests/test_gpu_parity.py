@@ -480,19 +480,22 @@ def test_polar_ns_with_tiles_of_64(P, ns_path, r, c):
 @pytest.mark.parametrize("opts", [dict(gemm_tile=128), dict(gemm_tile=256), dict(gemm_tile=256, ns_store="full"),
                                   dict(gemm_tile=128, ns_path="stepwise")])
 @pytest.mark.parametrize("r,c", [(1152, 1408), (1408, 1152)])
-def test_polar_ns_on_grids_of_several_tile_bands(P, opts, r, c):
+@pytest.mark.parametrize("batch", [2, 6])
+def test_polar_ns_on_grids_of_several_tile_bands(P, opts, r, c, batch):
     """The GEMM kernels list a matrix's tiles in bands of 4 (256-wide tiles) or 8 (128-wide) tile rows.  A short
     side of 1152 is 4.5 and 9 tiles: the symmetric products and the apply run over a full band and a ragged
-    one, in both operand orientations."""
+    one, in both operand orientations.  The symmetric launches of two matrices have 90 tiles of 128, one round of a
+    card of 256 compute units: three LDS stages, whole s x s matrices; those of six have 270: two stages, of the s x s
+    matrices the blocks on and above the diagonal.  256-wide tiles have two stages either way."""
     ctx = P.Context(**opts)
-    x = wl.normal((2, r, c), stream=27, block=r, worker=c)
+    x = wl.normal((batch, r, c), stream=27, block=r, worker=c)
     xd = dev(wl.to_bf16_bits(x).view(np.int16)).view(torch.bfloat16)
     xin = wl.from_bf16_bits(wl.to_bf16_bits(x))
     P.signmuon_polar_ns(ctx, xd, 5, scale="fro")
     got = xd.float().cpu().numpy()
-    for b in range(2):
+    for b in (0, batch - 1):
         ns_check(got[b], O.polar_ns(xin[b], 5, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32),
-                 f"{(r, c, opts)} item {b}")
+                 f"{(batch, r, c, opts)} item {b}")
     torch.cuda.synchronize()
     ctx.close()
 
