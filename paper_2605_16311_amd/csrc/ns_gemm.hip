@@ -900,7 +900,7 @@ using namespace sm_gemm;
 // tile_begin[n_prob]; returns the total number of tiles, or -1 on bad arguments.
 extern "C" int signmuon_debug_tile_ranges(int n_prob, const int* M, const int* N, const int* K, const int* batch,
                                           const int* mate, int sym, int ts, int* xcd_begin, int* tile_begin) {
-  if (n_prob < 1 || n_prob > SM_GEMM_MAX_PROB || (ts != 128 && ts != 256)) return -1;
+  if (n_prob < 1 || n_prob > SM_GEMM_MAX_PROB || (ts != 64 && ts != 128 && ts != 256)) return -1;
   sm_gemm_args a;
   a.n_prob = n_prob;
   for (int i = 0; i < n_prob; ++i) {

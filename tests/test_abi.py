@@ -121,6 +121,19 @@ def test_gemm_tile_ranges_cover_the_list_and_balance_cost():
     # a leader with a mate owns the tiles of both; the mate's range is empty and sits at the leader's end
     total, xcd, begin = _tile_ranges(lib, [(768, 768, 768, 10, 1), (768, 768, 768, 10, 0), (512, 512, 512, 3, 0)], True, 256)
     assert begin == [0, 120, 120] and total == 120 + 3 * 3
+    # every tile size: the ranges cover the list, and each range's cost is the mean within one tile of the longest K
+    probs = [(1000, 1000, 2048, 3, 0), (192, 192, 192, 7, 0), (512, 512, 4608, 4, 0), (64, 64, 576, 5, 0)]
+    for ts in (64, 128, 256):
+        for sym in (True, False):
+            total, xcd, begin = _tile_ranges(lib, probs, sym, ts)
+            grid = [-(-p[0] // ts) for p in probs]
+            tiles = [(g * (g + 1) // 2 if sym else g * g) * p[3] for g, p in zip(grid, probs)]
+            assert total == sum(tiles) and begin == [sum(tiles[:i]) for i in range(4)], (ts, sym)
+            assert xcd[0] == 0 and xcd[8] == total and all(a <= b for a, b in zip(xcd, xcd[1:])), (ts, sym)
+            per = [k / 64 + 6.0 for (_, _, k, _, _), n in zip(probs, tiles) for _ in range(n)]
+            cost = [sum(per[xcd[x]:xcd[x + 1]]) for x in range(8)]
+            assert max(cost) <= sum(per) / 8 + max(per), (ts, sym)
+    assert lib.signmuon_debug_tile_ranges(1, None, None, None, None, None, 1, 96, None, None) == -1
     assert lib.signmuon_debug_tile_ranges(0, None, None, None, None, None, 1, 256, None, None) == -1
 
 

@@ -587,10 +587,13 @@ def test_step_mixed_set(P, vctx, sign_fmt, Kp):
     run_step_case(P, ctx, shapes, 3, sign_fmt=sign_fmt, Kp=Kp, wd=0.1, rsqrt=(Kp > 0))
 
 
-@pytest.mark.parametrize("batch,r,c", [(8, 641, 700), (8, 764, 710), (7, 830, 770), (1, 1990, 2010)])
+@pytest.mark.parametrize("batch,r,c", [(8, 641, 700), (8, 764, 710), (7, 830, 770), (1, 1990, 2010), (5, 641, 700), (5, 700, 641),
+                                       (5, 710, 764), (5, 764, 710), (5, 770, 830), (5, 830, 770)])
 def test_polar_ns_in_one_round_of_tiles_of_128(P, ctx, batch, r, c):
-    """Launches of 129 to 256 tiles of 128 with a long K, which take three LDS stages: every remainder of the number of
-    slices by three, last tiles that are half empty, both orientations."""
+    """Launches of 129 to 256 tiles of 128 with more than ten slices of K, which take three LDS stages on a card of 256
+    compute units; last tiles are half empty.  Batches of 7 and 8: the symmetric products, 11, 12 and 13 slices (every
+    remainder by three), while their applies have 288 tiles or more and keep two stages.  Batches of 5: the applies (180
+    to 245 tiles), 11, 12 and 13 slices, wide and tall.  One matrix of 1990 x 2010: both, 32 slices."""
     x = wl.normal((batch, r, c), stream=63, block=r, worker=c)
     xd = dev(x)
     P.signmuon_polar_ns(ctx, xd, 5)
