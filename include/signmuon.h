@@ -83,14 +83,19 @@ int signmuon_destroy(signmuon_ctx* ctx);
 /* Tuning switches of a context.  Every setting computes the same path within the
  * same tolerances; they exist for measurements and tests.  Values other than the
  * listed ones give SM_EINVAL. */
-#define SM_OPT_GEMM_TILE 0 /* workgroup tile of the Newton-Schulz GEMMs: 0 = by launch size (default), 64, 128, 256 */
+#define SM_OPT_GEMM_TILE 0 /* workgroup tile of the Newton-Schulz GEMMs: 0 = by launch size (default), 64, 128, 256.
+                            * A fixed tile also gives every product a launch of its own: the run of products of
+                            * small matrices in one launch (short sides up to 128, or up to 256 for many matrices)
+                            * belongs to 0.  The number of LDS stages goes by the launch in any case. */
 #define SM_OPT_NS_PATH 1   /* how the K steps of the cubic iteration are grouped: */
 #define SM_NS_PATH_PAIRS 0    /*   short-side recurrence, two steps per quartic (default) */
 #define SM_NS_PATH_SINGLE 1   /*   short-side recurrence, one step at a time */
 #define SM_NS_PATH_STEPWISE 2 /*   Alg. PolarNS as written: Gram and apply of Y per step */
 #define SM_OPT_NS_STORE 2  /* storage of the symmetric s x s matrices of the recurrence: */
-#define SM_NS_STORE_UPPER 0   /*   blocks on and above the diagonal only (default) */
-#define SM_NS_STORE_FULL 1    /*   whole matrices */
+#define SM_NS_STORE_UPPER 0   /*   blocks on and above the diagonal only (default), where the products of a step
+                               *   have two LDS stages; launches of few tiles (three stages: tiles of 64, and one
+                               *   round of tiles of 128 with a long K) hold whole matrices */
+#define SM_NS_STORE_FULL 1    /*   whole matrices, and every product in a launch of its own */
 #define SM_OPT_POWER_ITER 3 /* passes of Alg. PowerIter over X: */
 #define SM_PI_AUTO 0          /*   fused where that is faster by a launch-cost estimate (default) */
 #define SM_PI_FUSED 1         /*   u = X v and X^T u from one read of X wherever the matrix is narrow enough */
