@@ -227,12 +227,13 @@ void gram_of_y(ns_class& cl, sm_gemm_prob& P, const bf16_t* y, bf16_t* c, int ba
 struct ns_sign_req {
   int fmt;
   bool write_y;
+  bool whole_rows;  // only of the classes whose rows are not padded; the others' Y is written
 };
 
 void apply_to_y(signmuon_ctx* ctx, ns_class& cl, sm_gemm_prob& P, const bf16_t* sm, const bf16_t* y, bf16_t* yout,
                 int batch, const ns_sign_req* signs) {
   const long long ss = (long long)cl.s * cl.s;
-  if (signs) {
+  if (signs && !(signs->whole_rows && cl.cp != cl.cols)) {
     P.sign_out = at<void>(ctx, cl.off_signs);
     P.sign_stride = cl.sign_stride;
     P.sign_rows = cl.rows;
@@ -930,20 +931,29 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
 
   // a3 + a4: K Newton-Schulz steps on all (block, worker) matrices
   // When the iteration has at least one step, its last apply writes the packed signs (a5); U itself is then only
-  // written if a tap asks for it, or for signs whose rows are not those of the internal buffer.
+  // written if a tap asks for it, or for signs whose rows are not those of the internal buffer.  Where the vote only
+  // updates W and every block with such rows has its signs tapped, the vote reads the taps, and the apply need not
+  // write these blocks' signs as well (1000 x 2047, 9 workers, int8: 693 us with them, 659 without).
+  const int Kp = s->local_polar_steps;
+  auto tapped = [&](int i) { return s->signs_out && s->signs_out[i]; };
+  bool any = false, all = true;  // blocks with padded rows and a tap of their signs
+  for (int i = 0; i < n; ++i) {
+    if (s->cols[i] % 64 == 0) continue;
+    any = any || tapped(i);
+    all = all && tapped(i);
+  }
+  const bool vote_taps = any && all && Kp == 0 && !op_norm;
   ns_sign_req sreq;
   sreq.fmt = s->sign_fmt;
-  sreq.write_y = false;
+  sreq.whole_rows = vote_taps;
+  sreq.write_y = any && !vote_taps;
   if (s->u_out)
     for (int i = 0; i < n; ++i) sreq.write_y = sreq.write_y || (s->u_out[i] != nullptr);
-  if (s->signs_out)
-    for (int i = 0; i < n; ++i) sreq.write_y = sreq.write_y || (s->signs_out[i] != nullptr && s->cols[i] % 64 != 0);
   const bool fused = s->ns_steps > 0;
   int cur = 0;
   rc = run_ns(ctx, pl, M, s->ns_steps, s->coeffs, use_scale, &cur, fused ? &sreq : nullptr);
   if (rc != SM_OK) return rc;
 
-  const int Kp = s->local_polar_steps;
   // a5 + a6 (+ a8 when there is no local polar step): one vote launch over all blocks, after a sign-pack launch where
   // no apply has written the signs, and another for the taps of signs with rows that are not whole words
   std::vector<sm_sp_desc> sp, sp_tap;
@@ -952,34 +962,35 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     ns_class& cl = pl->classes[pl->class_of[i]];
     const int idx = pl->index_in_class[i];
     const long long d = (long long)cl.rows * cl.cols;
-    const bool padded = cl.cp != cl.cols;
+    const bool padded = cl.cp != cl.cols, from_tap = padded && vote_taps;
     const bf16_t* u = at<bf16_t>(ctx, cl.off_x[cur]) + (long long)idx * M * cl.mat;
     if (s->u_out && s->u_out[i]) {
       rc = sm_launch_copy_out(ctx, u, cl.cp, cl.mat, M, cl.rows, cl.cols, s->u_out[i], SM_BF16,
                               (s->ns_steps == 0 && use_scale) ? at<float>(ctx, cl.off_inv) + (long long)idx * M : nullptr);
       if (rc != SM_OK) return rc;
     }
-    void* signs = at<void>(ctx, pl->off_signs[i]);
-    const long long stride = pl->sign_stride[i];
+    const long long tap_stride = (s->sign_fmt == SM_SIGN_INT8) ? d : 8 * ((d + 63) / 64);
+    void* signs = from_tap ? s->signs_out[i] : at<void>(ctx, pl->off_signs[i]);
+    const long long stride = from_tap ? tap_stride : pl->sign_stride[i];
     sm_sp_desc S;
     S.u = u;
     S.batch_stride = cl.mat;
     S.blocks_per_row = S.pad_ = 0;
-    if (!fused) {  // the rows of u with their padding are the rows of the internal buffer
+    if (!fused && !from_tap) {  // the rows of u with their padding are the rows of the internal buffer
       S.out = signs;
       S.n = (long long)cl.rows * cl.cp;
       S.out_stride = stride;
       S.cols = S.ld = cl.cp;
       sp.push_back(S);
     }
-    if (s->signs_out && s->signs_out[i] && (padded || !fused)) {
+    if (tapped(i) && (padded || !fused)) {
       S.out = s->signs_out[i];
       S.n = d;
-      S.out_stride = (s->sign_fmt == SM_SIGN_INT8) ? d : 8 * ((d + 63) / 64);
+      S.out_stride = tap_stride;
       S.cols = cl.cols;
       S.ld = cl.cp;
       sp_tap.push_back(S);
-    } else if (s->signs_out && s->signs_out[i]) {
+    } else if (tapped(i)) {
       SM_HIP(ctx, hipMemcpyAsync(s->signs_out[i], signs, (size_t)stride * M, hipMemcpyDeviceToDevice, ctx->stream));
     }
     float step = s->lr;
@@ -992,7 +1003,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     V.lr = step;
     V.M = M;
     V.cols = cl.cols;
-    V.sld = padded ? cl.cp : 0;
+    V.sld = (padded && !from_tap) ? cl.cp : 0;
     if (Kp == 0 && !op_norm) {
       V.voted = nullptr;
       V.vfmt = SM_VOTE_BF16;

@@ -619,6 +619,33 @@ def test_step_with_rows_of_any_length(P, sign_fmt, Kp, K):
         c.close()
 
 
+@pytest.mark.parametrize("sign_fmt", ["1bit", "int8"])
+@pytest.mark.parametrize("K,Kp", [(0, 0), (5, 0), (2, 3)])
+def test_step_results_do_not_depend_on_the_taps_of_signs(P, ctx, sign_fmt, K, Kp):
+    """No tap, a tap of every block's signs (from which the vote then reads padded blocks), of the padded blocks alone and
+    of some of them: the same momentum, weights and counts to the bit, and the same signs wherever they are tapped."""
+    shapes, M = [(129, 101), (64, 128), (67, 33), (1, 7), (5, 1), (1100, 1999)], 9
+    padded = {i for i, (r, c) in enumerate(shapes) if c % 64}
+    first = None
+    for tapped in (set(), set(range(6)), padded, {0, 1}, {5}):
+        w = [dev(wl.weights(r, c, block=i, stream=70)) for i, (r, c) in enumerate(shapes)]
+        grad = [dev(wl.normal((M, r, c), stream=70, block=i, worker=1)) for i, (r, c) in enumerate(shapes)]
+        mom = [torch.zeros_like(g) for g in grad]
+        size = [O.packed_stride_bytes(r * c) if sign_fmt == "1bit" else r * c for r, c in shapes]
+        signs = [torch.zeros((M, n), dtype=torch.uint8, device="cuda") if i in tapped else None for i, n in enumerate(size)]
+        counts = [torch.zeros((r * c,), dtype=torch.int32, device="cuda") for r, c in shapes]
+        plan = P.StepPlan(w, mom, grad, beta=0.9, lr=1e-3, ns_steps=K, sign_fmt=sign_fmt, local_polar_steps=Kp,
+                          signs_out=signs if tapped else None, counts_out=counts)
+        P.signmuon_step(ctx, plan)
+        got = [t.cpu() for t in w + mom + counts]
+        seen = {i: signs[i].cpu() for i in tapped}
+        if first is None:
+            first, sign_ref = got, {}
+        assert all(torch.equal(a, b) for a, b in zip(got, first)), tapped
+        for i, t in seen.items():
+            assert torch.equal(t, sign_ref.setdefault(i, t)), (tapped, i)
+
+
 @pytest.mark.parametrize("special", [False, True])
 def test_step_signs_written_by_the_apply_alone(P, vctx, special):
     """Without a u_out tap the last apply writes only the packed signs (U is never stored; the bits come
