@@ -39,7 +39,7 @@ SIMD_PER_XCD, XCDS = 128, 8          # 32 CUs x 4 SIMDs per XCD
 # kernel classes of bench.py -> substring of the kernel name
 CLASSES = {
     "sm_ns_gemm_kernel (Gram of Y)": ["sm_ns_gemm_kernel<0,"],
-    "sm_ns_gemm_kernel (short-side recurrence)": ["sm_ns_gemm_kernel<3,", "sm_ns_gemm_kernel<2,"],
+    "sm_ns_gemm_kernel (short-side recurrence)": ["sm_ns_gemm_kernel<3,", "sm_ns_gemm_kernel<2,", "sm_ns_chain_kernel<"],
     "sm_ns_gemm_kernel (apply to Y)": ["sm_ns_gemm_kernel<1,"],
 }
 
@@ -87,7 +87,7 @@ def collect(out, workload, passes):
 
 
 def short(n):
-    n = n.replace("void ", "").replace("(anonymous namespace)::", "").replace("sm_gemm::", "")
+    n = n.replace("void ", "").replace("(anonymous namespace)::", "").replace("sm_gemm::", "").replace("sm_chain::", "")
     return re.sub(r"\(.*", "", n)[:72]
 
 
@@ -117,10 +117,11 @@ def summarise_kt(out, workload, prof):
     for r in rows[:14]:
         lines.append("%-72s %6s %11.3f %10.2f %7.2f" % (short(r["Name"]), r["Calls"], float(r["TotalDurationNs"]) / 1e6,
                                                         float(r["AverageNs"]) / 1e3, float(r["Percentage"])))
-    lines += ["", "sm_ns_gemm_kernel<KIND, TILE>: KIND 0 = Gram of Y, 1 = apply to Y (the pre-vote launch also writes the packed",
-              "  signs: there is no sign-pack kernel in the step), 3 = products of s x s matrices of the short-side recurrence",
-              "  (2 = the same with whole-matrix storage); TILE = 256 before the vote, 128 after it on this workload.",
-              "  bench.py's per-class avg_launch_ms is the mean over the launches of both tile sizes."]
+    lines += ["", "sm_ns_gemm_kernel<KIND, TILE, STAGES>: KIND 0 = Gram of Y, 1 = apply to Y (the pre-vote launch also writes the",
+              "  packed signs: there is no sign-pack kernel in the step), 3 = products of s x s matrices of the short-side",
+              "  recurrence (2 = the same with whole-matrix storage); TILE: side of a workgroup's tile; STAGES: LDS stages of a",
+              "  slice.  sm_ns_chain_kernel<SB>: all products of a segment for matrices of s <= 128 SB, in one launch.",
+              "  bench.py's per-class avg_launch_ms is the mean over the class's launches of every tile size."]
     open(os.path.join(prof, f"{workload}_kernel_trace.txt"), "w").write("\n".join(lines) + "\n")
     return avg
 
@@ -203,7 +204,7 @@ def summarise_mfma(out, workload, prof, kt_avg):
              "clock = gui / 8 / kernel duration of the kernel-trace run (other run, same command line apart from --steps).", "",
              "%-40s %5s %12s %12s %7s %12s %10s %9s" % ("kernel", "disp", "mfma_busy", "gui", "util", "flop", "avg_us(kt)", "clock_GHz")]
     for k, d in sorted(m.items(), key=lambda kv: -kv[1].get("SQ_VALU_MFMA_BUSY_CYCLES", (0, 0))[1]):
-        if "sm_ns_gemm" not in k:
+        if "sm_ns_" not in k:
             continue
         n, busy = d.get("SQ_VALU_MFMA_BUSY_CYCLES", (0, 0.0))
         gui = d.get("GRBM_GUI_ACTIVE", (0, 0.0))[1]
