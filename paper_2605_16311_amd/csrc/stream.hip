@@ -1001,72 +1001,104 @@ __device__ __forceinline__ void vote_out(const vote_x_args& a, long long t, int 
   if (a.w) step4(a.w + at, a.lr, wv, bits, live);
 }
 
-// Expanding vote, a lane takes four entries: no exchange between lanes, so the chain from the signs to the results is
-// short, and accesses of every output are consecutive across lanes.  1 bit: the entries' bits out of every worker's word
-// (eight lanes read the same one), counted in the four bytes of a register, 248 workers at most before the bytes are
-// taken out.  us, this form / the other form of the transport (sm_vote_wide_kernel, sm_vote_int8_kernel):
-//   1 bit, bf16 votes + counts + update   0.26 M entries, M = 16   4.9 / 7.5      4 M, M = 1   11.6 / 13.0
+// Expanding vote, a lane takes GROUPS times four entries, a workgroup's width apart: no exchange between lanes, so the
+// chain from the signs to the results is short, and accesses of every output are consecutive across lanes.  1 bit: the
+// entries' bits out of every worker's word (eight lanes read the same one), counted in the four bytes of a register, 248
+// workers at most before the bytes are taken out.  us, one group (four where it says so) / the other form of the
+// transport (sm_vote_wide_kernel, sm_vote_int8_kernel):
+//   1 bit, bf16 votes + counts + update   0.26 M entries, M = 16   4.9 / 7.5      4 M, M = 1 (four)   10.1 / 13.0
 //                                         33 M, M = 8   73 / 76                   33 M, M = 32   134 / 94
 //   1 bit, counts                         33 M, M = 8   25 / 32                   1 bit, bf16 votes   8 M, M = 8   7.9 / 6.2
 //   int8, counts                          33 M, M = 8   60 / 75                   4 M, M = 16   18.9 / 17.3
 //   int8, f32 votes                       2 M, M = 8   4.5 / 5.5                  4 M, M = 32   31.5 / 30.2
 // ROWS as in sm_vote_wide_kernel.
-template <int FMT, bool ROWS>
+template <int FMT, bool ROWS, int GROUPS>
 __global__ void __launch_bounds__(TPB) sm_vote_narrow_kernel(const vote_g_args g) {
+  constexpr int AHEAD = GROUPS > 1 ? 4 : VOTE_GROUP;  // workers in flight
   const int di = sm_find(g.begin, g.n, blockIdx.x);
   const vote_x_args& a = g.d[di];
-  const long long t = (long long)(blockIdx.x - g.begin.v[di]) * TPB + threadIdx.x;
-  if (4 * t >= a.n) return;
-  int live;
-  long long at;
-  vote_place<ROWS>(a, t, live, at);
-  f32x4 wv = {0.f, 0.f, 0.f, 0.f};
-  if (a.w) wv = load4(a.w + at, live);
-  i32x4 c = {0, 0, 0, 0};
-  unsigned bits = 0;
-  if (FMT == SM_SIGN_1BIT) {
-    const unsigned* base = reinterpret_cast<const unsigned*>(a.signs) + (t >> 3);
-    const int sh = 4 * (int)(t & 7);
-    const long long stride_w = a.stride_bytes >> 2;
-    for (int p0 = 0; p0 < a.M; p0 += 31 * VOTE_GROUP) {
-      unsigned acc = 0;
-      for_workers<VOTE_GROUP>(p0, min(a.M, p0 + 31 * VOTE_GROUP), [&](auto count, int p) {
-        constexpr int N = decltype(count)::value;
-        unsigned x[N];
+  const long long first = (long long)(blockIdx.x - g.begin.v[di]) * TPB * GROUPS;
+  const long long t0 = first + threadIdx.x;
+  i32x4 c[GROUPS];
 #pragma unroll
-        for (int q = 0; q < N; ++q) x[q] = base[(long long)(p + q) * stride_w];
+  for (int j = 0; j < GROUPS; ++j) c[j] = i32x4{0, 0, 0, 0};
+  // whole: every group of the workgroup lies inside the buffer with all four entries
+  auto count = [&](auto whole) {
+    bool full[GROUPS];
 #pragma unroll
-        for (int q = 0; q < N; ++q) acc += (((x[q] >> sh) & 0xFu) * 0x00204081u) & 0x01010101u;
-      });
+    for (int j = 0; j < GROUPS; ++j) full[j] = decltype(whole)::value || 4 * (t0 + j * TPB) + (FMT == SM_SIGN_1BIT ? 1 : 4) <= a.n;
+    if (FMT == SM_SIGN_1BIT) {
+      const unsigned* base = reinterpret_cast<const unsigned*>(a.signs) + (t0 >> 3);
+      const int sh = 4 * (int)(t0 & 7);
+      const long long stride_w = a.stride_bytes >> 2;
+      for (int p0 = 0; p0 < a.M; p0 += 31 * VOTE_GROUP) {
+        unsigned acc[GROUPS] = {};
+        for_workers<AHEAD>(p0, min(a.M, p0 + 31 * VOTE_GROUP), [&](auto number, int p) {
+          constexpr int N = decltype(number)::value;
+          unsigned x[GROUPS][N];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] += (int)((acc >> (8 * k)) & 0xFFu);
-    }
+          for (int j = 0; j < GROUPS; ++j)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bits |= (2 * c[k] >= a.M ? 1u : 0u) << k;
-  } else {
-    const signed char* src = reinterpret_cast<const signed char*>(a.signs) + 4 * t;
-    if (4 * t + 4 <= a.n) {
-      for_workers<VOTE_GROUP>(0, a.M, [&](auto count, int p) {
-        constexpr int N = decltype(count)::value;
-        unsigned x[N];
+            for (int q = 0; q < N; ++q) x[j][q] = full[j] ? base[(long long)(p + q) * stride_w + j * (TPB / 8)] : 0u;
 #pragma unroll
-        for (int q = 0; q < N; ++q)
-          x[q] = __builtin_nontemporal_load(reinterpret_cast<const u32_u*>(src + (long long)(p + q) * a.stride_bytes));
+          for (int j = 0; j < GROUPS; ++j)
 #pragma unroll
-        for (int q = 0; q < N; ++q)
+            for (int q = 0; q < N; ++q) acc[j] += (((x[j][q] >> sh) & 0xFu) * 0x00204081u) & 0x01010101u;
+        });
 #pragma unroll
-          for (int k = 0; k < 4; ++k) c[k] += (int)(signed char)(x[q] >> (8 * k));
-      });
+        for (int j = 0; j < GROUPS; ++j)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) c[j][k] += (int)((acc[j] >> (8 * k)) & 0xFFu);
+      }
     } else {
-      for (int p = 0; p < a.M; ++p)
+      const signed char* src = reinterpret_cast<const signed char*>(a.signs) + 4 * t0;
+      for_workers<AHEAD>(0, a.M, [&](auto number, int p) {
+        constexpr int N = decltype(number)::value;
+        unsigned x[GROUPS][N];
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-          if (4 * t + k < a.n) c[k] += src[(long long)p * a.stride_bytes + k];
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+          for (int j = 0; j < GROUPS; ++j)
+            x[j][q] = full[j] ? __builtin_nontemporal_load(reinterpret_cast<const u32_u*>(src + (long long)(p + q) * a.stride_bytes + 4 * j * TPB)) : 0u;
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j)
+#pragma unroll
+          for (int q = 0; q < N; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[j][k] += (int)(signed char)(x[j][q] >> (8 * k));
+      });
+#pragma unroll
+      for (int j = 0; j < GROUPS; ++j)
+        if (!full[j] && 4 * (t0 + j * TPB) < a.n)  // up to three entries at the end of the buffer
+          for (int p = 0; p < a.M; ++p)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+              if (4 * (t0 + j * TPB) + k < a.n) c[j][k] += src[(long long)p * a.stride_bytes + 4 * j * TPB + k];
     }
+  };
+  int live[GROUPS];
+  long long at[GROUPS];
+  f32x4 wv[GROUPS];
+  auto weights = [&]() {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bits |= (c[k] >= 0 ? 1u : 0u) << k;
+    for (int j = 0; j < GROUPS; ++j) {
+      vote_place<ROWS>(a, t0 + j * TPB, live[j], at[j]);
+      if (a.w) wv[j] = load4(a.w + at[j], live[j]);
+    }
+  };
+  if (GROUPS == 1) weights();  // requested before the signs; with four groups after them (6.2 M, M = 4, all outputs: 22.5 / 17.8 us)
+  if (4 * (first + GROUPS * TPB) <= a.n) count(std::true_type());
+  else count(std::false_type());
+  if (GROUPS > 1) weights();
+#pragma unroll
+  for (int j = 0; j < GROUPS; ++j) {
+    const long long t = t0 + j * TPB;
+    if (4 * t >= a.n) break;
+    unsigned bits = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bits |= ((FMT == SM_SIGN_1BIT ? 2 * c[j][k] >= a.M : c[j][k] >= 0) ? 1u : 0u) << k;
+    vote_out<ROWS>(a, t, live[j], at[j], bits, c[j], wv[j]);
   }
-  vote_out<ROWS>(a, t, live, at, bits, c, wv);
 }
 
 // Expanding vote over int8 signs for many workers and entries (at least 16 of them).  A wave takes 1024 consecutive
@@ -1165,6 +1197,9 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
     const bool wide8 = fmt == SM_SIGN_INT8 && whole && (votes_alone || (max_m >= 16 && entries >= 2 * one_round));
     const bool narrow = fmt == SM_SIGN_1BIT ? entries <= one_round || (counts && max_m < 32)
                                             : !wide8 && (max_m <= 8 || entries <= one_round || shortest < 16);
+    // Four groups per lane where few workers leave a lane few loads (int8, int8 votes + counts, 6.2 M entries, M = 1 / 4 /
+    // 6 / 8, one group 9.8 / 13.5 / 14.4 / 16.5 us, four 7.5 / 10.7 / 13.8 / 17.0).
+    const bool few = narrow && max_m < 8 && entries > one_round;
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
       sm_vote_desc& D = a.d[i];
@@ -1177,7 +1212,7 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
         D.by_row = sm_div_by((unsigned)(fmt == SM_SIGN_1BIT && !narrow ? D.sld / 32 : D.sld / 4));
       }
       a.begin.v[i] = (int)blocks;
-      const long long per_wg = narrow ? 4 * TPB : fmt == SM_SIGN_1BIT ? 32 * TPB : 16 * TPB;
+      const long long per_wg = narrow ? 4 * TPB * (few ? 4 : 1) : fmt == SM_SIGN_1BIT ? 32 * TPB : 16 * TPB;
       blocks += (D.n + per_wg - 1) / per_wg;
     }
     if (blocks > 0x7FFFFFFFLL) return sm_fail(ctx, SM_EUNSUPPORTED, "vote: too many entries for one launch");
@@ -1187,13 +1222,15 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
 #define VOTE_WIDE(PLANES)                                                                                     \
   if (rows) hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, true>), grid, block, 0, ctx->stream, a);          \
   else hipLaunchKernelGGL((sm_vote_wide_kernel<PLANES, false>), grid, block, 0, ctx->stream, a)
-#define VOTE_NARROW(FMT)                                                                                      \
-  if (rows) hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, true>), grid, block, 0, ctx->stream, a);           \
-  else hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, false>), grid, block, 0, ctx->stream, a)
+#define VOTE_NARROW(FMT, GROUPS)                                                                               \
+  if (rows) hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, true, GROUPS>), grid, block, 0, ctx->stream, a);   \
+  else hipLaunchKernelGGL((sm_vote_narrow_kernel<FMT, false, GROUPS>), grid, block, 0, ctx->stream, a)
       if (narrow && fmt == SM_SIGN_1BIT) {
-        VOTE_NARROW(SM_SIGN_1BIT);
+        if (few) { VOTE_NARROW(SM_SIGN_1BIT, 4); }
+        else { VOTE_NARROW(SM_SIGN_1BIT, 1); }
       } else if (narrow) {
-        VOTE_NARROW(SM_SIGN_INT8);
+        if (few) { VOTE_NARROW(SM_SIGN_INT8, 4); }
+        else { VOTE_NARROW(SM_SIGN_INT8, 1); }
       } else if (fmt == SM_SIGN_1BIT) {
         if (max_m < 8) { VOTE_WIDE(3); }
         else if (max_m < 32) { VOTE_WIDE(5); }

@@ -271,12 +271,12 @@ ONE_ROUND = 1 << 21    # entries: the line between the vote kernels on a card of
 
 
 @pytest.mark.parametrize("fmt", ["1bit", "int8"])
-@pytest.mark.parametrize("M,n", [(1, ONE_ROUND), (1, ONE_ROUND + 1), (8, ONE_ROUND + 33), (9, ONE_ROUND), (9, ONE_ROUND + 1),
+@pytest.mark.parametrize("M,n", [(1, ONE_ROUND), (1, ONE_ROUND + 1), (4, ONE_ROUND + 1039), (7, ONE_ROUND + 4094), (8, ONE_ROUND + 33), (9, ONE_ROUND), (9, ONE_ROUND + 1),
                                  (12, ONE_ROUND + 1039), (9, 2 * ONE_ROUND + 8), (16, 2 * ONE_ROUND - 16), (16, 2 * ONE_ROUND), (17, 2 * ONE_ROUND + 8), (31, ONE_ROUND + 15), (32, ONE_ROUND + 17),
                                  (248, 70), (249, 3), (500, 1)])
 def test_vote_on_both_sides_of_the_lines_between_its_kernels(P, ctx, fmt, M, n):
-    """Launches of up to one round of waves and beyond, with and without counts, up to 8 int8 and 31 1-bit workers and
-    more, ends of the buffer at any place in a lane's entries: every format of the votes, sums and update."""
+    """Launches of up to one round of waves and beyond, with and without counts, up to 7 workers, 8 int8 and 31 1-bit ones
+    and more, ends of the buffer at any place in a lane's entries: every format of the votes, sums and update."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M * 31 + n)
     S = torch.randint(0, 2, (M, n), generator=gen, device="cuda", dtype=torch.int8)
