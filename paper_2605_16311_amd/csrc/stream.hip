@@ -349,6 +349,35 @@ __device__ __forceinline__ void planes_add(W (&plane)[PLANES], W x) {
   }
 }
 
+// Adds eight words at once: full adders down to one carry into plane 3, then one ripple.  For the many planes of 256
+// workers and more, where eight ripples are 16 operations per plane: bits from 300 workers, 0.1 / 1 / 17 M entries, by
+// ripples 179 / 158 / 505 us, so 68 / 57 / 125 (the first by the latency of 38 rounds of loads).
+template <int PLANES, typename W>
+__device__ __forceinline__ void planes_add8(W (&plane)[PLANES], const W (&x)[8]) {
+  if constexpr (PLANES <= 8) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) planes_add<PLANES>(plane, x[q]);
+  } else {
+    // sum <- sum + a + b of one weight; returns the carry
+    auto add = [](W& sum, W a, W b) {
+      const W d = sum ^ a, carry = (sum & a) | (d & b);
+      sum = d ^ b;
+      return carry;
+    };
+    const W two0 = add(plane[0], x[0], x[1]), two1 = add(plane[0], x[2], x[3]);
+    const W four0 = add(plane[1], two0, two1);
+    const W two2 = add(plane[0], x[4], x[5]), two3 = add(plane[0], x[6], x[7]);
+    const W four1 = add(plane[1], two2, two3);
+    W eight = add(plane[2], four0, four1);
+#pragma unroll
+    for (int k = 3; k < PLANES; ++k) {
+      const W t = plane[k] & eight;
+      plane[k] ^= eight;
+      eight = t;
+    }
+  }
+}
+
 // Bit mask of the positions whose count is >= T.
 template <int PLANES, typename W>
 __device__ __forceinline__ W planes_ge(const W (&plane)[PLANES], unsigned T) {
@@ -365,7 +394,7 @@ __device__ __forceinline__ W planes_ge(const W (&plane)[PLANES], unsigned T) {
 // Workers are read eight at a time: all eight loads of a group are issued before the first is
 // added, so a thread keeps 8 x 16 bytes in flight (rows beyond M read as zero words, which
 // count nothing).
-constexpr int VOTE_GROUP = 8;
+constexpr int VOTE_GROUP = 8;  // as many as planes_add8 takes
 constexpr int VOTE8_GROUP = 4;  // with 16 bytes per load and 16 sums: eight cost the registers of every other wave
 
 // f(number of workers, first worker) over workers [first, end) in groups of G, the number a constant in each group: the
@@ -428,12 +457,10 @@ __global__ void __launch_bounds__(TPB) sm_vote_bits_kernel(const unsigned long l
       }
     }
 #pragma unroll
-    for (int r = 0; r < VB_PAIRS; ++r)
-#pragma unroll
-      for (int q = 0; q < VOTE_GROUP; ++q) {
-        planes_add<PLANES>(p0[r], a[r][q]);
-        planes_add<PLANES>(p1[r], b[r][q]);
-      }
+    for (int r = 0; r < VB_PAIRS; ++r) {
+      planes_add8<PLANES>(p0[r], a[r]);
+      planes_add8<PLANES>(p1[r], b[r]);
+    }
   }
   const unsigned T = (unsigned)((M + 1) / 2);  // vote = (count >= T)
   const bool out_vec = (reinterpret_cast<uintptr_t>(voted) & 15) == 0;
@@ -822,8 +849,7 @@ __global__ void __launch_bounds__(TPB) sm_vote_wide_kernel(const vote_g_args g) 
       x[q] = 0;
       if (in && pb + q < a.M) x[q] = __builtin_nontemporal_load(sbase + (long long)(pb + q) * stride_w);
     }
-#pragma unroll
-    for (int q = 0; q < VOTE_GROUP; ++q) planes_add<PLANES>(plane, x[q]);
+    planes_add8<PLANES>(plane, x);
   }
   const unsigned v = planes_ge<PLANES>(plane, (unsigned)((a.M + 1) / 2));
   int row = 0, live = 0;  // of the lane's own word

@@ -310,6 +310,26 @@ def test_vote_on_both_sides_of_the_lines_between_its_kernels(P, ctx, fmt, M, n):
                 assert torch.equal(v[:n].float(), vote) and bool((v[n:] == 9).all()), what
 
 
+@pytest.mark.parametrize("M", [255, 256, 257, 263, 264, 511, 513, 1031])
+@pytest.mark.parametrize("n", [1, 129, 64 * 37])
+def test_vote_bits_of_many_workers(P, ctx, M, n):
+    """Voted bits by carry-save addition of eight words (256 workers and more), every remainder of eight, counts around the
+    threshold and around powers of two."""
+    rng = wl.rng_for(71, block=M, worker=n)
+    S = rng.integers(0, 2, size=(M, n), dtype=np.uint8)
+    half = (M + 1) // 2
+    for i, k in enumerate([half, half - 1, 0, M, 128, 255, 256 if M > 255 else 254]):
+        if i < n:                                             # exactly k of M set in entry i
+            S[:, i] = 0
+            S[rng.permutation(M)[:min(k, M)], i] = 1
+    packed = np.stack([O.pack_bits(S[p]) for p in range(M)])
+    ref = O.pack_bits((2 * S.astype(np.int64).sum(axis=0) >= M).astype(np.uint8))
+    vb = torch.full((packed.shape[1] + 8,), 0x55, dtype=torch.uint8, device="cuda")
+    P.signmuon_majority_vote(ctx, dev(packed), "1bit", M, n, packed.shape[1], voted=vb, vfmt="bits")
+    got = vb.cpu().numpy()
+    assert np.array_equal(got[:-8], ref) and np.all(got[-8:] == 0x55)
+
+
 @pytest.mark.parametrize("sign_fmt", ["1bit", "int8"])
 @pytest.mark.parametrize("M,Kp", [(9, 0), (3, 0), (9, 1)])
 def test_step_votes_beyond_one_round_over_padded_rows(P, ctx, sign_fmt, M, Kp):
