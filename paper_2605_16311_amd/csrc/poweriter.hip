@@ -24,8 +24,8 @@ constexpr int SM_PI_STARTS = (SM_PI_MAX_GROUP + 15) / 16 * 16;
 struct pi_args {
   int n;
   float eps;
-  sm_starts<SM_PI_STARTS> begin;
   sm_pi_desc d[SM_PI_MAX_GROUP];
+  sm_starts<SM_PI_STARTS> begin;
 };
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -35,9 +35,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 __device__ __forceinline__ const sm_pi_desc& find_desc(const pi_args& a, int bx, int& local) {
-  const int di = sm_find(a.begin, a.n, bx);
-  local = bx - a.begin.v[di];
-  return a.d[di];
+  return a.d[sm_entry(a.begin, a.n, bx, local)];
 }
 
 // 8 bf16 (one 16-byte load) times 8 floats

@@ -138,16 +138,15 @@ __global__ void __launch_bounds__(TPB) sm_reduce_partials_kernel(const float* pa
 struct sigma_args {
   int n;
   float eps;
-  sm_starts<SM_SIGMA_MAX_GROUP> begin;
   sm_sigma_desc d[SM_SIGMA_MAX_GROUP];
+  sm_starts<SM_SIGMA_MAX_GROUP> begin;
 };
 
 // One workgroup per item of every class of the table.
 __global__ void __launch_bounds__(TPB) sm_sigma_group_kernel(const sigma_args a) {
   __shared__ float red[4];
-  const int di = sm_find(a.begin, a.n, blockIdx.x);
-  const sm_sigma_desc& D = a.d[di];
-  const int i = blockIdx.x - a.begin.v[di];
+  int i;
+  const sm_sigma_desc& D = a.d[sm_entry(a.begin, a.n, blockIdx.x, i)];
   if (D.mode == 0) {
     const float* src = D.partial + (long long)i * D.chunks;
     float s = 0.f;
