@@ -1222,8 +1222,9 @@ int sm_launch_vote_group(signmuon_ctx* ctx, const sm_vote_desc* descs, int n, in
     const bool wide8 = fmt == SM_SIGN_INT8 && whole && (votes_alone || (max_m >= 16 && entries >= 2 * one_round));
     const bool narrow = fmt == SM_SIGN_1BIT ? entries <= one_round || (counts && max_m < 32)
                                             : !wide8 && (max_m <= 8 || entries <= one_round || shortest < 16);
-    // Four groups per lane where few workers leave a lane few loads (int8, int8 votes + counts, 6.2 M entries, M = 1 / 4 /
-    // 6 / 8, one group 9.8 / 13.5 / 14.4 / 16.5 us, four 7.5 / 10.7 / 13.8 / 17.0).
+    // Four groups per lane where few workers leave a lane few loads.  int8, int8 votes + counts, one group / four, us:
+    // 6.2 M entries, M = 1 / 4 / 6 / 8: 9.8 / 7.5, 14.0 / 10.7, 14.4 / 13.9, 17.1 / 16.9; 12 M: 17.0 / 14.7, 25.6 / 22.0,
+    // 25.1 / 26.5, 29.1 / 30.9.  1 bit, counts, 6.2 M, M = 6 / 8: 8.7 / 7.5, 7.6 / 7.6.
     const bool few = narrow && max_m < 8 && entries > one_round;
     long long blocks = 0;
     for (int i = 0; i < g; ++i) {
