@@ -434,11 +434,12 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
   // The s x s matrices between the Gram and the apply are symmetric: only their 256 x 256 blocks on and
   // above the diagonal are written, and a product reads the other blocks as transposes of those
   // (a third fewer bytes to and from memory).  SM_NS_STORE_FULL writes and reads whole matrices.
-  // Launches small enough for three LDS stages write whole matrices too: they are not bound by bytes, and the
+  // Launches small enough for a ring of LDS stages write whole matrices too: they are not bound by bytes, and the
   // loop over one operand form is the shorter one.
   sm_tile_count tc;
   for (auto& cl : pl->classes) tc.add(cl.s, cl.s, cl.s, cl.count * mult, true);
-  const int ss = (ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL || sm_gemm_stages(ctx, tc) == 3) ? 0 : 3;
+  const bool ring = sm_gemm_stages(ctx, tc) > 2;
+  const int ss = (ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL || ring) ? 0 : 3;
   const bool chain = pairs && chain_serves(ctx, pl, mult);
   int done = 0;
   while (done < steps) {
@@ -462,16 +463,25 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
       P[0].scale = sc ? at<float>(ctx, cl.off_inv) : nullptr;
     });
     if (rc != SM_OK) return rc;
-    // products  Q_k X = b (A_k + (a / b) I) X  over half-precision s x s matrices
+    // products  Q_k X = b (A_k + (a / b) I) X  over half-precision s x s matrices; launches of few tiles as
+    // b X (A_k + (a / b) I), all of these being polynomials in A_0: they add (a / b) X in float32
     gemm_params qx;
     qx.alpha = b;
-    qx.a_diag = a / b;
+    (ring ? qx.b_diag : qx.a_diag) = a / b;
+    auto q_product = [&](ns_class& cl, sm_gemm_prob& P, const bf16_t* q, const bf16_t* x, bf16_t* c) {
+      small_product(cl, P, ring ? x : q, ring ? q : x, c, cl.count * mult);
+    };
     qx.in_f16 = qx.out_f16 = true;
     qx.sym_store = ss;
     // first product of P: P_2 = Q_1 Q_0 = b^2 (A_1 + (a / b) I) (A_0 + (a / b) I)
     gemm_params qq = qx;
     qq.alpha = b * b;
     qq.b_diag = a / b;
+    if (ring) {  // with a b A_0 as the added term
+      qq.gamma = a * b;
+      qq.diag = a * a;
+      qq.r_f16 = true;
+    }
     int p_final = -1;  // -1: P_1 = Q_0 (bf16, in off_q[0]); else index into off_p
     if (chain && kk >= 2) {
       rc = run_chain(ctx, pl, mult, kk, a, b);
@@ -549,8 +559,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
         lp.out_f16 = false;
         lp.sym_store = ss & 1;  // the apply reads P_K as a full matrix
         rc = launch_over_classes(ctx, pl, lp, 1, [&](ns_class& cl, sm_gemm_prob* P) {
-          small_product(cl, P[0], ab(cl, aw), at<bf16_t>(ctx, cl.off_p[pw]), at<bf16_t>(ctx, cl.off_p[pw ^ 1]),
-                        cl.count * mult);
+          q_product(cl, P[0], ab(cl, aw), at<bf16_t>(ctx, cl.off_p[pw]), at<bf16_t>(ctx, cl.off_p[pw ^ 1]));
         });
         if (rc != SM_OK) return rc;
         pw ^= 1;
@@ -562,22 +571,21 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
         auto ak = [&](ns_class& cl) { return k == 0 ? at<bf16_t>(ctx, cl.off_q[0]) : a_ptr(cl, ai); };
         const bool with_p = (k >= 2);
         rc = launch_over_classes(ctx, pl, qx, with_p ? 2 : 1, [&](ns_class& cl, sm_gemm_prob* P) {
-          small_product(cl, P[0], ak(cl), ak(cl), at<bf16_t>(ctx, cl.off_t), cl.count * mult);
-          if (with_p)
-            small_product(cl, P[1], ak(cl), at<bf16_t>(ctx, cl.off_p[pi]), at<bf16_t>(ctx, cl.off_p[pi ^ 1]),
-                          cl.count * mult);
+          q_product(cl, P[0], ak(cl), ak(cl), at<bf16_t>(ctx, cl.off_t));
+          if (with_p) q_product(cl, P[1], ak(cl), at<bf16_t>(ctx, cl.off_p[pi]), at<bf16_t>(ctx, cl.off_p[pi ^ 1]));
         });
         if (rc != SM_OK) return rc;
         if (with_p) pi ^= 1;
         if (k == 1) {  // P_2 from A_1 and A_0
           rc = launch_over_classes(ctx, pl, qq, 1, [&](ns_class& cl, sm_gemm_prob* P) {
             small_product(cl, P[0], ak(cl), at<bf16_t>(ctx, cl.off_q[0]), at<bf16_t>(ctx, cl.off_p[pi]), cl.count * mult);
+            if (ring) P[0].R = at<bf16_t>(ctx, cl.off_q[0]);
           });
           if (rc != SM_OK) return rc;
         }
         const int an = (k == 0) ? 0 : (ai ^ 1);
         rc = launch_over_classes(ctx, pl, qx, 1, [&](ns_class& cl, sm_gemm_prob* P) {
-          small_product(cl, P[0], ak(cl), at<bf16_t>(ctx, cl.off_t), a_ptr(cl, an), cl.count * mult);
+          q_product(cl, P[0], ak(cl), at<bf16_t>(ctx, cl.off_t), a_ptr(cl, an));
         });
         if (rc != SM_OK) return rc;
         ai = an;
@@ -588,6 +596,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
         lp.sym_store = ss & 1;  // the apply reads P_K as a full matrix
         rc = launch_over_classes(ctx, pl, lp, 1, [&](ns_class& cl, sm_gemm_prob* P) {
           small_product(cl, P[0], a_ptr(cl, ai), at<bf16_t>(ctx, cl.off_q[0]), at<bf16_t>(ctx, cl.off_p[0]), cl.count * mult);
+          if (ring) P[0].R = at<bf16_t>(ctx, cl.off_q[0]);
         });
         if (rc != SM_OK) return rc;
         p_final = 0;
@@ -596,8 +605,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
         lp.out_f16 = false;
         lp.sym_store = ss & 1;  // the apply reads P_K as a full matrix
         rc = launch_over_classes(ctx, pl, lp, 1, [&](ns_class& cl, sm_gemm_prob* P) {
-          small_product(cl, P[0], a_ptr(cl, ai), at<bf16_t>(ctx, cl.off_p[pi]), at<bf16_t>(ctx, cl.off_p[pi ^ 1]),
-                        cl.count * mult);
+          q_product(cl, P[0], a_ptr(cl, ai), at<bf16_t>(ctx, cl.off_p[pi]), at<bf16_t>(ctx, cl.off_p[pi ^ 1]));
         });
         if (rc != SM_OK) return rc;
         p_final = pi ^ 1;

@@ -291,7 +291,8 @@ struct sm_gemm_prob {
   int M, N, K;
   int lda, ldb, ldc;
   int batch;
-  int tiles_m, tiles_n;  // filled by the launcher
+  int tiles_m, tiles_n;  // filled by the launcher, like the next
+  sm_div by_item;        // by the tiles of a batch item (the mate's among them)
   int layout;            // bit 0: A stored [K][M] (lda = its row length), bit 1: B stored [K][N]
   // Optional sign output of a general (non-symmetric) bf16 product: the signs (x >= 0) of the
   // leading sign_rows x sign_ld part of C[b], packed row by row (sign_ld a multiple of 64) into
@@ -312,10 +313,10 @@ struct sm_gemm_prob {
 constexpr int SM_GEMM_MAX_PROB = 24;
 constexpr int SM_GEMM_STARTS = 32;
 struct sm_gemm_args {
-  sm_starts<SM_GEMM_STARTS> tile_begin;  // first tile of every problem; filled by the launcher
   int n_prob;
+  int per_xcd_wgs;   // workgroups per XCD; filled by the launcher, like the next two
+  int reverse;       // an XCD walks its range of the tile list from the end (every other launch)
   int total_tiles;
-  int xcd_begin[9];  // XCD x owns tiles [xcd_begin[x], xcd_begin[x + 1]) of the tile list
   int scale_pow;     // 0, 1 or 2
   float alpha, gamma, diag;
   float a_diag, b_diag;  // 0 = none
@@ -323,7 +324,8 @@ struct sm_gemm_args {
   int sym_store;     // bit 0: the operands hold valid data only in their 256 x 256 blocks on and above the diagonal
                      // (symmetric matrices; half precision, M == N == K); bit 1: write the output that way; bit 2:
                      // write the output as packed 32 x 32 blocks on and above the diagonal (ns_chain.hip)
-  int reverse;       // an XCD walks its range of the tile list from the end (set by the launcher: every other launch)
+  int xcd_begin[9];  // XCD x owns tiles [xcd_begin[x], xcd_begin[x + 1]) of the tile list
+  sm_starts<SM_GEMM_STARTS> tile_begin;  // first tile of every problem; filled by the launcher
   sm_gemm_prob p[SM_GEMM_MAX_PROB];
 };
 static_assert(sizeof(sm_gemm_args) <= 4096, "kernel arguments are limited to 4 KB");

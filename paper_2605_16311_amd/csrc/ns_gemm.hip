@@ -15,8 +15,8 @@
 // the packed signs of its result (Alg. 3's encoding) besides or instead of the result itself.
 //
 // Structure.  A workgroup of 8 waves (2 per SIMD) owns a TS x TS tile of C (TS = 256, or 128
-// for launches with little work; TS = 64 with four waves and three stages for launches of few
-// tiles, see SLICE_STEP3); each wave a (TS/2) x (TS/4) sub-tile held as accumulators of
+// for launches with little work; TS = 64 with four waves and a ring of stages for launches of few
+// tiles, see RING_STEP); each wave a (TS/2) x (TS/4) sub-tile held as accumulators of
 // v_mfma_f32_32x32x16_bf16 (or _f16).  K advances in slices of 64 (four MFMA k-steps), so that every
 // global->LDS request covers a whole 128-byte line of a K-contiguous operand: the per-CU
 // L2 -> LDS path is limited by the number of outstanding requests, not by bytes.
@@ -41,6 +41,9 @@
 //       column i of the 4 x 16 block whose rows the group's lanes address.
 // The global->LDS load writes its 64 lanes in order, so each lane fetches the chunk that
 // belongs in its slot.
+//
+// With a ring of stages the added terms (db A of a shift, gamma R) join the accumulators in float32 and are
+// rounded with them; with two stages the shift is made in LDS and R is added to the rounded product.
 //
 // Symmetric outputs: only tiles with tile_m <= tile_n are computed; off-diagonal tiles are
 // also stored mirrored (from the same staged copy, with transposing LDS reads).
@@ -163,20 +166,49 @@ __device__ __forceinline__ void unpack2(unsigned w, bool f16, float& lo, float& 
   }
 }
 
+// A lane's entries of a tile, as its accumulators are: four groups of four columns per fragment.
+template <int FM, int FN>
+struct tile_term {
+  u32x2 v[FM][FN][4];
+  // from a K-contiguous slice in LDS; at: byte offset of group 0 of fragment (0, 0) (one fragment across: FN == 1)
+  __device__ __forceinline__ void fetch(const unsigned char* st, int at) {
+    static_assert(FN == 1, "");
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int vg = 0; vg < 4; ++vg) v[i][0][vg] = *reinterpret_cast<const u32x2*>(st + i * 32 * (BK * 2) + (at ^ (vg << 4)));
+  }
+  __device__ __forceinline__ void add_to(f32x16 (&acc)[FM][FN], float c, bool f16) const {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int jn = 0; jn < FN; ++jn)
+#pragma unroll
+        for (int vg = 0; vg < 4; ++vg)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            float lo, hi;
+            unpack2(v[i][jn][vg][q], f16, lo, hi);
+            acc[i][jn][4 * vg + 2 * q] = fmaf(c, lo, acc[i][jn][4 * vg + 2 * q]);
+            acc[i][jn][4 * vg + 2 * q + 1] = fmaf(c, hi, acc[i][jn][4 * vg + 2 * q + 1]);
+          }
+  }
+};
+
 // x >= 0 for a bf16 bit pattern (IEEE comparison: -0 counts as >= 0, NaN does not)
 __device__ __forceinline__ unsigned ge0_bf16(unsigned h) {
   const unsigned mag = h & 0x7FFFu;
   return (mag == 0u) | (((h >> 15) == 0u) & (mag <= 0x7F80u));
 }
 
-// One TS x TS tile of one problem.  The four stage arrays are the kernel's own __shared__
+// One TS x TS tile of one problem.  The stage arrays (an A slice, then a B slice) are the kernel's own __shared__
 // variables, passed by reference so that every access keeps its identity after inlining.
+#define STAGE_PARAMS(SIZE)                                                                                             \
+  unsigned char(&S0)[SIZE(0)], unsigned char(&S1)[SIZE(1)], unsigned char(&S2)[SIZE(2)], unsigned char(&S3)[SIZE(3)]
+#define STAGE_SIZE(i) ST > i ? TS * 256 : 16
 template <int TS, int ST, bool A_MN, bool B_MN, bool SYM, bool F16, bool SYMSTORE = false>
 __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gemm_prob& P, int b, int tm, int tn,
-                                          unsigned char (&sA0)[TS * 128], unsigned char (&sA1)[TS * 128],
-                                          unsigned char (&sB0)[TS * 128], unsigned char (&sB1)[TS * 128],
-                                          unsigned char (&sA2)[ST > 2 ? TS * 128 : 16],
-                                          unsigned char (&sB2)[ST > 2 ? TS * 128 : 16]) {
+                                          STAGE_PARAMS(STAGE_SIZE)) {
   using shape = tile_shape<TS>;
   constexpr int NTH = shape::NTH, WM = shape::WM, WN = shape::WN, FM = shape::FM, FN = shape::FN, NLOAD = shape::NLOAD;
   const int m0 = tm * TS, n0 = tn * TS;
@@ -195,9 +227,9 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   const int w_m = wv & 1, w_n = wv >> 1;
 
   // ---- global -> LDS: TS/8 wave-loads per operand slice; this wave issues NLOAD of A and of B.
-  // Buffer loads: the per-lane byte offset is fixed for the whole K walk, the slice offset is scalar.
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, 0x7FFFFFFF, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(B), 0, 0x7FFFFFFF, 0x00020000);
+  // Buffer loads: the per-lane byte offset is fixed for the whole K walk, the slice offset is scalar.  Every step issues
+  // a slice, so that the number of loads in flight is the same in all of them; past the end the buffer has no records
+  // and the loads are dropped.
   operand_lane<A_MN, TS> oa;
   operand_lane<B_MN, TS> ob;
   oa.init(lane, wv, m0, M, P.lda, w_m * WM);
@@ -211,17 +243,21 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     vb[q] = ob.voff[q];
   }
   const int ksa = __builtin_amdgcn_readfirstlane(oa.kstep), ksb = __builtin_amdgcn_readfirstlane(ob.kstep);
-#define ISSUE_V(sa, sb, slice, VA, KSA, VB, KSB)                                                                     \
+#define ISSUE_V(st, slice, VA, KSA, VB, KSB)                                                                          \
   {                                                                                                                   \
+    const int records = (slice) < nk ? 0x7FFFFFFF : 0;                                                                \
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, records, 0x00020000); \
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(B), 0, records, 0x00020000); \
     _Pragma("unroll") for (int q = 0; q < NLOAD; ++q) {                                                               \
       const int voa = VA[q], vob = VB[q];                                                                             \
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, LDS_PTR((sa) + (NLOAD * wv + q) * 1024), 16, voa, (slice) * (KSA), \
-                                               0, 0);                                                                 \
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, LDS_PTR((sb) + (NLOAD * wv + q) * 1024), 16, vob, (slice) * (KSB), \
-                                               0, 0);                                                                 \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, LDS_PTR((st) + (NLOAD * wv + q) * 1024), 16, voa,                  \
+                                               (int)((unsigned)(slice) * (unsigned)(KSA)), 0, 0);                     \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, LDS_PTR((st) + TS * 128 + (NLOAD * wv + q) * 1024), 16, vob,       \
+                                               (int)((unsigned)(slice) * (unsigned)(KSB)), 0, 0);                     \
     }                                                                                                                 \
   }
-#define ISSUE(sa, sb, slice) ISSUE_V(sa, sb, slice, va, ksa, vb, ksb)
+#define ISSUE(st, slice) ISSUE_V(st, slice, va, ksa, vb, ksb)
+  const int nk = K / BK;
 
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -233,20 +269,21 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
 
   // two fragment sets: while the matrix pipe works through one, the LDS reads of the other are in flight
   bf16x8 fa[2][FM], fb[2][FN];
-#define FETCH_L(set, sa, sb, ks, LA, LB)                                                \
-  {                                                                                     \
-    _Pragma("unroll") for (int i = 0; i < FM; ++i) fa[set][i] = LA.fetch(sa, i, ks);    \
-    _Pragma("unroll") for (int j = 0; j < FN; ++j) fb[set][j] = LB.fetch(sb, j, ks);    \
+#define FETCH_L(set, st, ks, LA, LB)                                                          \
+  {                                                                                           \
+    _Pragma("unroll") for (int i = 0; i < FM; ++i) fa[set][i] = LA.fetch(st, i, ks);          \
+    _Pragma("unroll") for (int j = 0; j < FN; ++j) fb[set][j] = LB.fetch((st) + TS * 128, j, ks); \
   }
-#define FETCH(set, sa, sb, ks) FETCH_L(set, sa, sb, ks, oa, ob)
-#define MMA(set)                                                                                                \
+#define FETCH(set, st, ks) FETCH_L(set, st, ks, oa, ob)
+#define MMA(set) MMA_OF(fa[set], fb[set])
+#define MMA_OF(fa, fb)                                                                                          \
   {                                                                                                             \
     _Pragma("unroll") for (int i = 0; i < FM; ++i) _Pragma("unroll") for (int j = 0; j < FN; ++j) {             \
       if (F16)                                                                                                  \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[set][j]),               \
-                                                           __builtin_bit_cast(f16x8, fa[set][i]), acc[i][j], 0, 0, 0); \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fb[j]),               \
+                                                           __builtin_bit_cast(f16x8, fa[i]), acc[i][j], 0, 0, 0); \
       else                                                                                                      \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);        \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);        \
     }                                                                                                           \
   }
 #define SB() __builtin_amdgcn_sched_barrier(0)
@@ -257,30 +294,30 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     __builtin_amdgcn_s_barrier();                 \
     asm volatile("" ::: "memory");                \
   }
-  // Slice j sits in (ca, cb); slice j + 1 goes to (na, nb).  On entry fragment set 1 holds k-step 3
+  // Slice j sits in stage cur; slice j + 1 goes to stage nxt.  On entry fragment set 1 holds k-step 3
   // of the previous slice (garbage-free zeros for the first slice: see below).
-#define SLICE_STEP(ca, cb, na, nb, first)                                 \
+#define SLICE_STEP(cur, nxt, first)                                       \
   {                                                                       \
-    ISSUE(na, nb, min(j + 1, nk - 1));                                    \
-    FETCH(0, ca, cb, 0);                                                  \
+    ISSUE(nxt, j + 1);                                                    \
+    FETCH(0, cur, 0);                                                     \
     SB();                                                                 \
     if (!(first)) MMA(1);                                                 \
     SB();                                                                 \
-    FETCH(1, ca, cb, 1);                                                  \
+    FETCH(1, cur, 1);                                                     \
     SB();                                                                 \
     MMA(0);                                                               \
     SB();                                                                 \
-    FETCH(0, ca, cb, 2);                                                  \
+    FETCH(0, cur, 2);                                                     \
     SB();                                                                 \
     MMA(1);                                                               \
     SB();                                                                 \
-    FETCH(1, ca, cb, 3);                                                  \
+    FETCH(1, cur, 3);                                                     \
     SB();                                                                 \
     MMA(0);                                                               \
     SB();                                                                 \
     SYNC();                                                               \
     ++j;                                                                  \
-    if (j < nk) SHIFT_DIAG(na, nb, j);                                    \
+    if (j < nk) SHIFT_DIAG(nxt, j);                                       \
   }
 
   // Optional identity shift of the operands, opA + a_diag I and opB + b_diag I (half precision,
@@ -289,84 +326,145 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   // after the slice has landed and before any fragment of it is read.
   const _Float16 dga = (_Float16)args.a_diag, dgb = (_Float16)args.b_diag;
   const bool dg_a = F16 && args.a_diag != 0.f, dg_b = F16 && args.b_diag != 0.f;
-#define SHIFT_DIAG(sa, sb, slice)                                                                      \
+#define SHIFT_DIAG(st, slice)                                                                           \
   if (F16 && (dg_a || dg_b)) {                                                                         \
     const int ra = (slice) * BK - m0, rb = (slice) * BK - n0; /* tile row of the slice's first k */   \
     const bool ha = dg_a && ra >= 0 && ra < TS, hb = dg_b && rb >= 0 && rb < TS;                       \
     if (ha || hb) {                                                                                    \
       if (wv == 0 && ha) {                                                                             \
         const int r = ra + lane;                                                                       \
-        _Float16* e = reinterpret_cast<_Float16*>((sa) + r * (BK * 2) + (((lane >> 3) ^ ((r >> 1) & 7)) << 4)) + (lane & 7); \
+        _Float16* e = reinterpret_cast<_Float16*>((st) + r * (BK * 2) + (((lane >> 3) ^ ((r >> 1) & 7)) << 4)) + (lane & 7); \
         *e = (_Float16)(*e + dga);                                                                     \
       }                                                                                                \
       if (wv == 1 && hb) {                                                                             \
         const int r = rb + lane;                                                                       \
-        _Float16* e = reinterpret_cast<_Float16*>((sb) + r * (BK * 2) + (((lane >> 3) ^ ((r >> 1) & 7)) << 4)) + (lane & 7); \
+        _Float16* e = reinterpret_cast<_Float16*>((st) + TS * 128 + r * (BK * 2) + (((lane >> 3) ^ ((r >> 1) & 7)) << 4)) + (lane & 7); \
         *e = (_Float16)(*e + dgb);                                                                     \
       }                                                                                                \
       __syncthreads();                                                                                 \
     }                                                                                                  \
   }
-  const int nk = K / BK;
   int j = 0;
-  if constexpr (ST == 3) {
-    // Three stages, slices requested two ahead: a launch that gets them (sm_gemm_stages) has few tiles, so a slice's
-    // latency is not hidden by other workgroups.  The wait before slice j leaves slice j + 1 in flight.
-    static_assert(!SYMSTORE && NLOAD * 2 < 16, "");
-#define SLICE_STEP3(ca, cb, na, nb)                                       \
-  {                                                                       \
-    asm volatile("" ::: "memory");                                        \
-    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * NLOAD));                     \
-    __builtin_amdgcn_s_barrier();                                         \
-    asm volatile("" ::: "memory");                                        \
-    SHIFT_DIAG(ca, cb, j);                                                \
-    ISSUE(na, nb, min(j + 2, nk - 1));                                    \
-    FETCH(0, ca, cb, 0);                                                  \
-    SB();                                                                 \
-    MMA(1);                                                               \
-    SB();                                                                 \
-    FETCH(1, ca, cb, 1);                                                  \
-    SB();                                                                 \
-    MMA(0);                                                               \
-    SB();                                                                 \
-    FETCH(0, ca, cb, 2);                                                  \
-    SB();                                                                 \
-    MMA(1);                                                               \
-    SB();                                                                 \
-    FETCH(1, ca, cb, 3);                                                  \
-    SB();                                                                 \
-    MMA(0);                                                               \
-    SB();                                                                 \
-    ++j;                                                                  \
+  // With a ring, what is added to the product, A (B + db I) = A B + db A and gamma R, is added to its sums in float32:
+  // a shift in LDS would cost every product a barrier or two more.  The tile's part of A passes by in the K loop, as the
+  // slices of A from first_n on; those of R follow the last slice.
+  tile_term<FM, (ST > 2 ? FN : 1)> of_a, of_r;
+  const int first_n = n0 / BK, tile_slices = TS / BK;
+  const bool with_a = ST > 2 && F16 && args.b_diag != 0.f, with_r = ST > 2 && F16 && P.R;
+  if constexpr (ST > 2) {
+    const int own_n = w_n * WN;  // tile column of the lane's first group, but for its half of eight
+    const int own_slice = own_n / BK, own_row = w_m * WM + (lane & 31);
+    const int own = own_row * (BK * 2) + ((((own_n % BK) >> 3) ^ ((own_row >> 1) & 7)) << 4) + (lane >> 5) * 8;
+    // A ring of ST stages, slices requested ST - 1 ahead, for launches of few tiles: there is no second workgroup to hide
+    // what a wave waits for.  So the fragments of two k-steps are fetched at once, while those of the two before are
+    // multiplied: with one k-step at a time every k-step waited for the LDS.
+    static_assert(!SYMSTORE && ST <= 4, "");
+    constexpr int LEFT = (ST - 2) * 2 * NLOAD;  // loads in flight behind the slice that a step waits for
+    static_assert(LEFT < 16, "the low four bits of vmcnt");
+    bf16x8 wa[2][2][FM], wb[2][2][FN];
+#define FETCH2(set, st)                                                                                               \
+  _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                                     \
+    _Pragma("unroll") for (int i = 0; i < FM; ++i) wa[set][h][i] = oa.fetch(st, i, 2 * (set) + h);                    \
+    _Pragma("unroll") for (int n = 0; n < FN; ++n) wb[set][h][n] = ob.fetch((st) + TS * 128, n, 2 * (set) + h);       \
   }
-    // fragment set 1 starts as zeros, so the first step can run its "previous k-step" like any other
+#define MMA2(set)                  \
+  MMA_OF(wa[set][0], wb[set][0]); \
+  MMA_OF(wa[set][1], wb[set][1])
+    // Past the last slice of A come those of the tile's part of R, rows as long as A's; chosen by scalars, not by a
+    // branch, for the same reason that no step goes without loads.
+    const bf16_t* const Rb = with_r ? uniform_ptr(P.R + (long long)b * P.sC) : A;
+#define ISSUE_RING(st, slice)                                                                                         \
+  {                                                                                                                   \
+    const int sl = (slice), in_r = with_r && sl >= nk ? first_n + sl - nk : -1;                                       \
+    const bool dead_a = in_r >= 0 ? sl - nk >= tile_slices || in_r >= nk : sl >= nk;                                  \
+    const bf16_t* const Ab = uniform_ptr(in_r >= 0 ? Rb : A);                                                         \
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Ab), 0, __builtin_amdgcn_readfirstlane(dead_a ? 0 : 0x7FFFFFFF), 0x00020000); \
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(B), 0, sl >= nk ? 0 : 0x7FFFFFFF, 0x00020000); \
+    const int oa_s = (int)((unsigned)__builtin_amdgcn_readfirstlane(in_r >= 0 ? in_r : sl) * (unsigned)ksa);          \
+    const int ob_s = (int)((unsigned)sl * (unsigned)ksb);                                                             \
+    _Pragma("unroll") for (int q = 0; q < NLOAD; ++q) {                                                               \
+      const int voa = va[q], vob = vb[q];                                                                             \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, LDS_PTR((st) + (NLOAD * wv + q) * 1024), 16, voa, oa_s, 0, 0); \
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, LDS_PTR((st) + TS * 128 + (NLOAD * wv + q) * 1024), 16, vob, ob_s, 0, 0); \
+    }                                                                                                                 \
+  }
+#define RING_STEP(cur, nxt)                     \
+  {                                             \
+    asm volatile("" ::: "memory");              \
+    __builtin_amdgcn_s_waitcnt(0x0070 | LEFT);  \
+    __builtin_amdgcn_s_barrier();               \
+    asm volatile("" ::: "memory");              \
+    ISSUE_RING(nxt, j + ST - 1);                \
+    if (with_a && j == first_n + own_slice) of_a.fetch(cur, own); \
+    FETCH2(0, cur);                             \
+    SB();                                       \
+    MMA2(1);                                    \
+    SB();                                       \
+    FETCH2(1, cur);                             \
+    SB();                                       \
+    MMA2(0);                                    \
+    SB();                                       \
+    ++j;                                        \
+  }
+    auto ring = [&](auto at) -> unsigned char* {
+      constexpr int I = decltype(at)::value % ST;
+      if constexpr (I == 0) return S0;
+      else if constexpr (I == 1) return S1;
+      else if constexpr (I == 2) return S2;
+      else return S3;
+    };
+#define RING(i) ring(std::integral_constant<int, (i)>())
+    // the second set starts as zeros, so the first step can multiply like any other
 #pragma unroll
-    for (int i = 0; i < FM; ++i) fa[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < FN; ++i) fb[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    ISSUE(sA0, sB0, 0);
-    ISSUE(sA1, sB1, min(1, nk - 1));
-    while (j + 3 <= nk) {
-      SLICE_STEP3(sA0, sB0, sA2, sB2);
-      SLICE_STEP3(sA1, sB1, sA0, sB0);
-      SLICE_STEP3(sA2, sB2, sA1, sB1);
+      for (int i = 0; i < FM; ++i) wa[1][h][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int n = 0; n < FN; ++n) wb[1][h][n] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
     }
-    if (j < nk) SLICE_STEP3(sA0, sB0, sA2, sB2);
-    if (j < nk) SLICE_STEP3(sA1, sB1, sA0, sB0);
-    SYNC();  // every wave has its last fragments and the requests past the end have landed: the stages are free
-#undef SLICE_STEP3
+    ISSUE(S0, 0);
+    ISSUE_RING(S1, 1);
+    if constexpr (ST > 3) ISSUE_RING(S2, 2);
+    while (j + ST <= nk) {
+      RING_STEP(RING(0), RING(ST - 1));
+      RING_STEP(RING(1), RING(0));
+      RING_STEP(RING(2), RING(1));
+      if constexpr (ST > 3) RING_STEP(RING(3), RING(2));
+    }
+    // the rest; jumps, so that the compiler, too, knows how many loads are in flight at each step
+    if (j >= nk) goto ring_end;
+    RING_STEP(RING(0), RING(ST - 1));
+    if (j >= nk) goto ring_end;
+    RING_STEP(RING(1), RING(0));
+    if constexpr (ST > 3) {
+      if (j >= nk) goto ring_end;
+      RING_STEP(RING(2), RING(1));
+    }
+  ring_end:
+    SYNC();  // every wave has its last fragments: the stages are free, but for R
+    MMA2(1);
+    if (with_r) {  // slice r of R is in the stage of slice nk + r
+      const int at = (nk + own_slice) % ST;
+      unsigned char* const last = ST > 3 ? &S3[0] : &S2[0];
+      of_r.fetch(at == 0 ? S0 : at == 1 ? S1 : at == 2 ? S2 : last, own);
+      __syncthreads();
+    }
+#undef ISSUE_RING
+#undef RING
+#undef RING_STEP
+#undef MMA2
+#undef FETCH2
   } else if constexpr (!SYMSTORE) {
-    ISSUE(sA0, sB0, 0);
+    ISSUE(S0, 0);
     SYNC();
-    SHIFT_DIAG(sA0, sB0, 0);
+    SHIFT_DIAG(S0, 0);
     // first slice: no pending k-step from a previous slice
-    SLICE_STEP(sA0, sB0, sA1, sB1, true);
-    // Past the end the issue re-reads the last slice (never consumed), so every step has the same shape.
+    SLICE_STEP(S0, S1, true);
     while (j + 1 < nk) {
-      SLICE_STEP(sA1, sB1, sA0, sB0, false);
-      SLICE_STEP(sA0, sB0, sA1, sB1, false);
+      SLICE_STEP(S1, S0, false);
+      SLICE_STEP(S0, S1, false);
     }
-    if (j < nk) SLICE_STEP(sA1, sB1, sA0, sB0, false);
+    if (j < nk) SLICE_STEP(S1, S0, false);
   } else {
     // Operands are symmetric matrices of which only the 256 x 256 blocks on and above the diagonal
     // hold valid data (M == N == K).  Block (r, c) with r > c is read as the transpose of block
@@ -391,73 +489,71 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     for (int i = 0; i < FM; ++i) fa[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < FN; ++i) fb[1][i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#define ISSUE_MM(sa, sb, slice) ISSUE_V(sa, sb, slice, vam, ksam, vbm, ksbm)
-#define ISSUE_KM(sa, sb, slice) ISSUE_V(sa, sb, slice, va, ksa, vbm, ksbm)
-#define ISSUE_KK(sa, sb, slice) ISSUE_V(sa, sb, slice, va, ksa, vb, ksb)
-#define ISSUE_KKC(sa, sb, slice) ISSUE_KK(sa, sb, min((slice), nk - 1))
-#define ISSUE_AT(sa, sb, slice)                  \
+#define ISSUE_MM(st, slice) ISSUE_V(st, slice, vam, ksam, vbm, ksbm)
+#define ISSUE_KM(st, slice) ISSUE_V(st, slice, va, ksa, vbm, ksbm)
+#define ISSUE_KK(st, slice) ISSUE_V(st, slice, va, ksa, vb, ksb)
+#define ISSUE_AT(st, slice)                      \
   {                                              \
     if ((slice) < J1) {                          \
-      ISSUE_MM(sa, sb, slice);                   \
+      ISSUE_MM(st, slice);                       \
     } else if ((slice) < J2) {                   \
-      ISSUE_KM(sa, sb, slice);                   \
+      ISSUE_KM(st, slice);                       \
     } else {                                     \
-      ISSUE_KK(sa, sb, min((slice), nk - 1));    \
+      ISSUE_KK(st, slice);                       \
     }                                            \
   }
-#define STEP3(ca, cb, na, nb, LA, LB, ISSUE_NEXT)                         \
+#define STEP3(cur, nxt, LA, LB, ISSUE_NEXT)                               \
   {                                                                       \
-    ISSUE_NEXT(na, nb, j + 1);                                            \
-    FETCH_L(0, ca, cb, 0, LA, LB);                                        \
+    ISSUE_NEXT(nxt, j + 1);                                               \
+    FETCH_L(0, cur, 0, LA, LB);                                           \
     SB();                                                                 \
     MMA(1);                                                               \
     SB();                                                                 \
-    FETCH_L(1, ca, cb, 1, LA, LB);                                        \
+    FETCH_L(1, cur, 1, LA, LB);                                           \
     SB();                                                                 \
     MMA(0);                                                               \
     SB();                                                                 \
-    FETCH_L(0, ca, cb, 2, LA, LB);                                        \
+    FETCH_L(0, cur, 2, LA, LB);                                           \
     SB();                                                                 \
     MMA(1);                                                               \
     SB();                                                                 \
-    FETCH_L(1, ca, cb, 3, LA, LB);                                        \
+    FETCH_L(1, cur, 3, LA, LB);                                           \
     SB();                                                                 \
     MMA(0);                                                               \
     SB();                                                                 \
     SYNC();                                                               \
     ++j;                                                                  \
-    if (j < nk) SHIFT_DIAG(na, nb, j);                                    \
+    if (j < nk) SHIFT_DIAG(nxt, j);                                       \
   }
 #define PHASE3(LA, LB, ISSUE_SAME, jend)                                  \
   if (j < (jend)) {                                                       \
     while (j + 2 < (jend)) {                                              \
-      STEP3(sA0, sB0, sA1, sB1, LA, LB, ISSUE_SAME);                      \
-      STEP3(sA1, sB1, sA0, sB0, LA, LB, ISSUE_SAME);                      \
+      STEP3(S0, S1, LA, LB, ISSUE_SAME);                                  \
+      STEP3(S1, S0, LA, LB, ISSUE_SAME);                                  \
     }                                                                     \
-    STEP3(sA0, sB0, sA1, sB1, LA, LB, ISSUE_SAME);                        \
-    STEP3(sA1, sB1, sA0, sB0, LA, LB, ISSUE_AT);                          \
+    STEP3(S0, S1, LA, LB, ISSUE_SAME);                                    \
+    STEP3(S1, S0, LA, LB, ISSUE_AT);                                      \
   }
-    ISSUE_AT(sA0, sB0, 0);
+    ISSUE_AT(S0, 0);
     SYNC();
-    SHIFT_DIAG(sA0, sB0, 0);
+    SHIFT_DIAG(S0, 0);
     PHASE3(ma, mb, ISSUE_MM, J1);
     PHASE3(oa, mb, ISSUE_KM, J2);
-    // last phase: any number of slices; past the end the issue re-reads the last slice (never consumed)
-    STEP3(sA0, sB0, sA1, sB1, oa, ob, ISSUE_KKC);
+    // last phase: any number of slices
+    STEP3(S0, S1, oa, ob, ISSUE_KK);
     while (j + 1 < nk) {
-      STEP3(sA1, sB1, sA0, sB0, oa, ob, ISSUE_KKC);
-      STEP3(sA0, sB0, sA1, sB1, oa, ob, ISSUE_KKC);
+      STEP3(S1, S0, oa, ob, ISSUE_KK);
+      STEP3(S0, S1, oa, ob, ISSUE_KK);
     }
-    if (j < nk) STEP3(sA1, sB1, sA0, sB0, oa, ob, ISSUE_KKC);
+    if (j < nk) STEP3(S1, S0, oa, ob, ISSUE_KK);
 #undef PHASE3
 #undef STEP3
 #undef ISSUE_AT
-#undef ISSUE_KKC
 #undef ISSUE_KK
 #undef ISSUE_KM
 #undef ISSUE_MM
   }
-  MMA(1);  // k-step 3 of the last slice
+  if constexpr (ST == 2) MMA(1);  // k-step 3 of the last slice
 #undef SLICE_STEP
 #undef SHIFT_DIAG
 #undef SYNC
@@ -465,6 +561,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
 #undef FETCH
 #undef FETCH_L
 #undef MMA
+#undef MMA_OF
 #undef ISSUE
 #undef ISSUE_V
 
@@ -474,7 +571,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     s = P.scale[b];
     if (args.scale_pow == 2) s *= s;
   }
-  const float alpha = args.alpha * s;
+  float alpha = args.alpha * s;
   const bool of16 = args.out_f16 != 0;
   bf16_t* __restrict__ C = P.C ? P.C + (long long)b * P.sC : nullptr;
   // a fresh opaque thread id: the store addresses are worked out here, after the K loop,
@@ -484,6 +581,20 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   const int elane = etid & 63, ewv = __builtin_amdgcn_readfirstlane(etid >> 6);  // wave-uniform
   const int e_m = ewv & 1, e_n = ewv >> 1;
   const int fr = elane & 31, fg = elane >> 5;
+  if constexpr (ST > 2 && F16) {
+    // the added terms: one rounding
+    if (with_a || with_r) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int jn = 0; jn < FN; ++jn)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][jn][v] *= alpha;
+      if (with_a) of_a.add_to(acc, alpha * args.b_diag, true);
+      if (with_r) of_r.add_to(acc, args.gamma, true);
+      alpha = 1.f;
+    }
+  }
   if constexpr (!SYM) {
     // Only the packed 1-bit signs of the tile are wanted (the apply before the vote): they are taken
     // straight from the accumulators.  A lane holds, per 32 x 32 fragment, 16 entries of one row:
@@ -542,14 +653,14 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   // upper-only output (sym_store bit 1): the mirrored tile is written only inside a diagonal 256 x 256 block
   const bool packed = SYM && !F16 && (args.sym_store & 4);
   const bool mirror = SYM && (tm != tn) && !packed && (!(args.sym_store & 2) || (m0 / 256 == n0 / 256));
-  // The tile leaves through LDS so that every global store is a 16-byte piece of a row.  The four
-  // stage arrays (the first one at TS = 64) hold 64 tile rows each (rows of TS * 2 bytes, 16-byte chunk c of row r at slot
-  // c ^ (r & (CPR - 1))).  The tile is staged once; it is read out row by row for C and, for an
+  // The tile leaves through LDS so that every global store is a 16-byte piece of a row.  The first two
+  // stages (the first one at TS <= 128) hold the tile's rows (of TS * 2 bytes, 16-byte chunk c of row r at slot
+  // c ^ (r & (CPR - 1))), 64 rows per call of stage().  The tile is staged once; it is read out row by row for C and, for an
   // off-diagonal tile of a symmetric output, once more column by column (transposing LDS reads)
   // for the mirrored tile.  The R term (a symmetric matrix when the output is) is added at
   // read-out, on the rounded product, with loads shaped like the stores.
   constexpr int RB = TS * 2, CPR = TS / 8, RPP = NTH / CPR, PASSES = TS / RPP;
-  const bf16_t* __restrict__ R = P.R ? P.R + (long long)b * P.sC : nullptr;
+  const bf16_t* __restrict__ R = (ST == 2 && P.R) ? P.R + (long long)b * P.sC : nullptr;  // (added above otherwise)
   const bool rf16 = args.r_f16 != 0;
   const float gamma = args.gamma;
   // 8 staged outputs + gamma times 8 elements of R, rounded again.  When both are half precision and
@@ -575,7 +686,7 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     }
     return w;
   };
-  auto stage = [&](int idx) -> unsigned char* { return idx == 0 ? sA0 : idx == 1 ? sA1 : idx == 2 ? sB0 : sB1; };
+  auto stage = [&](int idx) -> unsigned char* { return idx < 2 ? S0 + idx * 64 * RB : S1 + (idx - 2) * 64 * RB; };
   // the staging loop in four forms: with or without the check for diagonal entries (only tiles that
   // meet the diagonal of a product with a diag term need it) and for either output type, so that
   // neither costs vector instructions per entry where it does not apply
@@ -664,9 +775,9 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     }
   }
   if (!SYM && P.sign_out) {
-    // packed signs of the tile: NTH / TS threads per tile row, each turning CPT consecutive columns
+    // packed signs of the tile: TPR threads per tile row, each turning CPT consecutive columns
     // of the staged row into CPT / 8 bytes (1 bit) or CPT bytes (int8)
-    constexpr int TPR = (TS == 64) ? 2 : NTH / TS, CPT = TS / TPR, NCH = CPT / 8;  // TS = 64: half of the threads
+    constexpr int TPR = NTH / TS < TS / 32 ? NTH / TS : TS / 32, CPT = TS / TPR, NCH = CPT / 8;  // at least a word each
     const int row = etid / TPR, part = etid % TPR;
     const int gr = m0 + row, gc0 = n0 + part * CPT;
     const unsigned char* sp = stage(row >> 6) + (row & 63) * RB;
@@ -794,10 +905,9 @@ __host__ __device__ __forceinline__ void tile_of(int t, int tiles_m, int tiles_n
 template <int KIND, int TS, int ST>
 __global__ void __launch_bounds__(tile_shape<TS>::NTH) sm_ns_gemm_kernel(const sm_gemm_args args) {
   constexpr bool SYM = (KIND != 1);
-  __shared__ __attribute__((aligned(1024))) unsigned char sA0[TS * 128], sA1[TS * 128];
-  __shared__ __attribute__((aligned(1024))) unsigned char sB0[TS * 128], sB1[TS * 128];
-  constexpr int THIRD = ST > 2 ? TS * 128 : 16;
-  __shared__ __attribute__((aligned(1024))) unsigned char sA2[THIRD], sB2[THIRD];
+  __shared__ __attribute__((aligned(1024))) unsigned char S0[STAGE_SIZE(0)], S1[STAGE_SIZE(1)], S2[STAGE_SIZE(2)],
+      S3[STAGE_SIZE(3)];
+#define STAGES S0, S1, S2, S3
 
   // Persistent workgroups: the grid is one (TS = 256, or 128 with three stages), two (128) or three
   // (64) workgroups per CU and each walks a list of tiles, so the global stores of one tile drain while the next tile is loaded
@@ -805,44 +915,58 @@ __global__ void __launch_bounds__(tile_shape<TS>::NTH) sm_ns_gemm_kernel(const s
   // range of the tile list (ranges of equal estimated cost) and its workgroups take neighbouring
   // tiles at any one time, so tiles that share operand panels share an L2.
   const int wg = blockIdx.x;
-  const int per_xcd_wgs = gridDim.x >> 3;
+  const int per_xcd_wgs = args.per_xcd_wgs, n_prob = args.n_prob, reverse = args.reverse;
   const int xcd_first = args.xcd_begin[wg & 7], xcd_end = args.xcd_begin[(wg & 7) + 1];
+  if constexpr (ST > 2) {
+    // A launch of few tiles waits for its arguments, line by line (half a microsecond each where one is asked for after
+    // the other): the lines that the first tile is likely to need are all requested here.
+    const int l0 = args.tile_begin.v[0], l1 = args.tile_begin.v[16], l2 = args.p[0].K, l3 = args.p[0].mate;
+    const void *l4 = args.p[0].A, *l5 = args.p[0].C;
+    asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3), "s"(l4), "s"(l5), "s"(xcd_first), "s"(n_prob));
+  }
   bool first_tile = true;
   for (int Lf = xcd_first + (wg >> 3); Lf < xcd_end; Lf += per_xcd_wgs) {
     // every other launch goes through the range backwards: it starts with the matrices the launch before it
     // wrote last, which are the ones still in the caches
-    const int L = args.reverse ? xcd_first + xcd_end - 1 - Lf : Lf;
+    const int L = reverse ? xcd_first + xcd_end - 1 - Lf : Lf;
     if (!first_tile) __syncthreads();  // the previous tile has been read out of the stage arrays
     first_tile = false;
     // (a mate owns no tiles: it begins where the problem after it does, and the last of equal starts is found)
-    int pi = sm_find(args.tile_begin, args.n_prob, L);
+    int pi = sm_find(args.tile_begin, n_prob, L);
+    if constexpr (ST > 2) {
+      if (pi) {
+        const int l2 = args.p[pi].K, l3 = args.p[pi].mate;
+        const void *l4 = args.p[pi].A, *l5 = args.p[pi].C;
+        asm volatile("" ::"s"(l2), "s"(l3), "s"(l4), "s"(l5));
+      }
+    }
     int t = L - args.tile_begin.v[pi];
-    const int per_batch = SYM ? args.p[pi].tiles_m * (args.p[pi].tiles_m + 1) / 2 : args.p[pi].tiles_m * args.p[pi].tiles_n;
-    const int mate = args.p[pi].mate;
+    const int tiles_m = args.p[pi].tiles_m, tiles_n = args.p[pi].tiles_n, mate = args.p[pi].mate;
+    const int per_batch = SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     const int per_item = mate ? 2 * per_batch : per_batch;
-    const int b = t / per_item;
+    const int b = sm_quot(args.p[pi].by_item, t);
     t -= b * per_item;
     if (t >= per_batch) {  // the mate's tile of the same item
       t -= per_batch;
       pi = mate;
     }
-    const sm_gemm_prob& P = args.p[pi];
+    const std::conditional_t<(ST > 2), sm_gemm_prob, const sm_gemm_prob&> P = args.p[pi];
     int tm, tn;
-    tile_of<SYM, (TS == 256 ? 4 : 8)>(t, P.tiles_m, P.tiles_n, tm, tn);
+    tile_of<SYM, (TS == 256 ? 4 : 8)>(t, tiles_m, tiles_n, tm, tn);
     if constexpr (KIND == 0) {
       if (P.layout == 0)
-        gemm_tile<TS, ST, false, false, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, false, true, false>(args, P, b, tm, tn, STAGES);
       else
-        gemm_tile<TS, ST, true, true, true, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, true, true, true, false>(args, P, b, tm, tn, STAGES);
     } else if constexpr (KIND == 1) {
       if (P.layout == 0)
-        gemm_tile<TS, ST, false, false, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, false, false, false>(args, P, b, tm, tn, STAGES);
       else
-        gemm_tile<TS, ST, false, true, false, false>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+        gemm_tile<TS, ST, false, true, false, false>(args, P, b, tm, tn, STAGES);
     } else if constexpr (KIND == 2) {
-      gemm_tile<TS, ST, false, false, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+      gemm_tile<TS, ST, false, false, true, true>(args, P, b, tm, tn, STAGES);
     } else {
-      gemm_tile<TS, ST, false, false, true, true, true>(args, P, b, tm, tn, sA0, sA1, sB0, sB1, sA2, sB2);
+      gemm_tile<TS, ST, false, false, true, true, true>(args, P, b, tm, tn, STAGES);
     }
   }
 }
@@ -864,7 +988,9 @@ static int fill_tiles(sm_gemm_args& args, bool sym, int ts) {
     P.tiles_n = (P.N + ts - 1) / ts;
     args.tile_begin.v[i] = total;  // for a mate: the end of its leader's range, which the tile lookup steps over
     if (is_mate[i]) continue;
-    const int n = (sym ? P.tiles_m * (P.tiles_m + 1) / 2 : P.tiles_m * P.tiles_n) * P.batch * (P.mate ? 2 : 1);
+    const int per_item = (sym ? P.tiles_m * (P.tiles_m + 1) / 2 : P.tiles_m * P.tiles_n) * (P.mate ? 2 : 1);
+    const int n = per_item * P.batch;
+    P.by_item = sm_div_by(per_item);
     total += n;
     cost += n * (P.K / 64 + FIXED);
   }
@@ -958,9 +1084,13 @@ int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
 // K = 5, two stages against three: 2048 x 2048 293 -> 234 us, 4 of 1024 x 2048 206 -> 184, 7 of 768 x 3072 (147 tiles)
 // 223 -> 196, 12 of them (252 tiles) 264 -> 262; with eight slices (25 of 512 x 512, 250 tiles) 152-161 -> 168, so
 // the line.
+// Tiles of 64 take a ring always: of four stages where they fit one round (two workgroups per CU at most: 768 x 3072
+// 92.5 us, 95.7 with three stages, 108 one k-step of fragments at a time with the shift in LDS), of three where a third
+// workgroup per CU can help (a step on 1000 x 2047 and smaller blocks, 550 tiles after the vote: 468 us, 477 with four).
 int sm_gemm_stages(const signmuon_ctx* ctx, const sm_tile_count& c) {
   const int ts = sm_gemm_tile(ctx, c);
-  return (ts == 64 || (ts == 128 && c.tiles[1] <= ctx->n_cu && c.longest > 640)) ? 3 : 2;
+  if (ts == 64) return c.tiles[0] <= ctx->n_cu ? 4 : 3;
+  return (ts == 128 && c.tiles[1] <= ctx->n_cu && c.longest > 640) ? 3 : 2;
 }
 
 // Per problem, P.layout bit 0: A is MN-contiguous, bit 1: B is MN-contiguous.  sym: symmetric
@@ -1007,17 +1137,26 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
   for (int i = 0; i < args.n_prob; ++i) tc.add(args.p[i].M, args.p[i].N, args.p[i].K, args.p[i].batch, gram);
   int ts = sm_gemm_tile(ctx, tc);
   int stages = sm_gemm_stages(ctx, tc);
-  if (args.sym_store & 3) {
+  // the forms with two stages alone have upper-block matrices, an R added to a bf16 product and a shift of A
+  bool plain_r = false;
+  for (int i = 0; i < args.n_prob; ++i) plain_r = plain_r || (args.p[i].R && !args.in_f16);
+  if ((args.sym_store & 3) || plain_r || args.a_diag != 0.f) {
     if (ts == 64) ts = 128;
     stages = 2;
   }
+  if (stages > 2 && args.in_f16 && !args.r_f16)
+    for (int i = 0; i < args.n_prob; ++i)
+      if (args.p[i].R) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: a ring adds half-precision terms");
+  for (int i = 0; stages > 2 && i < args.n_prob; ++i)
+    if (args.p[i].R && args.p[i].lda != args.p[i].ldc) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: rows of an added term");
   const int most = fill_tiles(args, gram, ts);
   if (args.total_tiles == 0) return SM_OK;
   args.reverse = ctx->gemm_flip;
   ctx->gemm_flip ^= 1;
   // persistent grid: as many workgroups per CU as fit (LDS), a multiple of 8, never more than tiles
-  int wgs = ctx->n_cu * (ts == 64 ? 3 : ts == 128 && stages == 2 ? 2 : 1);
-  wgs = std::max(1, std::min(wgs / 8, most)) * 8;
+  int wgs = ctx->n_cu * (ts == 256 ? 1 : (160 << 10) / (stages * ts * 256));
+  args.per_xcd_wgs = std::max(1, std::min(wgs / 8, most));
+  wgs = args.per_xcd_wgs * 8;
   const dim3 grid(wgs), block(ts == 64 ? tile_shape<64>::NTH : tile_shape<256>::NTH);
   if ((ctx->profiling >> klass) & 1u) {
     for (int i = 0; i < args.n_prob; ++i) {
@@ -1055,6 +1194,7 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
 #define GEMM_LAUNCH(KIND, TS, ST) hipLaunchKernelGGL((sm_ns_gemm_kernel<KIND, TS, ST>), grid, block, 0, ctx->stream, args)
 #define GEMM_TILES(KIND)                                   \
   if (ts == 256) GEMM_LAUNCH(KIND, 256, 2);                \
+  else if (ts == 64 && stages == 4) GEMM_LAUNCH(KIND, 64, 4); \
   else if (ts == 64) GEMM_LAUNCH(KIND, 64, 3);             \
   else if (stages == 3) GEMM_LAUNCH(KIND, 128, 3);         \
   else GEMM_LAUNCH(KIND, 128, 2)

@@ -497,6 +497,24 @@ def test_polar_ns_with_tiles_of_64(P, ns_path, r, c):
         ns_check(got[b], ref, f"{(r, c, ns_path)} item {b}")
 
 
+@pytest.mark.parametrize("opts", [dict(ns_store="full"), dict(ns_path="single", ns_store="full"), dict(gemm_tile=64, ns_path="single")])
+@pytest.mark.parametrize("steps", [2, 3, 5])
+@pytest.mark.parametrize("batch,s", [(1, 64), (2, 128), (1, 180), (1, 256), (3, 320), (40, 330), (1, 576)])
+def test_polar_ns_products_of_few_tiles(P, opts, steps, batch, s):
+    """Products in a ring of LDS stages, one to nine slices of K (fewer than there are stages, and every remainder by three
+    and four), with every kind of added term; 40 of 330: the three-stage ring.  Both sides of the matrix."""
+    for r, c in ((s, s + 70), (s + 70, s)):
+        x = wl.normal((batch, r, c), stream=64, block=r, worker=c)
+        xd = dev(x)
+        ctx = P.Context(**opts)
+        P.signmuon_polar_ns(ctx, xd, steps)
+        ctx.close()
+        got = xd.cpu().numpy()
+        for b in {0, batch - 1}:
+            ns_check(got[b], O.polar_ns(x[b], steps, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32),
+                     f"{(batch, r, c, steps, opts)} item {b}")
+
+
 @pytest.mark.parametrize("opts", [dict(gemm_tile=128), dict(gemm_tile=256), dict(gemm_tile=256, ns_store="full"),
                                   dict(gemm_tile=128, ns_path="stepwise")])
 @pytest.mark.parametrize("r,c", [(1152, 1408), (1408, 1152)])
