@@ -157,7 +157,8 @@ int get_plan(signmuon_ctx* ctx, int slot, int n, const int* rows, const int* col
 // ---- grouped GEMM launches over the classes of a plan
 struct gemm_params {
   float alpha = 1.f, gamma = 0.f, diag = 0.f, a_diag = 0.f, b_diag = 0.f;
-  int scale_pow = 0;
+  int scale_pow = 0, scale_mode = SM_SCALE_INV, direct = 0;
+  float eps = 0.f;
   bool sym = true;
   bool in_f16 = false, out_f16 = false, r_f16 = false;
   int sym_store = 0;  // bit 0: operands valid in their upper blocks only; bit 1: write the output that way
@@ -183,6 +184,9 @@ int launch_over_classes(signmuon_ctx* ctx, ns_plan* pl, const gemm_params& gp, i
     ga.a_diag = gp.a_diag;
     ga.b_diag = gp.b_diag;
     ga.scale_pow = gp.scale_pow;
+    ga.scale_mode = gp.scale_mode;
+    ga.eps = gp.eps;
+    ga.direct = gp.direct;
     for (int i = 0; i < g; ++i) {
       sm_gemm_prob* P = &ga.p[i * per_class];
       for (int j = 0; j < per_class; ++j) {
@@ -283,25 +287,64 @@ void small_product(ns_class& cl, sm_gemm_prob& P, const bf16_t* a, const bf16_t*
   P.mu = P.nu = P.ku = std::min(cl.rows, cl.cols);
 }
 
+// The scale of a run of steps: how the first Gram and apply of every item take 1 / sigma (SM_SCALE_*), none with pow = 0.
+struct ns_scale {
+  bool on = false;
+  int mode = SM_SCALE_INV;
+  float eps = 0.f;
+};
+
+// Where the last apply of a run of one class may write its result instead of the workspace; see sm_gemm_args::direct.
+struct ns_out {
+  void* x;
+  int direct;
+};
+
+// Sets up the scale of one problem of a Gram (pow 2) or an apply (pow 1).
+void set_scale(signmuon_ctx* ctx, ns_class& cl, sm_gemm_prob& P, gemm_params& g, const ns_scale& sc) {
+  if (!g.scale_pow) return;
+  if (g.scale_mode == SM_SCALE_VALUE) {  // a +-1 matrix: its Frobenius norm is sqrt(rows * cols)
+    P.scale_value = 1.0f / fmaxf(sqrtf((float)cl.rows * (float)cl.cols), sc.eps);
+    return;
+  }
+  P.scale = at<float>(ctx, g.scale_mode == SM_SCALE_SIG ? cl.off_sig : cl.off_inv);
+  if (g.scale_mode == SM_SCALE_PARTIAL) {
+    P.sign_out = at<void>(ctx, cl.off_partial);
+    P.sign_rows = cl.chunks;
+  }
+}
+
+void set_scale(gemm_params& g, const ns_scale& sc, bool first, int pow) {
+  g.scale_pow = (sc.on && first) ? pow : 0;
+  g.scale_mode = sc.mode;
+  if (pow == 1 && sc.mode == SM_SCALE_PARTIAL) g.scale_mode = SM_SCALE_INV;  // the Gram before has left it
+  g.eps = sc.eps;
+}
+
+void to_caller(const ns_class& cl, sm_gemm_prob& P, const ns_out& out) {
+  P.C = reinterpret_cast<bf16_t*>(out.x);
+  P.sC = (long long)cl.rows * cl.cols;
+  P.ldc = cl.cols;
+}
+
 // Step-by-step form of Alg. PolarNS: per step one Gram launch (Bm = a I + b G [+ c G^2], G the
 // Gram matrix of Y over its short side) and one apply launch (Y' = Bm Y or Y Bm) over all
 // classes; batch = count * mult per class, starting from buffer `cur` (0/1) of each class.
-// The first step carries the per-item 1 / sigma when use_scale.  Y is read in place.
-int run_ns_stepwise(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, bool use_scale,
-                    int* cur_io, const ns_sign_req* signs) {
+// The first step carries the per-item 1 / sigma.  Y is read in place.
+int run_ns_stepwise(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, const ns_scale& scale,
+                    int* cur_io, const ns_sign_req* signs, const ns_out* out) {
   int cur = *cur_io;
   const float a = coeffs[0], b = coeffs[1], c = coeffs[2];
   for (int k = 0; k < steps; ++k) {
-    const bool sc = use_scale && k == 0;
     gemm_params g;
     g.klass = SM_K_NS_GRAM;
-    g.scale_pow = sc ? 2 : 0;
+    set_scale(g, scale, k == 0, 2);
     g.alpha = (c != 0.f) ? 1.f : b;
     g.diag = (c != 0.f) ? 0.f : a;
     int rc = launch_over_classes(ctx, pl, g, 1, [&](ns_class& cl, sm_gemm_prob* P) {
       gram_of_y(cl, P[0], at<bf16_t>(ctx, cl.off_x[cur]), at<bf16_t>(ctx, (c != 0.f) ? cl.off_a : cl.off_q[0]),
                 cl.count * mult);
-      P[0].scale = sc ? at<float>(ctx, cl.off_inv) : nullptr;
+      set_scale(ctx, cl, P[0], g, scale);
     });
     if (rc != SM_OK) return rc;
     if (c != 0.f) {  // Bm = c G G^T + b G + a I   (G symmetric)
@@ -319,11 +362,14 @@ int run_ns_stepwise(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const f
     gemm_params ap;
     ap.klass = SM_K_NS_APPLY;
     ap.sym = false;
-    ap.scale_pow = sc ? 1 : 0;
+    set_scale(ap, scale, k == 0, 1);
+    const bool last = k + 1 == steps;
+    if (last && out) ap.direct = out->direct;
     rc = launch_over_classes(ctx, pl, ap, 1, [&](ns_class& cl, sm_gemm_prob* P) {
       apply_to_y(ctx, cl, P[0], at<bf16_t>(ctx, cl.off_q[0]), at<bf16_t>(ctx, cl.off_x[cur]),
-                 at<bf16_t>(ctx, cl.off_x[cur ^ 1]), cl.count * mult, (k + 1 == steps) ? signs : nullptr);
-      P[0].scale = sc ? at<float>(ctx, cl.off_inv) : nullptr;
+                 at<bf16_t>(ctx, cl.off_x[cur ^ 1]), cl.count * mult, last ? signs : nullptr);
+      set_scale(ctx, cl, P[0], ap, scale);
+      if (last && out) to_caller(cl, P[0], *out);
     });
     if (rc != SM_OK) return rc;
     cur ^= 1;
@@ -426,8 +472,8 @@ int run_chain(signmuon_ctx* ctx, ns_plan* pl, int mult, int kk, float a, float b
   return SM_OK;
 }
 
-int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, bool use_scale,
-                      int* cur_io, const ns_sign_req* signs, bool pairs) {
+int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, const ns_scale& scale,
+                      int* cur_io, const ns_sign_req* signs, const ns_out* out, bool pairs) {
   int cur = *cur_io;
   const float a = coeffs[0], b = coeffs[1];
   if (b == 0.f) return SM_EINVAL;  // run_ns routes b == 0 to the step-by-step form
@@ -444,14 +490,13 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
   int done = 0;
   while (done < steps) {
     const int kk = std::min(SM_NS_SEGMENT, steps - done);
-    const bool sc = use_scale && done == 0;
     // A_k alternates between off_a and off_q[1] (A_0 stays in off_q[0] until P_2 is formed);
     // P_k (k >= 2) alternates between off_p[0] and off_p[1]
     int ai = 0, pi = 0;
     auto a_ptr = [&](ns_class& cl, int which) { return at<bf16_t>(ctx, which == 0 ? cl.off_a : cl.off_q[1]); };
     gemm_params g;
     g.klass = SM_K_NS_GRAM;
-    g.scale_pow = sc ? 2 : 0;
+    set_scale(g, scale, done == 0, 2);
     g.out_f16 = (kk > 1);
     g.sym_store = (kk > 1) ? (chain ? 4 : ss & 2) : 0;  // A_0 is only read by the products below
     if (kk == 1) {  // only P_1 = Q_0 is needed, in bf16
@@ -460,7 +505,7 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
     }
     int rc = launch_over_classes(ctx, pl, g, 1, [&](ns_class& cl, sm_gemm_prob* P) {
       gram_of_y(cl, P[0], at<bf16_t>(ctx, cl.off_x[cur]), at<bf16_t>(ctx, cl.off_q[0]), cl.count * mult);
-      P[0].scale = sc ? at<float>(ctx, cl.off_inv) : nullptr;
+      set_scale(ctx, cl, P[0], g, scale);
     });
     if (rc != SM_OK) return rc;
     // products  Q_k X = b (A_k + (a / b) I) X  over half-precision s x s matrices; launches of few tiles as
@@ -614,12 +659,15 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
     gemm_params ap;
     ap.klass = SM_K_NS_APPLY;
     ap.sym = false;
-    ap.scale_pow = sc ? 1 : 0;
+    set_scale(ap, scale, done == 0, 1);
+    const bool last = done + kk == steps;
+    if (last && out) ap.direct = out->direct;
     rc = launch_over_classes(ctx, pl, ap, 1, [&](ns_class& cl, sm_gemm_prob* P) {
       apply_to_y(ctx, cl, P[0], at<bf16_t>(ctx, p_final < 0 ? cl.off_q[0] : cl.off_p[p_final]),
                  at<bf16_t>(ctx, cl.off_x[cur]), at<bf16_t>(ctx, cl.off_x[cur ^ 1]), cl.count * mult,
-                 (done + kk == steps) ? signs : nullptr);
-      P[0].scale = sc ? at<float>(ctx, cl.off_inv) : nullptr;
+                 last ? signs : nullptr);
+      set_scale(ctx, cl, P[0], ap, scale);
+      if (last && out) to_caller(cl, P[0], *out);
     });
     if (rc != SM_OK) return rc;
     cur ^= 1;
@@ -635,13 +683,14 @@ int run_ns_recurrence(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const
 // Option SM_OPT_NS_PATH forces the latter (SM_NS_PATH_STEPWISE) or the recurrence one step at a
 // time (SM_NS_PATH_SINGLE: three products per step), for comparisons.
 // signs (optional): the last apply also emits the packed signs.
-int run_ns(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, bool use_scale, int* cur_io,
-           const ns_sign_req* signs = nullptr) {
+// out (optional, one class): the last apply writes there, not to the workspace.
+int run_ns(signmuon_ctx* ctx, ns_plan* pl, int mult, int steps, const float* coeffs, const ns_scale& scale, int* cur_io,
+           const ns_sign_req* signs = nullptr, const ns_out* out = nullptr) {
   const bool force_stepwise = ctx->opt[SM_OPT_NS_PATH] == SM_NS_PATH_STEPWISE;
   const bool force_single = ctx->opt[SM_OPT_NS_PATH] == SM_NS_PATH_SINGLE;
   if (!force_stepwise && coeffs[2] == 0.f && coeffs[1] != 0.f && fabsf(coeffs[0]) <= 1.5f && steps >= 2)
-    return run_ns_recurrence(ctx, pl, mult, steps, coeffs, use_scale, cur_io, signs, !force_single);
-  return run_ns_stepwise(ctx, pl, mult, steps, coeffs, use_scale, cur_io, signs);
+    return run_ns_recurrence(ctx, pl, mult, steps, coeffs, scale, cur_io, signs, out, !force_single);
+  return run_ns_stepwise(ctx, pl, mult, steps, coeffs, scale, cur_io, signs, out);
 }
 
 // Spectral scale of Alg. PolarNS for every block of the plan: `items` matrices per block starting at
@@ -677,8 +726,8 @@ int spectral_sigma(signmuon_ctx* ctx, ns_plan* pl, int buf, int items, int items
 }
 
 // inv = 1 / max(sigma, eps) for `items` matrices per block of every class, in one launch.
-// mode 0: sigma from the momentum kernel's partial sums of squares; 1: sigma as left by PowerIter;
-// 2: the Frobenius norm of a +-1 matrix, sqrt(rows * cols), known in closed form.
+// mode 0: sigma from the momentum kernel's partial sums of squares; 1: sigma as left by PowerIter.  (Runs of steps take
+// their scales themselves, see ns_scale: this is for what is scaled without one.)
 int class_inv_sigma(signmuon_ctx* ctx, ns_plan* pl, int items, int mode, float eps) {
   std::vector<sm_sigma_desc> d;
   for (auto& cl : pl->classes) {
@@ -689,7 +738,6 @@ int class_inv_sigma(signmuon_ctx* ctx, ns_plan* pl, int items, int mode, float e
     D.chunks = cl.chunks;
     D.count = cl.count * items;
     D.mode = mode;
-    D.value = 1.0f / fmaxf(sqrtf((float)cl.rows * (float)cl.cols), eps);
     d.push_back(D);
   }
   return sm_launch_sigma_group(ctx, d.data(), (int)d.size(), eps);
@@ -792,23 +840,29 @@ int signmuon_polar_ns(signmuon_ctx* ctx, void* x, int dtype, int batch, int rows
   rc = sm_launch_copy_in(ctx, x, dtype, batch, rows, cols, at<bf16_t>(ctx, cl.off_x[0]), cl.cp, cl.mat,
                          scale == SM_SCALE_FRO ? at<float>(ctx, cl.off_partial) : nullptr);
   if (rc != SM_OK) return rc;
-  bool use_scale = false;
-  if (scale == SM_SCALE_FRO) {
-    rc = class_inv_sigma(ctx, pl, batch, 0, eps);
-    if (rc != SM_OK) return rc;
-    use_scale = true;
-  } else if (scale == SM_SCALE_SPECTRAL) {
+  ns_scale sc;
+  sc.on = scale != SM_SCALE_NONE;
+  sc.mode = scale == SM_SCALE_FRO ? SM_SCALE_PARTIAL : SM_SCALE_SIG;
+  sc.eps = eps;
+  if (scale == SM_SCALE_SPECTRAL) {
     rc = spectral_sigma(ctx, pl, 0, batch, batch, &v0, power_iters, eps);
     if (rc != SM_OK) return rc;
-    rc = class_inv_sigma(ctx, pl, batch, 1, eps);
-    if (rc != SM_OK) return rc;
-    use_scale = true;
   }
   int cur = 0;
-  rc = run_ns(ctx, pl, batch, steps, coeffs, use_scale, &cur);
-  if (rc != SM_OK) return rc;
-  return sm_launch_copy_out(ctx, at<bf16_t>(ctx, cl.off_x[cur]), cl.cp, cl.mat, batch, rows, cols, x, dtype,
-                            (steps == 0 && use_scale) ? at<float>(ctx, cl.off_inv) : nullptr);
+  if (steps == 0) {
+    if (sc.on) rc = class_inv_sigma(ctx, pl, batch, scale == SM_SCALE_FRO ? 0 : 1, eps);
+    if (rc != SM_OK) return rc;
+    return sm_launch_copy_out(ctx, at<bf16_t>(ctx, cl.off_x[0]), cl.cp, cl.mat, batch, rows, cols, x, dtype,
+                              sc.on ? at<float>(ctx, cl.off_inv) : nullptr);
+  }
+  // The last apply writes to x itself where rows of x are whole 16-byte pieces of the working copy's, which saves a launch
+  // and, in float32, writing and reading the bf16 result (768 x 3072 in float32: 92.5 -> 87.9 us, with the scale's launch
+  // gone as well).
+  const bool whole = cols % 8 == 0 && sm_aligned(x, 16);
+  const ns_out out{x, dtype == SM_F32 ? 2 : 1};
+  rc = run_ns(ctx, pl, batch, steps, coeffs, sc, &cur, nullptr, whole ? &out : nullptr);
+  if (rc != SM_OK || whole) return rc;
+  return sm_launch_copy_out(ctx, at<bf16_t>(ctx, cl.off_x[cur]), cl.cp, cl.mat, batch, rows, cols, x, dtype, nullptr);
 }
 
 int signmuon_sign_pack(signmuon_ctx* ctx, const void* u, int dtype, int batch, int64_t n, int fmt, void* out,
@@ -925,20 +979,19 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
   // the first GEMM launch (the Gram of Y) walks its tile ranges backwards: it starts with the blocks whose
   // bf16 copies the momentum kernel wrote last
   ctx->gemm_flip = 1;
-  // a2: sigma per (block, worker)
-  bool use_scale = false;
-  if (s->ns_steps > 0 || (s->u_out != nullptr)) {
-    if (s->scale == SM_SCALE_FRO) {
-      rc = class_inv_sigma(ctx, pl, M, 0, s->eps);
-      if (rc != SM_OK) return rc;
-      use_scale = true;
-    } else if (spectral) {
-      rc = spectral_sigma(ctx, pl, 0, M, M, s->v0, s->power_iters, s->eps);
-      if (rc != SM_OK) return rc;
-      rc = class_inv_sigma(ctx, pl, M, 1, s->eps);
-      if (rc != SM_OK) return rc;
-      use_scale = true;
-    }
+  // a2: sigma per (block, worker); the first Gram adds up the momentum kernel's partial sums, and every launch that
+  // scales takes the reciprocal itself
+  ns_scale sc;
+  sc.on = s->scale != SM_SCALE_NONE;
+  sc.mode = spectral ? SM_SCALE_SIG : SM_SCALE_PARTIAL;
+  sc.eps = s->eps;
+  if (spectral && (s->ns_steps > 0 || s->u_out != nullptr)) {
+    rc = spectral_sigma(ctx, pl, 0, M, M, s->v0, s->power_iters, s->eps);
+    if (rc != SM_OK) return rc;
+  }
+  if (sc.on && s->ns_steps == 0 && s->u_out != nullptr) {
+    rc = class_inv_sigma(ctx, pl, M, spectral ? 1 : 0, s->eps);
+    if (rc != SM_OK) return rc;
   }
 
   // a3 + a4: K Newton-Schulz steps on all (block, worker) matrices
@@ -963,7 +1016,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     for (int i = 0; i < n; ++i) sreq.write_y = sreq.write_y || (s->u_out[i] != nullptr);
   const bool fused = s->ns_steps > 0;
   int cur = 0;
-  rc = run_ns(ctx, pl, M, s->ns_steps, s->coeffs, use_scale, &cur, fused ? &sreq : nullptr);
+  rc = run_ns(ctx, pl, M, s->ns_steps, s->coeffs, sc, &cur, fused ? &sreq : nullptr);
   if (rc != SM_OK) return rc;
 
   // a5 + a6 (+ a8 when there is no local polar step): one vote launch over all blocks, after a sign-pack launch where
@@ -978,7 +1031,7 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
     const bf16_t* u = at<bf16_t>(ctx, cl.off_x[cur]) + (long long)idx * M * cl.mat;
     if (s->u_out && s->u_out[i]) {
       rc = sm_launch_copy_out(ctx, u, cl.cp, cl.mat, M, cl.rows, cl.cols, s->u_out[i], SM_BF16,
-                              (s->ns_steps == 0 && use_scale) ? at<float>(ctx, cl.off_inv) + (long long)idx * M : nullptr);
+                              (s->ns_steps == 0 && sc.on) ? at<float>(ctx, cl.off_inv) + (long long)idx * M : nullptr);
       if (rc != SM_OK) return rc;
     }
     const long long tap_stride = (s->sign_fmt == SM_SIGN_INT8) ? d : 8 * ((d + 63) / 64);
@@ -1053,26 +1106,19 @@ int signmuon_step(signmuon_ctx* ctx, const signmuon_step_args* s) {
   if (Kp == 0 && !op_norm) return SM_OK;
   // a7: local polar step on the voted sign matrices (one per block), or their operator norm for
   // the normalized-sign update (worker 0's start vector serves the voted matrix of each block)
-  bool use_scale2 = false;
-  if (op_norm) {
+  // (under the Frobenius scale every entry is +-1, so the norm is exactly sqrt(rows*cols))
+  if (op_norm || spectral) {
     rc = spectral_sigma(ctx, pl, cur ^ 1, 1, 1, s->v0, s->power_iters, s->eps);
     if (rc != SM_OK) return rc;
-    rc = class_inv_sigma(ctx, pl, 1, 1, s->eps);
-    if (rc != SM_OK) return rc;
-  } else if (s->scale == SM_SCALE_FRO) {
-    // every entry is +-1, so the Frobenius norm is exactly sqrt(rows*cols)
-    rc = class_inv_sigma(ctx, pl, 1, 2, s->eps);
-    if (rc != SM_OK) return rc;
-    use_scale2 = true;
-  } else if (spectral) {
-    rc = spectral_sigma(ctx, pl, cur ^ 1, 1, 1, s->v0, s->power_iters, s->eps);
-    if (rc != SM_OK) return rc;
-    rc = class_inv_sigma(ctx, pl, 1, 1, s->eps);
-    if (rc != SM_OK) return rc;
-    use_scale2 = true;
   }
+  if (op_norm) {
+    rc = class_inv_sigma(ctx, pl, 1, 1, s->eps);
+    if (rc != SM_OK) return rc;
+  }
+  ns_scale sc2 = sc;
+  if (!spectral) sc2.mode = SM_SCALE_VALUE;
   cur ^= 1;
-  rc = run_ns(ctx, pl, 1, Kp, s->coeffs, use_scale2, &cur);
+  rc = run_ns(ctx, pl, 1, Kp, s->coeffs, sc2, &cur);
   if (rc != SM_OK) return rc;
 
   // a8: W <- W - step * D, one launch over all blocks

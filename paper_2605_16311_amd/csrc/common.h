@@ -192,14 +192,13 @@ int sm_launch_momentum(signmuon_ctx* ctx, const sm_mom_desc* descs, int n, int M
 // sumsq[i] = sum_j partial[i*chunks + j], i < count (fixed order)
 int sm_launch_reduce_partials(signmuon_ctx* ctx, const float* partial, int chunks, int count, float* sumsq);
 // Inverse scales over a table of matrix classes, one launch: per class `count` items with
-//   mode 0: sig = sum of the item's `chunks` partial sums of squares, inv = 1 / max(sqrt(sig), eps)
-//   mode 1: inv = 1 / max(sig, eps)          mode 2: inv = value
+//   mode 0: sig (if not null) = sum of the item's `chunks` partial sums of squares, inv = 1 / max(sqrt(sig), eps)
+//   mode 1: inv = 1 / max(sig, eps)
 struct sm_sigma_desc {
   const float* partial;
   float* sig;
   float* inv;
   int chunks, count, mode;
-  float value;
 };
 constexpr int SM_SIGMA_MAX_GROUP = 64;
 int sm_launch_sigma_group(signmuon_ctx* ctx, const sm_sigma_desc* descs, int n, float eps);
@@ -286,7 +285,7 @@ struct sm_gemm_prob {
   const bf16_t* B;
   bf16_t* C;
   const bf16_t* R;       // or null
-  const float* scale;    // [batch] or null
+  float* scale;          // [batch], see sm_gemm_args::scale_mode
   long long sA, sB, sC;  // batch strides in elements (C and R share sC)
   int M, N, K;
   int lda, ldb, ldc;
@@ -297,6 +296,8 @@ struct sm_gemm_prob {
   // Optional sign output of a general (non-symmetric) bf16 product: the signs (x >= 0) of the
   // leading sign_rows x sign_ld part of C[b], packed row by row (sign_ld a multiple of 64) into
   // sign_out + b * sign_stride as in signmuon_sign_pack.  C may then be null.
+  // (A Gram launch with SM_SCALE_PARTIAL has its [batch][sign_rows] partial sums of squares here: one place for both, as
+  // a table of 24 problems just fits the kernel arguments.)
   void* sign_out;
   long long sign_stride;
   int sign_rows, sign_ld;
@@ -309,7 +310,13 @@ struct sm_gemm_prob {
   // writes zeros to the entries of C beyond mu x nu, whatever the product has there (0 * NaN where an operand is not
   // finite): the padding of the working layout reads as zero for every later call.
   int mu, nu, ku;
+  float scale_value;  // SM_SCALE_VALUE
 };
+// Inverse scale of a GEMM's item, taken by the kernel itself: a launch for it costs as much as a product of small matrices.
+constexpr int SM_SCALE_INV = 0;      // scale[b]
+constexpr int SM_SCALE_SIG = 1;      // 1 / max(scale[b], eps)
+constexpr int SM_SCALE_VALUE = 2;    // scale_value, the same for every item
+constexpr int SM_SCALE_PARTIAL = 3;  // Gram matrices: 1 / max(sqrt(sum of the item's partial sums), eps), also written to scale[b]
 constexpr int SM_GEMM_MAX_PROB = 24;
 constexpr int SM_GEMM_STARTS = 32;
 struct sm_gemm_args {
@@ -318,6 +325,9 @@ struct sm_gemm_args {
   int reverse;       // an XCD walks its range of the tile list from the end (every other launch)
   int total_tiles;
   int scale_pow;     // 0, 1 or 2
+  int scale_mode;    // SM_SCALE_*: what scale[b] of the formula is
+  float eps;
+  int direct;        // a general product writes to a caller's matrices of mu x nu (ldc = nu a multiple of 8): 1 bf16, 2 float32
   float alpha, gamma, diag;
   float a_diag, b_diag;  // 0 = none
   int in_f16, out_f16, r_f16;

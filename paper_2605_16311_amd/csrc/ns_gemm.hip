@@ -68,6 +68,9 @@ struct tile_shape {
   static constexpr int WM = TS / 2, WN = TS / (NW / 2), FM = WM / 32, FN = WN / 32, NLOAD = TS / 8 / NW;
 };
 
+// Partial sums that a thread of a Gram launch adds up at most (SM_SCALE_PARTIAL); beyond, a launch of its own is faster.
+constexpr int SUM_LOADS = 12;
+
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -259,6 +262,21 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
 #define ISSUE(st, slice) ISSUE_V(st, slice, va, ksa, vb, ksb)
   const int nk = K / BK;
 
+  // Frobenius scale of a Gram matrix in a ring: the partial sums are requested before the slices and added after them
+  constexpr bool SUMS = SYM && !F16 && ST > 2;
+  float part[SUMS ? SUM_LOADS : 1];
+  if constexpr (SUMS) {
+    if (args.scale_mode == SM_SCALE_PARTIAL) {
+      const int chunks = P.sign_rows;
+      const float* src = reinterpret_cast<const float*>(P.sign_out) + (long long)b * chunks;
+#pragma unroll
+      for (int k = 0; k < SUM_LOADS; ++k) {
+        part[k] = 0.f;
+        if (tid + k * NTH < chunks) part[k] = src[tid + k * NTH];
+      }
+    }
+  }
+
   f32x16 acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -288,8 +306,10 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   }
 #define SB() __builtin_amdgcn_sched_barrier(0)
   // wait for this wave's LDS reads and global->LDS loads, then meet the other waves
+  // (the barrier alone does not keep the compiler from moving LDS reads over it: both sides are fenced)
 #define SYNC()                                    \
   {                                               \
+    asm volatile("" ::: "memory");                \
     __builtin_amdgcn_s_waitcnt(0x0070);           \
     __builtin_amdgcn_s_barrier();                 \
     asm volatile("" ::: "memory");                \
@@ -443,6 +463,12 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
   ring_end:
     SYNC();  // every wave has its last fragments: the stages are free, but for R
     MMA2(1);
+    // The sums are in accumulation registers here, and where a jump lies between the last matrix instruction and
+    // v_accvgpr_read the compiler (clang of ROCm 7.2) has left three wait states instead of the eleven that are needed:
+    // half of the sums were those before it.
+    SB();
+    asm volatile("s_nop 15");
+    SB();
     if (with_r) {  // slice r of R is in the stage of slice nk + r
       const int at = (nk + own_slice) % ST;
       unsigned char* const last = ST > 3 ? &S3[0] : &S2[0];
@@ -567,8 +593,32 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
 
   // ---- epilogue straight from the accumulators: a lane holds row m and 4 consecutive columns
   float s = 1.f;
-  if (P.scale && args.scale_pow) {
-    s = P.scale[b];
+  if (args.scale_pow) {
+    bool have = false;
+    if constexpr (SUMS) {
+      if (args.scale_mode == SM_SCALE_PARTIAL) {
+        // each thread's sums in order, the lanes by a tree, the waves in order
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < SUM_LOADS; ++k) {
+          asm volatile("" : "+v"(part[k]));  // (added here, not where they were requested)
+          t += part[k];
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        float* red = reinterpret_cast<float*>(&S2[0]);  // free since the end of the K loop
+        if (lane == 0) red[wv] = t;
+        __syncthreads();
+        t = 0.f;
+#pragma unroll
+        for (int w = 0; w < NTH / 64; ++w) t += red[w];
+        s = 1.0f / fmaxf(sqrtf(t), args.eps);
+        if (tm == 0 && tn == 0 && tid == 0) P.scale[b] = s;  // for the apply
+        have = true;
+      }
+    }
+    if (!have) s = args.scale_mode == SM_SCALE_VALUE ? P.scale_value : P.scale[b];
+    if (args.scale_mode == SM_SCALE_SIG) s = 1.0f / fmaxf(s, args.eps);
     if (args.scale_pow == 2) s *= s;
   }
   float alpha = args.alpha * s;
@@ -748,7 +798,26 @@ __device__ __forceinline__ void gemm_tile(const sm_gemm_args& args, const sm_gem
     // set.  mu and nu stay in locals: read through P inside the loop, the arguments were copied to scratch memory, 3.9 KB
     // per lane, and that step took 7.35 instead of 6.85 ms.)
     const int mu = SYM ? M : P.mu, nu = SYM ? N : P.nu;
-    if (!SYM && (m0 + TS > mu || n0 + TS > nu)) {
+    if (!SYM && args.direct) {
+      // the caller's matrices, which a copy would otherwise fill: nothing beyond mu x nu
+#pragma unroll
+      for (int k = 0; k < PASSES; ++k) {
+        const u32x4 v = staged(k);
+        const int gr = m0 + rr + RPP * k;
+        if (gr >= mu || gc >= nu) continue;
+        const long long at = (long long)gr * P.ldc + gc;
+        if (args.direct == 1) {
+          *reinterpret_cast<u32x4*>(C + at) = v;
+        } else {
+          f32x4* o = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(P.C) + (long long)b * P.sC + at);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            o[h] = f32x4{__uint_as_float(v[2 * h] << 16), __uint_as_float(v[2 * h] & 0xFFFF0000u),
+                         __uint_as_float(v[2 * h + 1] << 16), __uint_as_float(v[2 * h + 1] & 0xFFFF0000u)};
+          }
+        }
+      }
+    } else if (!SYM && (m0 + TS > mu || n0 + TS > nu)) {
 #pragma unroll
       for (int k = 0; k < PASSES; ++k) {
         u32x4 v = staged(k);
@@ -1115,7 +1184,9 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
       if (Q.mate || Q.M != P.M || Q.N != P.N || Q.K != P.K || Q.batch != P.batch)
         return sm_fail(ctx, SM_EINVAL, "internal: GEMM mate of a different shape");
     }
-    if (P.sign_out && (sym || args.out_f16 || P.R || P.sign_ld % 64 || P.sign_stride % 8 || !sm_aligned(P.sign_out, 8) ||
+    if (args.scale_mode == SM_SCALE_PARTIAL && (!sym || args.in_f16)) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: partial sums");
+    if (args.direct && (sym || P.ldc != P.nu || P.sign_out || P.R)) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: direct output");
+    if (args.scale_mode != SM_SCALE_PARTIAL && P.sign_out && (sym || args.out_f16 || P.R || P.sign_ld % 64 || P.sign_stride % 8 || !sm_aligned(P.sign_out, 8) ||
                        (P.sign_fmt != SM_SIGN_1BIT && P.sign_fmt != SM_SIGN_INT8)))
       return sm_fail(ctx, SM_EUNSUPPORTED, "internal: GEMM sign output needs a general bf16 product and whole words per row");
     if ((args.a_diag != 0.f || args.b_diag != 0.f) && !args.in_f16)
@@ -1151,6 +1222,20 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
     if (args.p[i].R && args.p[i].lda != args.p[i].ldc) return sm_fail(ctx, SM_EUNSUPPORTED, "internal: rows of an added term");
   const int most = fill_tiles(args, gram, ts);
   if (args.total_tiles == 0) return SM_OK;
+  // the scales of a Gram launch that does not add up its partial sums itself
+  if (args.scale_mode == SM_SCALE_PARTIAL && args.scale_pow) {
+    bool own = stages > 2;
+    for (int i = 0; i < args.n_prob; ++i) own = own && args.p[i].sign_rows <= SUM_LOADS * 256;
+    if (!own) {
+      sm_sigma_desc d[SM_GEMM_MAX_PROB];
+      for (int i = 0; i < args.n_prob; ++i)
+        d[i] = sm_sigma_desc{reinterpret_cast<const float*>(args.p[i].sign_out), nullptr, args.p[i].scale, args.p[i].sign_rows,
+                             args.p[i].batch, 0};
+      const int rc = sm_launch_sigma_group(ctx, d, args.n_prob, args.eps);
+      if (rc != SM_OK) return rc;
+      args.scale_mode = SM_SCALE_INV;
+    }
+  }
   args.reverse = ctx->gemm_flip;
   ctx->gemm_flip ^= 1;
   // persistent grid: as many workgroups per CU as fit (LDS), a multiple of 8, never more than tiles
@@ -1185,7 +1270,7 @@ int sm_launch_gemm(signmuon_ctx* ctx, sm_gemm_args& args, bool sym, int klass) {
           2.0 * P.batch * (in_share * ((double)P.M * P.K + (same ? 0.0 : (double)P.N * P.K)) +
                            (double)P.M * P.N * (out_share * (P.C != nullptr) +
                                                 r_share * (P.R != nullptr && P.R != P.A && P.R != P.B))) +
-          (P.sign_out ? (double)P.batch * P.sign_stride : 0.0);
+          (args.direct == 2 ? 2.0 * P.batch * P.M * P.N : 0.0) + (!gram && P.sign_out ? (double)P.batch * P.sign_stride : 0.0);
     }
   }
   {

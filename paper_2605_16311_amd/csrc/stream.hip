@@ -153,11 +153,11 @@ __global__ void __launch_bounds__(TPB) sm_sigma_group_kernel(const sigma_args a)
     for (int j = threadIdx.x; j < D.chunks; j += TPB) s += src[j];
     const float tot = block_sum(s, red);
     if (threadIdx.x == 0) {
-      D.sig[i] = tot;
+      if (D.sig) D.sig[i] = tot;
       D.inv[i] = 1.0f / fmaxf(sqrtf(tot), a.eps);
     }
   } else if (threadIdx.x == 0) {
-    D.inv[i] = (D.mode == 1) ? 1.0f / fmaxf(D.sig[i], a.eps) : D.value;
+    D.inv[i] = 1.0f / fmaxf(D.sig[i], a.eps);
   }
 }
 

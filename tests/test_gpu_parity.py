@@ -538,6 +538,25 @@ def test_polar_ns_on_grids_of_several_tile_bands(P, opts, r, c, batch):
     ctx.close()
 
 
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("steps", [1, 5, 6])
+@pytest.mark.parametrize("batch,r,c,off", [(2, 100, 72, 0), (1, 72, 100, 0), (3, 130, 136, 0), (3, 130, 136, 2), (2, 1, 8, 0), (9, 700, 648, 0)])
+def test_polar_ns_writes_the_callers_matrix_alone(P, ctx, batch, r, c, off, steps, dt):
+    """Rows of whole 16-byte pieces, which the last apply writes itself (one to three tiles of either size), and rows or
+    starts that are not: the same result, and nothing before or behind the matrices."""
+    n = batch * r * c
+    x = dev(wl.normal((batch, r, c), stream=65, block=r, worker=c))
+    buf = torch.full((n + 96,), 7.0, device="cuda", dtype=dt)
+    buf[32 + off:32 + off + n] = x.flatten().to(dt)
+    xin = buf[32 + off:32 + off + n].clone()
+    P.signmuon_polar_ns(ctx, buf[32 + off:32 + off + n].view(batch, r, c), steps)
+    assert bool((buf[:32 + off] == 7).all()) and bool((buf[32 + off + n:] == 7).all())
+    got = buf[32 + off:32 + off + n].float().cpu().numpy().reshape(batch, r, c)
+    xin = xin.float().cpu().numpy().reshape(batch, r, c)
+    for b in {0, batch - 1}:
+        ns_check(got[b], O.polar_ns(xin[b], steps, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32), f"item {b}")
+
+
 def test_polar_ns_zero_matrix_and_errors(P, ctx):
     x = torch.zeros((2, 64, 128), dtype=torch.float32, device="cuda")
     P.signmuon_polar_ns(ctx, x, 5)
