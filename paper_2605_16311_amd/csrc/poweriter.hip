@@ -6,9 +6,8 @@
 // Matrices of up to SM_PI_FUSED_MAX_LD padded columns take the fused form: one pass over X yields both
 // u = X v and w = X^T u, because row i's share of w, u_i X_i, needs only that row's own product u_i:
 // a wave holds a row in registers, reduces u_i over its lanes and adds u_i X_i into per-lane sums.
-// The two normalisations of a round are scalars, so they are applied afterwards
-// (v' = (w / cu) / (|w / cu| + eps), cu = |u| + eps): P rounds and the final |X v| read X P + 1
-// times instead of 2 P + 1.
+// P rounds and the final |X v| read X P + 1 times instead of 2 P + 1.  The two normalisations of a round are scalars, so
+// in either form they are applied after both products (v' = (w / cu) / (|w / cu| + eps), cu = |u| + eps).
 // X is the bf16 working copy [rows][ld] with zero padding up to ld (a multiple of 64); vectors
 // and sums are fp32, u padded to a multiple of 8 and v to ld with zeros.  Every reduction runs
 // in a fixed order (no atomics), so sigma is reproducible.
@@ -205,33 +204,37 @@ __global__ void __launch_bounds__(TPB) sm_pi_fused_kernel(const pi_args a) {
   }
 }
 
-// Sum over the row chunks' partial sums of one column, in chunk order, the loads of eight chunks issued
+// Sum over chunks [first, end) of the partial sums of four columns, in chunk order, the loads of eight chunks issued
 // before the first is added.
-__device__ __forceinline__ float chunk_sum(const float* __restrict__ pp, int chunks, long long ld) {
-  float t = 0.f;
-  int ch = 0;
-  for (; ch + 8 <= chunks; ch += 8) {
-    float x[8];
+__device__ __forceinline__ f32x4 chunk_sum(const float* __restrict__ pp, int first, int end, long long ld) {
+  f32x4 t = {0.f, 0.f, 0.f, 0.f};
+  int ch = first;
+  for (; ch + 8 <= end; ch += 8) {
+    f32x4 x[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = pp[(ch + k) * ld];
+    for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const f32x4*>(pp + (ch + k) * ld);
 #pragma unroll
     for (int k = 0; k < 8; ++k) t += x[k];
   }
-  for (; ch < chunks; ++ch) t += pp[ch * ld];
+  for (; ch < end; ++ch) t += *reinterpret_cast<const f32x4*>(pp + ch * ld);
   return t;
 }
 
-// One workgroup of TPN threads per matrix.  which = 0: v <- v0 / (|v0| + eps), zero-padded to ld.
-// which = 1: u <- u / (|u| + eps).  which = 2: v <- s / (|s| + eps) with s the sum of the row chunks'
-// partial X^T u.  which = 3: sigma = |u|.  which = 4 (after a fused pass, u and the partial sums not yet
-// normalised): cu = |u| + eps, s = (sum of the chunks' partial X^T u) / cu, v <- s / (|s| + eps).
-constexpr int TPN = 1024;
-__global__ void __launch_bounds__(TPN) sm_pi_normalize_kernel(const pi_args a, int which) {
+// One workgroup of TPN threads per matrix.  PI_V0: v <- v0 / (|v0| + eps), zero-padded to ld.  PI_SIGMA: sigma = |u|.
+// PI_V: after the products of a round, u and the partial X^T u not yet normalised, cu = |u| + eps,
+// s = (sum of the partial X^T u over chunks of `chunk_rows` rows) / cu, v <- s / (|s| + eps).
+// The round's kernel is bound by the latency of its loads (one workgroup per matrix, few matrices): a thread takes four
+// columns and, of narrow matrices, a share of the chunks; what it sums stays in registers until v is written.  (One column
+// at a time through memory, 10 us, and 5 us for a launch of its own that normalised u: a step on six blocks of up to
+// 512 x 4608 with four workers, K = 1 and P = 2, 254 us; 239 so.)
+constexpr int TPN = 1024, PI_KEEP = 4;
+enum { PI_V0, PI_SIGMA, PI_V };
+__global__ void __launch_bounds__(TPN) sm_pi_normalize_kernel(const pi_args a, int which, int chunk_rows) {
   __shared__ float red[TPN / 64];
   __shared__ float nrm;
-  int local;
-  const sm_pi_desc& D = find_desc(a, blockIdx.x, local);
-  const int item = local;
+  __shared__ __attribute__((aligned(16))) f32x4 share[TPN];
+  int item;
+  const sm_pi_desc& D = find_desc(a, blockIdx.x, item);
   // sqrt of the workgroup's sum, the waves' sums added in wave order
   auto block_norm = [&](float ss) {
     ss = wave_sum(ss);
@@ -247,46 +250,71 @@ __global__ void __launch_bounds__(TPN) sm_pi_normalize_kernel(const pi_args a, i
     __syncthreads();  // red and nrm may be written again
     return r;
   };
-  const float* src;
-  float* dst;
-  int n, n_out;
-  if (which == 4) {
-    const float* uu = D.u + (long long)item * D.up;
-    float su = 0.f;
-    for (int i = threadIdx.x; i < D.rows; i += TPN) su += uu[i] * uu[i];
-    const float inv_cu = 1.0f / (block_norm(su) + a.eps);
-    const int chunks = (D.rows + SM_PI_FUSED_ROWS - 1) / SM_PI_FUSED_ROWS;
-    dst = D.v + (long long)item * D.ld;
-    const float* pp = D.part + (long long)item * chunks * D.ld;
-    for (int i = threadIdx.x; i < D.cols; i += TPN) dst[i] = chunk_sum(pp + i, chunks, D.ld) * inv_cu;
-    __syncthreads();
-    src = dst;
-    n = n_out = D.cols;
-  } else if (which == 0) {
-    src = D.v0 + (long long)item * D.v0_stride;
-    dst = D.v + (long long)item * D.ld;
-    n = D.cols;
-    n_out = D.ld;
-  } else if (which == 2) {
-    dst = D.v + (long long)item * D.ld;
-    const float* pp = D.part + (long long)item * D.chunks * D.ld;
-    for (int i = threadIdx.x; i < D.cols; i += TPN) dst[i] = chunk_sum(pp + i, D.chunks, D.ld);
-    __syncthreads();
-    src = dst;
-    n = n_out = D.cols;
-  } else {
-    src = dst = D.u + (long long)item * D.up;
-    n = n_out = D.rows;
-  }
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < n; i += TPN) ss += src[i] * src[i];
-  const float nr = block_norm(ss);
-  if (which == 3) {
+  auto norm_of = [&](const float* x, int n) {
+    float ss = 0.f;
+    for (int i = threadIdx.x; i < n; i += TPN) ss += x[i] * x[i];
+    return block_norm(ss);
+  };
+  float* v = D.v + (long long)item * D.ld;
+  const float* u = D.u + (long long)item * D.up;
+  if (which == PI_SIGMA) {
+    const float nr = norm_of(u, D.rows);
     if (threadIdx.x == 0) D.sigma[item] = nr;
     return;
   }
-  const float inv = 1.0f / (nr + a.eps);
-  for (int i = threadIdx.x; i < n_out; i += TPN) dst[i] = (i < n) ? src[i] * inv : 0.f;
+  if (which == PI_V0) {
+    const float* src = D.v0 + (long long)item * D.v0_stride;
+    const float inv = 1.0f / (norm_of(src, D.cols) + a.eps);
+    for (int i = threadIdx.x; i < D.ld; i += TPN) v[i] = (i < D.cols) ? src[i] * inv : 0.f;
+    return;
+  }
+  const int chunks = (D.rows + chunk_rows - 1) / chunk_rows, quads = D.ld / 4;
+  const float* part = D.part + (long long)item * chunks * D.ld;
+  int across = 1;  // threads side by side in a row of quads
+  while (across < quads && across < TPN) across *= 2;
+  const int shares = TPN / across, mine = threadIdx.x / across, q0 = threadIdx.x & (across - 1);
+  const int per = (chunks + shares - 1) / shares, first = min(mine * per, chunks), end = min(first + per, chunks);
+  f32x4 s[PI_KEEP];
+  // entries of four columns from 4 q on, zero beyond the matrix
+  auto live = [&](f32x4 x, int q) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = (4 * q + k < D.cols) ? x[k] : 0.f;
+    return x;
+  };
+#pragma unroll
+  for (int i = 0; i < PI_KEEP; ++i) {
+    const int q = q0 + i * across;
+    s[i] = (q < quads) ? chunk_sum(part + 4 * q, first, end, D.ld) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float inv_cu = 1.0f / (norm_of(u, D.rows) + a.eps);
+  if (shares > 1) {  // (then a thread has one quad at most)
+    share[threadIdx.x] = s[0];
+    __syncthreads();
+    if (mine == 0)
+      for (int g = 1; g < shares; ++g) s[0] += share[g * across + q0];
+  }
+  float ss = 0.f;
+  auto add = [&](f32x4 x) { ss += (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]); };
+  if (mine == 0) {
+#pragma unroll
+    for (int i = 0; i < PI_KEEP; ++i) {
+      const int q = q0 + i * across;
+      s[i] = live(s[i] * inv_cu, q);
+      add(s[i]);
+    }
+  }
+  // columns beyond what the threads keep (more than 16384) are summed twice instead
+  for (int q = threadIdx.x + PI_KEEP * TPN; q < quads; q += TPN) add(live(chunk_sum(part + 4 * q, 0, chunks, D.ld) * inv_cu, q));
+  const float inv = 1.0f / (block_norm(ss) + a.eps);
+  if (mine == 0) {
+#pragma unroll
+    for (int i = 0; i < PI_KEEP; ++i) {
+      const int q = q0 + i * across;
+      if (q < quads) *reinterpret_cast<f32x4*>(v + 4 * q) = s[i] * inv;
+    }
+  }
+  for (int q = threadIdx.x + PI_KEEP * TPN; q < quads; q += TPN)
+    *reinterpret_cast<f32x4*>(v + 4 * q) = live(chunk_sum(part + 4 * q, 0, chunks, D.ld) * inv_cu, q) * inv;
 }
 
 }  // namespace
@@ -336,15 +364,15 @@ static int power_iter_fused(signmuon_ctx* ctx, const sm_pi_desc* descs, int n, i
     if (b_nrm > 0) {
       sm_launch_scope sc(ctx, SM_K_POWER_ITER);
       auto normalize = [&](int which) {
-        hipLaunchKernelGGL(sm_pi_normalize_kernel, dim3((unsigned)b_nrm), dim3(TPN), 0, ctx->stream, a_nrm, which);
+        hipLaunchKernelGGL(sm_pi_normalize_kernel, dim3((unsigned)b_nrm), dim3(TPN), 0, ctx->stream, a_nrm, which, SM_PI_FUSED_ROWS);
       };
-      normalize(0);
+      normalize(PI_V0);
       for (int p = 0; p < P; ++p) {
         launch_fused<true>(ns, (unsigned)b_pass, ctx->stream, a_pass);
-        normalize(4);
+        normalize(PI_V);
       }
       launch_fused<false>(ns, (unsigned)b_pass, ctx->stream, a_pass);
-      normalize(3);
+      normalize(PI_SIGMA);
     }
     SM_HIP(ctx, hipGetLastError());
     done += g;
@@ -356,7 +384,7 @@ int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n
   // the fused form serves the matrices that fit its register budget; wider ones take a pass per product
   // One set of launches per strip count in use, so that narrow matrices do not run the wide kernel.  The
   // fused form saves two of five passes over X and costs more launches (7 per strip count in use instead
-  // of 10 in all): it is taken when the bytes saved outweigh them at about 10 us a launch.
+  // of 8 in all): it is taken when the bytes saved outweigh them at about 10 us a launch.
   std::vector<sm_pi_desc> wide;
   double bytes = 0.0;
   int buckets = 0;
@@ -372,7 +400,7 @@ int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n
   }
   for (int i = 0; i < n; ++i) any_wide = any_wide || descs[i].ld > SM_PI_FUSED_MAX_LD;
   const double saved_us = 2.0 * bytes / 5e6;  // two passes at about 5 TB/s
-  const double extra_us = 10.0 * (7.0 * buckets + (any_wide ? 10.0 : 0.0) - 10.0);
+  const double extra_us = 10.0 * (7.0 * buckets + (any_wide ? 8.0 : 0.0) - 8.0);
   const int mode = ctx->opt[SM_OPT_POWER_ITER];
   const bool fuse = P > 0 && buckets > 0 && mode != SM_PI_SEPARATE && (mode == SM_PI_FUSED || saved_us > extra_us);
   if (fuse) {
@@ -418,19 +446,18 @@ int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n
     if (b_nrm > 0) {
       sm_launch_scope sc(ctx, SM_K_POWER_ITER);
       auto normalize = [&](int which) {
-        hipLaunchKernelGGL(sm_pi_normalize_kernel, dim3((unsigned)b_nrm), dim3(TPN), 0, ctx->stream, a_nrm, which);
+        hipLaunchKernelGGL(sm_pi_normalize_kernel, dim3((unsigned)b_nrm), dim3(TPN), 0, ctx->stream, a_nrm, which, SM_PI_ROW_CHUNK);
       };
       auto xv = [&]() { hipLaunchKernelGGL(sm_pi_xv_kernel, dim3((unsigned)b_xv), dim3(TPB), 0, ctx->stream, a_xv); };
       auto xtu = [&]() { hipLaunchKernelGGL(sm_pi_xtu_kernel, dim3((unsigned)b_xtu), dim3(TPB), 0, ctx->stream, a_xtu); };
-      normalize(0);
+      normalize(PI_V0);
       for (int p = 0; p < P; ++p) {
         xv();
-        normalize(1);
         xtu();
-        normalize(2);
+        normalize(PI_V);
       }
       xv();
-      normalize(3);
+      normalize(PI_SIGMA);
     }
     SM_HIP(ctx, hipGetLastError());
     done += g;

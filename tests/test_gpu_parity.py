@@ -816,6 +816,21 @@ def test_step_with_normalized_sign_update(P, ctx):
                                         update_rsqrt_mn="op_norm", local_polar_steps=2))
 
 
+@pytest.mark.parametrize("mode", ["fused", "separate"])
+@pytest.mark.parametrize("batch,r,c", [(2, 9, 16500), (3, 300, 70), (1, 2050, 64), (2, 130, 4100), (1, 1, 1)])
+def test_polar_ns_spectral_scale_of_any_width(P, mode, batch, r, c):
+    """Shares of the row chunks (narrow matrices), several quads per thread, more columns than the threads keep."""
+    x = wl.normal((batch, r, c), stream=66, block=r, worker=c)
+    v0 = wl.start_vectors(batch, c, block=r)
+    ctx = P.Context(power_iter=mode)
+    xd = dev(x)
+    P.signmuon_polar_ns(ctx, xd, 1, scale="spectral", power_iters=2, eps=1e-12, v0=dev(v0))
+    ctx.close()
+    got = xd.cpu().numpy()
+    for b in range(batch):
+        ns_check(got[b], O.polar_ns(x[b], 1, O.PAPER_COEFFS, "spectral", 2, 1e-12, v0[b], dtype=np.float32), f"{(r, c)} item {b}")
+
+
 def test_step_spectral(P, vctx):
     run_step_case(P, vctx, [(128, 256), (256, 128)], 2, sign_fmt="1bit", Kp=2, scale="spectral")
 
