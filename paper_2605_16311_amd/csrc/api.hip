@@ -418,11 +418,12 @@ pair_coeffs pair_coefficients(float a, float b) {
 
 // Whether the products of a segment run as one launch of one workgroup per matrix (ns_chain.hip).  A polar factor with
 // K = 5, one launch per product against one launch, us:
-//   matrices           1          16          32          40          48          64          256
-//   128 x 128     59 / 37    62 / 38     63 / 39     64 / 39     65 / 39     66 / 40     98 / 52
-//   192 x 192     65 / 74    66 / 76     70 / 79     74 / 81     89 / 83     95 / 86    190 / 121
-//   256 x 256     68 / 78    71 / 82     85 / 86     91 / 90    110 / 94    119 / 95    280 / 155
-// so always for s <= 128, and above from 40 matrices on, where the tiles of one launch no longer fit one round.
+//   matrices           1         16         40         48         64        256
+//   128 x 128     47 / 29    49 / 29                          54 / 33    96 / 50
+//   192 x 192     52 / 60    53 / 60    62 / 63    84 / 67    88 / 71   195 / 106
+//   256 x 256     54 / 70    58 / 71    76 / 74   104 / 80   117 / 84   304 / 136
+// (the second of those of 192 and 256 with 1 and 16 matrices from 40, as a workgroup has its own matrix) so always for
+// s <= 128, and above from 40 matrices on, where the tiles of one launch no longer fit one round.
 bool chain_serves(const signmuon_ctx* ctx, const ns_plan* pl, int mult) {
   if (ctx->opt[SM_OPT_GEMM_TILE] || ctx->opt[SM_OPT_NS_STORE] == SM_NS_STORE_FULL) return false;
   int most = 0;

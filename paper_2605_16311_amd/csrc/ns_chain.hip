@@ -11,9 +11,12 @@
 // is 2 KB of row-major entries at index c (c + 1) / 2 + r; 72 KB at s = 256.  A block row of an operand is read through
 // the symmetry: block (r, k) as stored for r <= k, otherwise as the transpose of block (k, r).
 //
-// Split.  Eight waves.  The matrix is a 4 x 4 grid of super-blocks of SB x SB blocks (SB = 1 for s <= 128, 2 above);
-// six waves take a super-block above the diagonal each, two take a pair of diagonal ones (of which only the blocks on
-// and above the diagonal are computed): 4 or 6 accumulators of v_mfma_f32_32x32x16_f16 per wave.  A wave always writes
+// Split.  Ten waves.  The matrix is a 4 x 4 grid of super-blocks of SB x SB blocks (SB = 1 for s <= 128, 2 above); six
+// waves take a super-block above the diagonal each, four a diagonal one (of which only the blocks on and above the
+// diagonal are computed): 4 or 3 accumulators of v_mfma_f32_32x32x16_f16 per wave.  (Two waves with two diagonal ones
+// each were the last by far, waiting for the LDS once per three matrix instructions: 9100 cycles per product at s = 256
+// where the others took 4500.  With a test per term and not per block and term: 40 polar factors of 192 x 192, K = 5,
+// 77 -> 63 us, 256 of 256 x 256 136 -> 122.)  A wave always writes
 // the same blocks, so what it adds to a product (a multiple of A, of P or of the matrix it overwrites) it has in
 // registers or in its own blocks in LDS; the sum is taken in float32 and rounded once.
 //
@@ -25,7 +28,12 @@
 
 namespace sm_chain {
 
-constexpr int NTH = 512;
+constexpr int WAVES = 10, NTH = WAVES * 64;
+// Wave w takes super-block off_diagonal(w) of those above the diagonal, or diagonal(w): numbered so that each SIMD (w mod
+// 4) has 8 to 10 blocks at SB = 2.
+__device__ __forceinline__ bool on_diagonal(int wv) { return wv == 4 || wv == 5 || wv >= 8; }
+__device__ __forceinline__ int off_diagonal(int wv) { return wv < 4 ? wv : wv - 2; }
+__device__ __forceinline__ int diagonal(int wv) { return wv < 6 ? wv - 4 : wv - 6; }
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -65,15 +73,15 @@ struct frag_lane {
 // Blocks of a wave: NU of them, block u at (row[u], col) = (r, c), computed from its super-blocks.
 template <int SB, bool DIAG>
 struct wave_blocks {
-  static constexpr int NU = DIAG ? SB * (SB + 1) : SB * SB;
-  int I, J;  // super-block (I, J) above the diagonal, or the diagonal super-blocks I and J
+  static constexpr int NU = DIAG ? SB * (SB + 1) / 2 : SB * SB;
+  int I, J;  // super-block (I, J)
   __device__ __forceinline__ wave_blocks(int wv) {
     if (!DIAG) {
-      I = wv < 3 ? 0 : wv < 5 ? 1 : 2;
-      J = wv < 3 ? wv + 1 : wv < 5 ? wv - 1 : 3;
+      const int w = off_diagonal(wv);
+      I = w < 3 ? 0 : w < 5 ? 1 : 2;
+      J = w < 3 ? w + 1 : w < 5 ? w - 1 : 3;
     } else {
-      I = wv & 1;
-      J = 3 - I;
+      I = J = diagonal(wv);
     }
   }
   __device__ __forceinline__ void at(int u, int& r, int& c) const {
@@ -81,15 +89,14 @@ struct wave_blocks {
       r = SB * I + u / SB;
       c = SB * J + u % SB;
     } else {
-      constexpr int T = SB * (SB + 1) / 2;
-      const int w = u % T, j = w < 1 ? 0 : w < 3 ? 1 : 2, b0 = SB * (u < T ? I : J);
-      r = b0 + w - j * (j + 1) / 2;
-      c = b0 + j;
+      const int j = u < 1 ? 0 : u < 3 ? 1 : 2;
+      r = SB * I + u - j * (j + 1) / 2;
+      c = SB * I + j;
     }
   }
 };
 
-// acc = X Y for super-block (I, J), or (DIAG) for the super-blocks (I, I) and (J, J), I < J, over the whole short side.
+// acc = X Y for super-block (I, J), or (DIAG) for the super-block (I, I), over the whole short side.
 // No barrier: the operands do not change meanwhile.  Everything about a fragment's place and form (stored or
 // transposed) is fixed at compile time, so the reads run ahead of the matrix instructions; choosing the form at run
 // time put a branch and a wait for the LDS in front of every read (s = 256: 11 us per product, 7 without).
@@ -116,18 +123,15 @@ __device__ __forceinline__ void multiply_at(f32x16 (&acc)[NU], const unsigned ch
 #pragma unroll
           for (int c = 0; c < SB; ++c) MMA(r * SB + c, fa[r], fb[c]);
       } else {
+        f16x8 fa[SB], fb[SB];
 #pragma unroll
-        for (int d = 0; d < 2; ++d) {
-          f16x8 fa[SB], fb[SB];
+        for (int i = 0; i < SB; ++i) fa[i] = FRAG(X, SB * I + i, kb, ks);
 #pragma unroll
-          for (int i = 0; i < SB; ++i) fa[i] = FRAG(X, SB * (d ? J : I) + i, kb, ks);
+        for (int i = 0; i < SB; ++i) fb[i] = SQUARE ? fa[i] : FRAG(Y, SB * I + i, kb, ks);
 #pragma unroll
-          for (int i = 0; i < SB; ++i) fb[i] = SQUARE ? fa[i] : FRAG(Y, SB * (d ? J : I) + i, kb, ks);
+        for (int c = 0; c < SB; ++c)
 #pragma unroll
-          for (int c = 0; c < SB; ++c)
-#pragma unroll
-            for (int r = 0; r <= c; ++r) MMA(d * NU / 2 + c * (c + 1) / 2 + r, fa[r], fb[c]);
-        }
+          for (int r = 0; r <= c; ++r) MMA(c * (c + 1) / 2 + r, fa[r], fb[c]);
       }
     }
 #undef FRAG
@@ -137,7 +141,7 @@ __device__ __forceinline__ void multiply_at(f32x16 (&acc)[NU], const unsigned ch
 template <int SB, bool DIAG, int NU>
 __device__ __forceinline__ void multiply(f32x16 (&acc)[NU], const unsigned char* X, const unsigned char* Y, int wv, const frag_lane& fl) {
   if constexpr (!DIAG) {
-    switch (wv) {
+    switch (off_diagonal(wv)) {
       case 0: multiply_at<SB, 0, 1, false, false>(acc, X, Y, fl); break;
       case 1: multiply_at<SB, 0, 2, false, false>(acc, X, Y, fl); break;
       case 2: multiply_at<SB, 0, 3, false, false>(acc, X, Y, fl); break;
@@ -146,11 +150,19 @@ __device__ __forceinline__ void multiply(f32x16 (&acc)[NU], const unsigned char*
       default: multiply_at<SB, 2, 3, false, false>(acc, X, Y, fl);
     }
   } else if (X == Y) {
-    if (wv == 6) multiply_at<SB, 0, 3, true, true>(acc, X, Y, fl);
-    else multiply_at<SB, 1, 2, true, true>(acc, X, Y, fl);
+    switch (diagonal(wv)) {
+      case 0: multiply_at<SB, 0, 0, true, true>(acc, X, Y, fl); break;
+      case 1: multiply_at<SB, 1, 1, true, true>(acc, X, Y, fl); break;
+      case 2: multiply_at<SB, 2, 2, true, true>(acc, X, Y, fl); break;
+      default: multiply_at<SB, 3, 3, true, true>(acc, X, Y, fl);
+    }
   } else {
-    if (wv == 6) multiply_at<SB, 0, 3, true, false>(acc, X, Y, fl);
-    else multiply_at<SB, 1, 2, true, false>(acc, X, Y, fl);
+    switch (diagonal(wv)) {
+      case 0: multiply_at<SB, 0, 0, true, false>(acc, X, Y, fl); break;
+      case 1: multiply_at<SB, 1, 1, true, false>(acc, X, Y, fl); break;
+      case 2: multiply_at<SB, 2, 2, true, false>(acc, X, Y, fl); break;
+      default: multiply_at<SB, 3, 3, true, false>(acc, X, Y, fl);
+    }
   }
 }
 
@@ -221,59 +233,57 @@ __device__ __forceinline__ void chain(const chain_args& a, const chain_class& C,
       fl.init(lane);
       multiply<SB, DIAG>(acc, op.x ? L1 : L0, op.y ? L1 : L0, wv, fl);
     }
-    for_blocks([&](int u, int r, int c, int b, int fr, int fg) {
-      if (op.alpha != 1.f) {
+    // one pass over the blocks per term that there is (a test per block and term took as long as the terms)
+    if (op.alpha != 1.f) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[u][v] *= op.alpha;
-      }
-      if (op.ca != 0.f) {
+    }
+    if (op.ca != 0.f) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[u][v] = fmaf((float)A.v[u][v >> 2][v & 3], op.ca, acc[u][v]);
-      }
-      if (op.cp != 0.f) {
+    }
+    if (op.cp != 0.f) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[u][v] = fmaf((float)P.v[u][v >> 2][v & 3], op.cp, acc[u][v]);
-      }
-      if (op.cl != 0.f) {
+    }
+    if (op.cl != 0.f) {
+      for_blocks([&](int u, int, int, int b, int, int) {
 #pragma unroll
         for (int vg = 0; vg < 4; ++vg) {
           const f16x4 e = *reinterpret_cast<const f16x4*>(L1 + (b ^ (vg << 4)));
 #pragma unroll
           for (int k = 0; k < 4; ++k) acc[u][4 * vg + k] = fmaf((float)e[k], op.cl, acc[u][4 * vg + k]);
         }
-      }
-      if (op.diag != 0.f && r == c) {
+      });
+    }
+    if (DIAG && op.diag != 0.f) {
+      for_blocks([&](int u, int r, int c, int, int fr, int fg) {
+        if (r == c) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (fr == 8 * (v >> 2) + 4 * fg + (v & 3)) acc[u][v] += op.diag;
-      }
-    });
-    __syncthreads();  // every wave is done with both operands
-    if (op.put >= 0) {
-      unsigned char* L = op.put ? L1 : L0;
-      for_blocks([&](int u, int, int, int b, int, int) {
-#pragma unroll
-        for (int vg = 0; vg < 4; ++vg) {
-          const f16x4 h = {(_Float16)acc[u][4 * vg], (_Float16)acc[u][4 * vg + 1], (_Float16)acc[u][4 * vg + 2], (_Float16)acc[u][4 * vg + 3]};
-          *reinterpret_cast<f16x4*>(L + (b ^ (vg << 4))) = h;
+          for (int v = 0; v < 16; ++v)
+            if (fr == 8 * (v >> 2) + 4 * fg + (v & 3)) acc[u][v] += op.diag;
         }
       });
     }
-    if (op.keep & 1) {
+    __syncthreads();  // every wave is done with both operands
+    if (o + 1 < a.n_ops) {  // (the last result leaves from acc)
+      kept<NU> h;
 #pragma unroll
       for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int vg = 0; vg < 4; ++vg)
-          A.v[u][vg] = f16x4{(_Float16)acc[u][4 * vg], (_Float16)acc[u][4 * vg + 1], (_Float16)acc[u][4 * vg + 2], (_Float16)acc[u][4 * vg + 3]};
+          h.v[u][vg] = f16x4{(_Float16)acc[u][4 * vg], (_Float16)acc[u][4 * vg + 1], (_Float16)acc[u][4 * vg + 2], (_Float16)acc[u][4 * vg + 3]};
+      if (op.put >= 0) put(op.put ? L1 : L0, h);
+      if (op.keep & 1) A = h;
+      if (op.keep & 2) P = h;
+      if (op.put >= 0) __syncthreads();
     }
-    if (op.keep & 2) {
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int vg = 0; vg < 4; ++vg)
-          P.v[u][vg] = f16x4{(_Float16)acc[u][4 * vg], (_Float16)acc[u][4 * vg + 1], (_Float16)acc[u][4 * vg + 2], (_Float16)acc[u][4 * vg + 3]};
-    }
-    if (op.put >= 0) __syncthreads();
   }
   // the result leaves in bf16 as a whole row-major matrix; the mirrored blocks are transposed through the wave's share
   // of L0
@@ -315,7 +325,7 @@ __global__ void __launch_bounds__(NTH) sm_ns_chain_kernel(const chain_args a) {
   const unsigned char* in = C.in + at;
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(in), 0, 0x7FFFFFFF, 0x00020000);
   const int voff = (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
-  for (int L = wv; L < nb * (nb + 1); L += 8) {
+  for (int L = wv; L < nb * (nb + 1); L += WAVES) {
     const int vo = voff, so = L * 1024;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, LDS_PTR(L0 + L * 1024), 16, vo, so, 0, 0);
   }
@@ -326,8 +336,8 @@ __global__ void __launch_bounds__(NTH) sm_ns_chain_kernel(const chain_args a) {
   }
   __builtin_amdgcn_s_waitcnt(0x0070);
   __syncthreads();
-  if (wv < 6) chain<SB, false>(a, C, at, nb, L0, L1, ops);
-  else chain<SB, true>(a, C, at, nb, L0, L1, ops);
+  if (on_diagonal(wv)) chain<SB, true>(a, C, at, nb, L0, L1, ops);
+  else chain<SB, false>(a, C, at, nb, L0, L1, ops);
 }
 
 }  // namespace sm_chain
