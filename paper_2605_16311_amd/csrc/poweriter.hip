@@ -383,8 +383,9 @@ static int power_iter_fused(signmuon_ctx* ctx, const sm_pi_desc* descs, int n, i
 int sm_launch_power_iter_group(signmuon_ctx* ctx, const sm_pi_desc* descs, int n, int P, float eps) {
   // the fused form serves the matrices that fit its register budget; wider ones take a pass per product
   // One set of launches per strip count in use, so that narrow matrices do not run the wide kernel.  The
-  // fused form saves two of five passes over X and costs more launches (7 per strip count in use instead
-  // of 8 in all): it is taken when the bytes saved outweigh them at about 10 us a launch.
+  // fused form saves two of five passes over X and costs more launches (P = 2: 7 per strip count in use instead
+  // of 9 in all): it is taken when the bytes saved outweigh them at about 10 us a launch (8 are counted, which leaves the
+  // products apart where the two are close).
   std::vector<sm_pi_desc> wide;
   double bytes = 0.0;
   int buckets = 0;

@@ -101,6 +101,18 @@ def test_momentum_bit_exact(P, ctx, M, r, c, wd):
     assert np.array_equal(mom.cpu().numpy().view(np.uint32), ref2.view(np.uint32))
 
 
+@pytest.mark.parametrize("chunks", [1, 1023, 1024, 1025, 8191, 8192, 8193])
+def test_momentum_sums_of_squares(P, ctx, chunks):
+    """Edges of the sum over a worker's partial sums (of 1024 entries): 1024 threads, eight loads each at a time."""
+    M, n = 2, 1024 * chunks - 3
+    mom = torch.randn((M, 1, n), generator=torch.Generator("cuda").manual_seed(chunks), device="cuda")
+    ss = torch.empty(M, dtype=torch.float32, device="cuda")
+    P.signmuon_momentum(ctx, mom, torch.zeros_like(mom), None, 0.9, 0.0, sumsq=ss)
+    ref = mom.cpu().numpy().astype(np.float64) ** 2
+    # positive terms: at most 37 roundings of 2^-24 lie between an entry and the sum (partial 11, thread 16, trees 10)
+    assert np.allclose(ss.cpu().numpy(), ref.sum(axis=(1, 2)), rtol=37 * 2.0 ** -24, atol=0)
+
+
 # ------------------------------------------------------------------ a5
 @pytest.mark.parametrize("n", [1, 7, 8, 63, 64, 65, 1000, 4096, 65536 + 13, 300001])
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
