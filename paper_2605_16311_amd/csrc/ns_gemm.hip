@@ -1137,6 +1137,8 @@ void sm_tile_count::add(int M, int N, int K, int batch, bool sym) {
   }
 }
 
+constexpr int SM_SHORT_K = 640;  // ten slices
+
 int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
   const int opt = ctx->opt[SM_OPT_GEMM_TILE];
   if (opt) return opt;
@@ -1144,8 +1146,13 @@ int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
   // matrices fill them badly (a 384-wide matrix covers one and a half: the small tile then computes a
   // third less)
   if (c.tiles[2] >= 1024 && 4.0 * c.tiles[2] <= 1.15 * c.tiles[1]) return 256;
-  // 64 x 64 tiles while tiles of 128 would leave half of the CUs without one
-  return (c.tiles[1] <= 0.5 * ctx->n_cu) ? 64 : 128;
+  // 64 x 64 tiles while tiles of 128 would leave half of the CUs without one, and with ten slices of K or fewer, where
+  // those have two stages only, as long as three workgroups per CU take all of them in one round.  One polar factor per
+  // matrix, K = 5, us, these products in tiles of 128 against tiles of 64: 22 of 384 x 384 (462 tiles of 64) 118 -> 92, 30
+  // (630) 129 -> 118, 36 (756) 139 -> 130, 37 (777) 140 either way; 13 of 512 x 2048 (468) 167 -> 135, 21 (756) 193 -> 180;
+  // with tiles of 64 in every launch 25 (900) 208 -> 222; 13 of 640 x 640 (715) 164 -> 151.  With eleven slices and more,
+  // in every launch, 7 of 768 x 3072 (546) 179 -> 206.
+  return (c.tiles[1] <= 0.5 * ctx->n_cu || (c.longest <= SM_SHORT_K && c.tiles[0] <= 3.0 * ctx->n_cu)) ? 64 : 128;
 }
 
 // Three LDS stages (whole s x s matrices, one workgroup per CU at 128) where the tiles of 128 fit one round, so that no
@@ -1159,7 +1166,7 @@ int sm_gemm_tile(const signmuon_ctx* ctx, const sm_tile_count& c) {
 int sm_gemm_stages(const signmuon_ctx* ctx, const sm_tile_count& c) {
   const int ts = sm_gemm_tile(ctx, c);
   if (ts == 64) return c.tiles[0] <= ctx->n_cu ? 4 : 3;
-  return (ts == 128 && c.tiles[1] <= ctx->n_cu && c.longest > 640) ? 3 : 2;
+  return (ts == 128 && c.tiles[1] <= ctx->n_cu && c.longest > SM_SHORT_K) ? 3 : 2;
 }
 
 // Per problem, P.layout bit 0: A is MN-contiguous, bit 1: B is MN-contiguous.  sym: symmetric

@@ -527,6 +527,18 @@ def test_polar_ns_products_of_few_tiles(P, opts, steps, batch, s):
                      f"{(batch, r, c, steps, opts)} item {b}")
 
 
+@pytest.mark.parametrize("steps", [1, 4, 5])
+@pytest.mark.parametrize("batch,s,l", [(36, 384, 384), (37, 384, 384), (13, 640, 640), (14, 640, 640), (12, 641, 641), (24, 300, 650)])
+def test_polar_ns_around_one_round_of_short_tiles(P, ctx, batch, s, l, steps):
+    """Both sides of the lines between tiles of 64 and 128: all tiles of 64 in one round, ten slices of K and eleven."""
+    x = wl.normal((batch, s, l), stream=67, block=s, worker=l)
+    xd = dev(x)
+    P.signmuon_polar_ns(ctx, xd, steps)
+    got = xd.cpu().numpy()
+    for b in (0, batch - 1):
+        ns_check(got[b], O.polar_ns(x[b], steps, O.PAPER_COEFFS, "fro", 2, 1e-12, None, dtype=np.float32), f"{(batch, s, l)} item {b}")
+
+
 @pytest.mark.parametrize("opts", [dict(gemm_tile=128), dict(gemm_tile=256), dict(gemm_tile=256, ns_store="full"),
                                   dict(gemm_tile=128, ns_path="stepwise")])
 @pytest.mark.parametrize("r,c", [(1152, 1408), (1408, 1152)])
